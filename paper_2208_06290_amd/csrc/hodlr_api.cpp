@@ -186,7 +186,7 @@ struct hodlr_factors {
   std::vector<Tile*> d_tiles;                 // per tile level q = 0..L
   std::vector<int> ntiles;                    // per q
   std::vector<std::vector<Tile>> h_tiles;     // per q (host copy)
-  std::vector<int> tiles_aligned;             // per q: bit 0 every tile height % 16 == 0, bit 1 % 32 == 0
+  std::vector<TileShape> tile_shape;          // per q
   int64_t ldy = 0, gsy = 256;                 // Y layout: row i, column c at (i >> 8) * gsy + (i & 255) + c * ldy
   std::vector<std::vector<int>> tile_start;   // per q, 2^q + 1
   std::map<std::pair<int, int>, ProdPlan> prods;
@@ -346,7 +346,7 @@ hodlr_status plan(hodlr_factors* F) {
   const int L = F->L;
   F->d_tiles.assign(L + 1, nullptr);
   F->ntiles.assign(L + 1, 0);
-  F->tiles_aligned.assign(L + 1, 0);
+  F->tile_shape.assign(L + 1, TileShape());
   F->h_tiles.assign(L + 1, {});
   F->tile_start.assign(L + 1, {});
   std::vector<Tile> tl;
@@ -354,10 +354,11 @@ hodlr_status plan(hodlr_factors* F) {
     build_tiles(F, q, tl, F->tile_start[q]);
     F->ntiles[q] = (int)tl.size();
     F->h_tiles[q] = tl;
-    F->tiles_aligned[q] = 3;
-    for (const Tile& t : tl)
-      if (t.nrows % 16) F->tiles_aligned[q] = 0;
-      else if (t.nrows % 32) F->tiles_aligned[q] &= 1;
+    TileShape& sh = F->tile_shape[q];
+    for (const Tile& t : tl) {
+      sh.rows = std::max(sh.rows, t.nrows);
+      sh.bits |= t.nrows;
+    }
     hodlr_status s = F->mem.alloc(&F->d_tiles[q], tl.size());
     if (s) return s;
     if (hipMemcpy(F->d_tiles[q], tl.data(), tl.size() * sizeof(Tile), hipMemcpyHostToDevice) != hipSuccess)
@@ -512,7 +513,7 @@ hodlr_status run_factor(hodlr_factors* F, hipStream_t st, int bf) {
                                             F->perm, tp<T>(F->invl), U, F->ldu, Y, F->ldy, F->R, 256, F->gsy, bf)));
   if (L > 0) {
     // products V^T Y for the children of level L-1 (the leaves)
-    HL("level_pass", (launch_level_pass<T, T, S>(st, F->ntiles[L], F->d_tiles[L], F->tiles_aligned[L], Y, F->ldy, F->R,
+    HL("level_pass", (launch_level_pass<T, T, S>(st, F->ntiles[L], F->d_tiles[L], F->tile_shape[L], Y, F->ldy, F->R,
                                                  (const T*)nullptr, F->ldy, 0, (const T*)nullptr, 0, 0, 0,
                                                  V + (int64_t)F->Rp[L - 1] * F->ldv, F->ldv, F->ranks[L - 1],
                                                  tp<T>(F->P), GroupStrides{F->gsy, F->gsy, 256}, bf)));
@@ -536,13 +537,13 @@ hodlr_status run_factor(hodlr_factors* F, hipStream_t st, int bf) {
                                                 tp<T>(F->Kinv) + F->kioff[p], tp<T>(F->W), 2 * r, Rp)));
       if (p > 0 && r > 0) {
         HL("level_pass",
-           (launch_level_pass<T, T, S>(st, F->ntiles[q], F->d_tiles[q], F->tiles_aligned[q], Y, F->ldy, Rp,
+           (launch_level_pass<T, T, S>(st, F->ntiles[q], F->d_tiles[q], F->tile_shape[q], Y, F->ldy, Rp,
                                        Y + (int64_t)Rp * F->ldy, F->ldy, r, tp<T>(F->W), 2 * r, (int64_t)2 * r * Rp, 0,
                                        V + (int64_t)F->Rp[p - 1] * F->ldv, F->ldv, F->ranks[p - 1], tp<T>(F->P),
                                        GroupStrides{F->gsy, F->gsy, 256}, bf)));
       } else if (p > 0) {
         // rank-0 children: no update; products for level p still needed
-        HL("level_pass", (launch_level_pass<T, T, S>(st, F->ntiles[q], F->d_tiles[q], F->tiles_aligned[q], Y, F->ldy,
+        HL("level_pass", (launch_level_pass<T, T, S>(st, F->ntiles[q], F->d_tiles[q], F->tile_shape[q], Y, F->ldy,
                                                      Rp, (const T*)nullptr, F->ldy, 0, (const T*)nullptr, 0, 0, 0,
                                                      V + (int64_t)F->Rp[p - 1] * F->ldv, F->ldv, F->ranks[p - 1],
                                                      tp<T>(F->P), GroupStrides{F->gsy, F->gsy, 256}, bf)));
@@ -680,7 +681,7 @@ hodlr_status apply_inverse(hodlr_factors* F, Workspace& Wk, hipStream_t st, int 
     HL("leaf_solve", (launch_leaf_trsm<T, T>(st, 0, F->nleaf, F->ldl, F->d_off, tp<T>(F->lu), F->lul, F->inplace,
                                              F->perm, tp<T>(F->invl), X, ldx, X, ldx, nrhs)));
     if (L == 0) return HODLR_OK;
-    HL("solve_pass", (launch_level_pass<T, T, S>(st, F->ntiles[L], F->d_tiles[L], F->tiles_aligned[L], X, ldx, nrhs, (const T*)nullptr, N,
+    HL("solve_pass", (launch_level_pass<T, T, S>(st, F->ntiles[L], F->d_tiles[L], F->tile_shape[L], X, ldx, nrhs, (const T*)nullptr, N,
                                                  0, (const T*)nullptr, 0, 0, 0, V + (int64_t)F->Rp[L - 1] * F->ldv,
                                                  F->ldv, F->ranks[L - 1], P)));
     for (int p = L - 1; p >= 0; --p) {
@@ -698,7 +699,7 @@ hodlr_status apply_inverse(hodlr_factors* F, Workspace& Wk, hipStream_t st, int 
       }
       const int kb = p > 0 ? F->ranks[p - 1] : 0;
       if (r == 0 && kb == 0) continue;
-      HL("solve_pass", (launch_level_pass<T, T, S>(st, F->ntiles[q], F->d_tiles[q], F->tiles_aligned[q], X, ldx, nrhs,
+      HL("solve_pass", (launch_level_pass<T, T, S>(st, F->ntiles[q], F->d_tiles[q], F->tile_shape[q], X, ldx, nrhs,
                                                    Y + (int64_t)F->Rp[p] * F->ldy, F->ldy, r, w, 2 * r,
                                                    (int64_t)2 * r * nrhs, 0,
                                                    p > 0 ? V + (int64_t)F->Rp[p - 1] * F->ldv : nullptr, F->ldv, kb,
@@ -708,7 +709,7 @@ hodlr_status apply_inverse(hodlr_factors* F, Workspace& Wk, hipStream_t st, int 
   }
   // adjoint: top level first, transposed coupling solves, leaves last
   if (L > 0) {
-    HL("adjoint_pass", (launch_level_pass<T, S, T>(st, F->ntiles[1], F->d_tiles[1], F->tiles_aligned[1], X, ldx, nrhs, (const S*)nullptr,
+    HL("adjoint_pass", (launch_level_pass<T, S, T>(st, F->ntiles[1], F->d_tiles[1], F->tile_shape[1], X, ldx, nrhs, (const S*)nullptr,
                                                    N, 0, (const T*)nullptr, 0, 0, 0, Y, F->ldy, F->ranks[0], P,
                                                    GroupStrides{256, 256, F->gsy})));
     for (int p = 0; p < L; ++p) {
@@ -727,7 +728,7 @@ hodlr_status apply_inverse(hodlr_factors* F, Workspace& Wk, hipStream_t st, int 
       const int tq = q < L ? q + 1 : L;
       const int kb = q < L ? F->ranks[q] : 0;
       if (r == 0 && kb == 0) continue;
-      HL("adjoint_pass", (launch_level_pass<T, S, T>(st, F->ntiles[tq], F->d_tiles[tq], F->tiles_aligned[tq], X, ldx, nrhs,
+      HL("adjoint_pass", (launch_level_pass<T, S, T>(st, F->ntiles[tq], F->d_tiles[tq], F->tile_shape[tq], X, ldx, nrhs,
                                                      V + (int64_t)F->Rp[p] * F->ldv, F->ldv, r, w, 2 * r,
                                                      (int64_t)2 * r * nrhs, tq - q,
                                                      q < L ? Y + (int64_t)F->Rp[q] * F->ldy : nullptr, F->ldy, kb, P,
@@ -749,7 +750,7 @@ hodlr_status matvec_impl(hodlr_factors* F, hipStream_t st, int trans, int nrhs, 
   const int64_t lda = trans ? F->ldv : F->ldu, ldb = trans ? F->ldu : F->ldv;
   if (L > 0 && F->R > 0) {
     double* leaves = tree + tree_slot(L, 0) * F->R * nrhs;
-    HL("mv_project", (launch_level_pass<double, double, S>(st, F->ntiles[L], F->d_tiles[L], F->tiles_aligned[L], const_cast<double*>(X),
+    HL("mv_project", (launch_level_pass<double, double, S>(st, F->ntiles[L], F->d_tiles[L], F->tile_shape[L], const_cast<double*>(X),
                                                            ldx, nrhs, (const double*)nullptr, 0, 0,
                                                            (const double*)nullptr, 0, 0, 0, Vb, ldb, F->R, leaves)));
     for (int l = L - 1; l >= 1; --l)
@@ -1204,11 +1205,11 @@ hodlr_status grad_impl(hodlr_factors* F, Workspace& Wk, hipStream_t st, int64_t 
     double* leaves = tree + tree_slot(L, 0) * F->R * n;
     if (F->storage == HODLR_F64)
       HL("grad_project", (launch_level_pass<double, double, double>(
-                             st, F->ntiles[L], F->d_tiles[L], F->tiles_aligned[L], const_cast<double*>(Xin), ldxin, n, (const double*)nullptr,
+                             st, F->ntiles[L], F->d_tiles[L], F->tile_shape[L], const_cast<double*>(Xin), ldxin, n, (const double*)nullptr,
                              0, 0, (const double*)nullptr, 0, 0, 0, static_cast<const double*>(Mv), ldm, F->R, leaves)));
     else
       HL("grad_project", (launch_level_pass<double, double, float>(
-                             st, F->ntiles[L], F->d_tiles[L], F->tiles_aligned[L], const_cast<double*>(Xin), ldxin, n, (const double*)nullptr,
+                             st, F->ntiles[L], F->d_tiles[L], F->tile_shape[L], const_cast<double*>(Xin), ldxin, n, (const double*)nullptr,
                              0, 0, (const double*)nullptr, 0, 0, 0, static_cast<const float*>(Mv), ldm, F->R, leaves)));
     for (int l = L - 1; l >= 1; --l)
       HL("grad_tree", launch_tree_sum(st, 1 << l, (int64_t)F->R * n, tree + tree_slot(l + 1, 0) * F->R * n,
@@ -1419,7 +1420,7 @@ hodlr_status logdet_grad_impl(hodlr_factors* F, hipStream_t st, DevMem& M, void*
   // projection trees V^T Y and U^T Lam (per node, all columns)
   auto project = [&](const void* Mv, int64_t ldm, const double* Xin, double* tree) -> hodlr_status {
     double* leaves = tree + tree_slot(L, 0) * (int64_t)R * R;
-    HL("logdet_grad", (launch_level_pass<double, double, S>(st, F->ntiles[L], F->d_tiles[L], F->tiles_aligned[L],
+    HL("logdet_grad", (launch_level_pass<double, double, S>(st, F->ntiles[L], F->d_tiles[L], F->tile_shape[L],
                                                             const_cast<double*>(Xin), N, R, (const double*)nullptr, 0,
                                                             0, (const double*)nullptr, 0, 0, 0,
                                                             static_cast<const S*>(Mv), ldm, R, leaves)));

@@ -20,6 +20,14 @@ struct Tile {
   int32_t node;  // node index (0-based, left to right) at the pass's level
 };
 
+// Heights of the tiles of one level: the largest, and every bit that is set
+// in one of them.
+struct TileShape {
+  int rows = 0;
+  int bits = 0;
+  bool mult(int p) const { return bits % p == 0; }  // every height a multiple of the power of two p
+};
+
 // Segment of tiles summed by the reduction kernel.
 constexpr int kSegTiles = 16;
 
@@ -92,23 +100,21 @@ hipError_t launch_block_trsm(hipStream_t s, int trans, int nblk, int ldl, int m,
 //   product: P_tile(0:kb, 0:nz) = B1(tile, 0:kb)^T * Z(tile, 0:nz)      (if kb > 0)
 // nd = tile.node >> node_shift; W for node nd starts at W + (nd >> 1) * w_pstride + (nd & 1) * ka, ld = w_ld.
 // P_tile starts at P + tile * kb * nz, col-major ld = kb.
-// tiles_aligned: bit 0 - every tile height is a multiple of 16 (enables the fast kernel);
-// bit 1 - a multiple of 32 (4-byte Z: two rows per lane).
 // Row addressing of the Z, A1 and B1 operands: row i of an operand lives at
 // (i >> 8) * gs + (i & 255) (plus column * ld).  gs = 256 is the plain
 // column-major layout; gs = 256 * ncols with ld = 256 is the row-group blocked
 // layout (each 256-row group of all columns contiguous), valid when no tile
 // crosses a 256-row boundary.
-// bf = 1 (4-byte TZ): the products of the fast kernel take bfloat16 operands
-// with FP32 accumulation (the coupling GEMMs of a BF16 factorization); tiles
-// that need the general kernel are computed in FP32.
+// bf = 1 (4-byte TZ): the products take bfloat16 operands with FP32
+// accumulation (the coupling GEMMs of a BF16 factorization); shapes without
+// whole 16 x 16 x 16 blocks are computed in FP32.
 struct GroupStrides {
   int64_t z = 256, a = 256, b = 256;
 };
 __host__ __device__ __forceinline__ int64_t group_row(int64_t row, int64_t gs) { return (row >> 8) * gs + (row & 255); }
 
 template <typename TZ, typename SA, typename SB>
-hipError_t launch_level_pass(hipStream_t s, int ntiles, const Tile* tiles, int tiles_aligned, TZ* Z, int64_t ldz, int nz,
+hipError_t launch_level_pass(hipStream_t s, int ntiles, const Tile* tiles, TileShape shape, TZ* Z, int64_t ldz, int nz,
                              const SA* A1, int64_t lda, int ka, const TZ* W, int64_t w_ld,
                              int64_t w_pstride, int node_shift, const SB* B1, int64_t ldb, int kb, TZ* P,
                              GroupStrides gs = GroupStrides(), int bf = 0);

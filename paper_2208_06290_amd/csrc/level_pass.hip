@@ -8,12 +8,10 @@
 //            the partial sums of V^T Y (eq. "e:node1" right side and the T
 //            blocks of eq. "e:k") or of V^T x (eq. "e:node3") for the next level
 //
-// Workgroup = 256 threads = 4 waves; tile <= 256 rows (wave w owns rows
-// 64w..64w+63), one chunk of 64 columns of Z and one chunk of <= 64 columns
-// of B1; the four waves' partial products are summed in LDS in a fixed order.
-//
-// Two kernels: level_pass_fast_kernel when tile heights, ka and kb are
-// multiples of 16 (the common case), level_pass_kernel otherwise.
+// Two kernels, both 256 threads = 4 waves on a tile of <= 256 rows and a chunk
+// of <= 64 columns of Z: level_pass_block_kernel for wide Z on shapes made of
+// whole 16-row and 16-column blocks, level_pass_rows_kernel for everything
+// else (launch_level_pass has the rule).
 #include "mfma.h"
 
 #include <algorithm>
@@ -23,168 +21,356 @@ namespace hodlr {
 
 constexpr int kLpThreads = 256;
 
-// General kernel: any tile height and any sizes, with clamped loads and
-// masked values and stores.  The updated Z tile stays in the accumulator
-// registers and feeds the product directly as B operand: in the accumulator
-// layout each 4-register group holds 4 rows x 16 columns, one K-step.
-template <typename TZ, typename SA, typename SB, int MB>
-__global__ __launch_bounds__(kLpThreads, 2) void level_pass_kernel(const Tile* __restrict__ tiles, int zchunks,
-                                                                   int bchunks, TZ* Z, int64_t ldz, int nz,
-                                                                   const SA* __restrict__ A1, int64_t lda, int ka,
-                                                                   const TZ* __restrict__ W, int64_t w_ld,
-                                                                   int64_t w_pstride, int node_shift,
-                                                                   const SB* __restrict__ B1, int64_t ldb,
-                                                                   int kb_total, TZ* __restrict__ P, GroupStrides gs) {
+// N consecutive elements at any element alignment.
+template <typename S, int N>
+struct Vec {
+  typedef S type __attribute__((ext_vector_type(N), aligned(sizeof(S))));
+};
+template <typename S, typename T, int N>
+__device__ __forceinline__ void load_run(const S* p, T (&d)[N]) {
+  const typename Vec<S, N>::type v = *reinterpret_cast<const typename Vec<S, N>::type*>(p);
+#pragma unroll
+  for (int t = 0; t < N; ++t) d[t] = (T)v[t];
+}
+
+// Rows of the accumulators.  A group of 16 RP rows (RP elements are 16 bytes)
+// is RP MFMA blocks; register t of lane group lq in block h is row
+// RP (4 t + lq) + h, so for each t a lane holds 16 contiguous bytes of its
+// column and the four lane groups 64.  Lane li feeds rows
+// RP row_of_lane(li) + h as MFMA A operands: 256 contiguous bytes over the 16.
+template <typename T>
+constexpr int kRp = 16 / (int)sizeof(T);
+template <typename T>
+__device__ __forceinline__ int row_of_lane(int li) {
+  return sizeof(T) == 8 ? li : 4 * (li & 3) + (li >> 2);
+}
+
+// Resident workgroups per CU asked of the register allocator: a wave's part
+// of Z takes 4 NCB accumulators (of 4 elements), the product NCB more.
+template <typename T, int NCB, bool FULL>
+constexpr int lp_occupancy() {
+  return sizeof(T) == 8 ? (NCB >= 3 || (NCB == 2 && !FULL) ? 2 : 3) : (FULL ? 4 : 3);
+}
+
+// Row kernel (any shape).  Bound by memory latency: few MFMAs per byte for
+// narrow Z, partial blocks for ragged trees; so it keeps whole parts of Z in
+// registers and all operand loads wide and independent.  On an uneven tree
+// (N = 102846, rank 37 .. 31, FP64) the passes of a factorization take 1.62 ms
+// and those of a 3-column solve 0.25 ms (clamped element loads: 3.75 and
+// 1.02 ms).  Workgroup = 4 waves on one tile and one chunk of
+// columns of Z; a wave owns 64 rows of the tile and NCB 16-column blocks.  The
+// waves stand WR x WC = 4 over rows x columns: tiles of more than 128 rows
+// take 4 x 1, shorter ones 2 x 2 or 1 x 4, so that no wave is left without
+// rows.  A wave holds its part of Z in accumulators with lanes on columns (see
+// kRp): Z and B1 move as 16-byte accesses, and register t of an accumulator
+// is directly the B operand of one 4-row K-step of the product, whose A
+// operand is B1 read in the same layout, so neither passes through LDS.  The
+// update takes A1 straight from memory and W from LDS in fragment order (one
+// read gives a lane its values of four K-steps).  Only the waves' partial
+// products meet in LDS, 16 rows of P at a time, and are summed in a fixed
+// order.  BF (4-byte Z): four consecutive K-steps of a lane are one
+// 16 x 16 x 16 bfloat16 MFMA; W is packed when staged, A1, B1 and Z once per
+// use.
+//
+// FULL: the tile heights are multiples of 64, so a wave has 64 rows or none;
+// otherwise a wave with fewer reads its last row in the place of those past
+// the end, zeroes them in B1 and never stores them.  K is padded with zero rows of
+// W (A1 re-reads its last column).  Columns past nz and B1 columns past kb
+// re-read the last one; their results are not stored.
+template <typename TZ, typename SA, typename SB, int WC, int NCB, bool FULL, bool BF>
+__global__ __launch_bounds__(kLpThreads, (lp_occupancy<TZ, NCB, FULL>())) void level_pass_rows_kernel(
+    const Tile* __restrict__ tiles, int zchunks, int c_base, int bchunks, int kbc, TZ* Z, int64_t ldz, int nz,
+    const SA* A1, int64_t lda, int ka, const TZ* __restrict__ W, int64_t w_ld, int64_t w_pstride, int node_shift,
+    const SB* __restrict__ B1, int64_t ldb, int kb_total, TZ* __restrict__ P, GroupStrides gs, int red_off) {
   using M = Mfma<TZ>;
   using V = typename M::V;
+  constexpr int WR = 4 / WC;
+  constexpr int kCw = 16 * NCB * WC;  // columns of a chunk
+  constexpr int kWc = 16 * NCB;       // columns of a wave
+  constexpr int RP = kRp<TZ>, kGr = 16 * RP, NG = 4 / RP;  // rows of a group, groups of a wave
+  // one column block: operands of the next step are in flight while this one
+  // computes (wider parts need the registers and hide latency by their MFMAs)
+  constexpr bool PF = NCB == 1;
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  TZ* Ws = reinterpret_cast<TZ*>(smem_raw);   // update phase: W chunk [k][64]
-  TZ* red = reinterpret_cast<TZ*>(smem_raw);  // product phase: [4 waves][MB*16][64]
+  TZ* Ws = reinterpret_cast<TZ*>(smem_raw);
 
   const int lid = (int)xcd_remap(blockIdx.x, gridDim.x);  // grid < 2^31: 32-bit index math
   const int bchunk = lid % bchunks;
   const int zchunk = (lid / bchunks) % zchunks;
   const int tile = lid / (bchunks * zchunks);
   const Tile tl = tiles[tile];
-  const int nrows = tl.nrows;
-  // first row of the tile in each operand (rows inside a tile are contiguous)
-  TZ* Zt = Z + group_row(tl.row0, gs.z);
-  const SA* At = A1 ? A1 + group_row(tl.row0, gs.a) : A1;
-  const SB* Bt = B1 ? B1 + group_row(tl.row0, gs.b) : B1;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, li = lane & 15, lq = lane >> 4;
-  const int c0 = zchunk * 64;
-  const int ncb = min(4, (nz - c0 + 15) >> 4);
-  const int wr0 = 64 * w;  // first tile row of this wave
-  const int nks = (ka + 3) >> 2;
+  const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lq = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wr = w / WC, wc = w % WC;
+  const int c0 = c_base + zchunk * kCw;
+  const int wr0 = 64 * wr;                                        // first tile row of this wave
+  const int wrows = tl.nrows - wr0;                               // its rows (64 and more: 64; <= 0: none)
+  const int ng = (ka + 15) >> 4;                                  // K groups of the update
+  const int k0 = bchunk * kbc, k1 = min(kb_total, k0 + kbc);      // columns of B1
 
+  // W chunk to LDS, negated: element (k, c) of the chunk, k = 16 g + 4 q + s, in slot s of
+  // lane 16 q + c % 16 of fragment (g, c / 16)
   if (ka > 0) {
     const int nd = tl.node >> node_shift;
     const TZ* Wn = W + (int64_t)(nd >> 1) * w_pstride + (int64_t)(nd & 1) * ka;
-    for (int e = tid; e < 64 * 4 * nks; e += kLpThreads) {  // rows padded to a whole K-step with zeros
-      const int c = e % 64, k = e / 64;
-      Ws[e] = (k < ka && c0 + c < nz) ? Wn[k + (int64_t)(c0 + c) * w_ld] : TZ(0);
+    for (int e = tid; e < ng * 4 * kCw; e += kLpThreads) {
+      const int q = e & 3, c = (e >> 2) % kCw, g = e / (4 * kCw);
+      const int k = 16 * g + 4 * q;
+      const TZ* src = Wn + (int64_t)min(c0 + c, nz - 1) * w_ld;
+      TZ v[4];
+      if (k + 4 <= ka) {
+        load_run(src + k, v);
+      } else {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const TZ x = src[min(k + s, ka - 1)];
+          v[s] = k + s < ka ? x : TZ(0);
+        }
+      }
+#pragma unroll
+      for (int s = 0; s < 4; ++s) v[s] = -v[s];
+      const int slot = (g * (kCw / 16) + (c >> 4)) * 64 + 16 * q + (c & 15);
+      if constexpr (BF) {
+        reinterpret_cast<s4*>(Ws)[slot] = pack_bf16(v);
+      } else {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) Ws[slot * 4 + s] = v[s];
+      }
     }
-    __syncthreads();
   }
 
-  // loads are clamped into range and masked with a select: no branches, nothing drains the queue
-  auto load_z = [&](int rb, V (&dst)[4]) {
+  // the wave's work, with 64 rows (whole) or fewer
+  auto body = [&](auto whole_t) {
+    constexpr bool whole = decltype(whole_t)::value;
+    const int nrg = whole ? NG : FULL ? 0 : min(NG, max(0, (wrows + kGr - 1) / kGr));  // row groups
+    const int last = max(wrows - 1, 0);
+    // RP rows of a column from row r of the wave's part
+    auto load_rows = [&](const auto* col, int r, TZ (&v)[RP]) {
+      if constexpr (whole) {
+        load_run(col + r, v);
+      } else {
 #pragma unroll
-    for (int cb = 0; cb < 4; ++cb)
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int row = wr0 + 16 * rb + M::crow(lq, t);
-        const int col = c0 + 16 * cb + li;
-        const bool ok = row < nrows && col < nz;
-        const TZ v = Zt[min(row, nrows - 1) + (int64_t)min(col, nz - 1) * ldz];
-        dst[cb][t] = ok ? v : TZ(0);
+        for (int h = 0; h < RP; ++h) v[h] = (TZ)col[min(r + h, last)];
       }
-  };
+    };
+    // A1(row, 16 g + 4 lq + s) of the lane's rows
+    const SA* Aw = A1 + (ka > 0 ? group_row(tl.row0, gs.a) + wr0 : 0);
+    auto load_a = [&](int g, TZ (&av)[4][4]) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const SA* col = Aw + (int64_t)min(16 * g + 4 * lq + s, ka - 1) * lda;
+#pragma unroll
+        for (int rg = 0; rg < NG; ++rg) {
+          if (rg >= nrg) continue;
+          TZ v[RP];
+          load_rows(col, kGr * rg + RP * row_of_lane<TZ>(li), v);
+#pragma unroll
+          for (int h = 0; h < RP; ++h) av[RP * rg + h][s] = v[h];
+        }
+      }
+    };
+    // B1(rows of the lane, kr0 + li), zero in rows past the tile
+    const SB* Bw = B1 + (kb_total > 0 ? group_row(tl.row0, gs.b) + wr0 : 0);
+    auto load_b = [&](int kr0, TZ (&bv)[4][4]) {
+      const SB* col = Bw + (int64_t)min(kr0 + li, kb_total - 1) * ldb;
+#pragma unroll
+      for (int rg = 0; rg < NG; ++rg) {
+        if (rg >= nrg) continue;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const int r = kGr * rg + 4 * RP * t + RP * lq;
+          TZ v[RP];
+          load_rows(col, r, v);
+#pragma unroll
+          for (int h = 0; h < RP; ++h) bv[RP * rg + h][t] = whole || r + h <= last ? v[h] : TZ(0);
+        }
+      }
+    };
 
-  const int kc0 = bchunk * 64;
-  const int kb = kb_total > 0 ? min(64, kb_total - kc0) : 0;
-  V pacc[MB][4];
+    TZ* Zw = Z + group_row(tl.row0, gs.z) + wr0;
+    int64_t zcol[NCB];
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb)
+    for (int cb = 0; cb < NCB; ++cb) zcol[cb] = (int64_t)min(c0 + kWc * wc + 16 * cb + li, nz - 1) * ldz;
+    V acc[4][NCB];
+    TZ av[4][4];
+    if (PF && ka > 0) load_a(0, av);
 #pragma unroll
-    for (int cb = 0; cb < 4; ++cb) pacc[mb][cb] = vzero<V>();
+    for (int rg = 0; rg < NG; ++rg) {
+      if (rg >= nrg) continue;
+#pragma unroll
+      for (int cb = 0; cb < NCB; ++cb) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          TZ v[RP];
+          load_rows(Zw + zcol[cb], kGr * rg + 4 * RP * t + RP * lq, v);
+#pragma unroll
+          for (int h = 0; h < RP; ++h) acc[RP * rg + h][cb][t] = v[h];
+        }
+      }
+    }
 
-  V acc[4], nxt[4];
-  load_z(0, nxt);
-#pragma unroll
-  for (int rb = 0; rb < 4; ++rb) {
-#pragma unroll
-    for (int cb = 0; cb < 4; ++cb) acc[cb] = nxt[cb];
-    if (rb < 3) load_z(rb + 1, nxt);  // next row block in flight while this one computes
     if (ka > 0) {
-      const int row = wr0 + 16 * rb + li;
-      const int rowc = min(row, nrows - 1);
-      for (int ks = 0; ks < nks; ++ks) {
-        const int kk = 4 * ks + lq;
-        const TZ av = -(TZ)At[rowc + (int64_t)min(kk, ka - 1) * lda];
-        const TZ a = (row < nrows && kk < ka) ? av : TZ(0);
+      __syncthreads();  // W staged
+#pragma unroll 1
+      for (int g = 0; g < ng; ++g) {
+        TZ an[4][4];
+        if (PF) {
+          if (g + 1 < ng) load_a(g + 1, an);
+          else if (kb_total > 0) load_b(k0, an);
+        } else {
+          load_a(g, av);
+        }
+        if constexpr (BF) {
+          s4 ap[4];
 #pragma unroll
-        for (int cb = 0; cb < 4; ++cb)
-          acc[cb] = M::mma(a, Ws[kk * 64 + 16 * cb + li], acc[cb]);
+          for (int rb = 0; rb < 4; ++rb)
+            if (rb < RP * nrg) ap[rb] = pack_bf16(av[rb]);
+#pragma unroll
+          for (int cb = 0; cb < NCB; ++cb) {
+            const s4 wp = reinterpret_cast<const s4*>(Ws)[(g * (kCw / 16) + wc * NCB + cb) * 64 + lane];
+#pragma unroll
+            for (int rb = 0; rb < 4; ++rb)
+              if (rb < RP * nrg) acc[rb][cb] = mma_bf16(ap[rb], wp, acc[rb][cb]);
+          }
+        } else {
+#pragma unroll
+          for (int cb = 0; cb < NCB; ++cb) {
+            TZ wv[4];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) wv[s] = Ws[((g * (kCw / 16) + wc * NCB + cb) * 64 + lane) * 4 + s];
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+              for (int rb = 0; rb < 4; ++rb)
+                if (rb < RP * nrg) acc[rb][cb] = M::mma(av[rb][s], wv[s], acc[rb][cb]);
+          }
+        }
+        if (PF) {
+#pragma unroll
+          for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) av[rb][s] = an[rb][s];
+        }
       }
 #pragma unroll
-      for (int cb = 0; cb < 4; ++cb)
+      for (int cb = 0; cb < NCB; ++cb) {
+        if (c0 + kWc * wc + 16 * cb + li < nz) {
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const int rr = wr0 + 16 * rb + M::crow(lq, t);
-          const int col = c0 + 16 * cb + li;
-          if (cb < ncb && rr < nrows && col < nz) Zt[rr + (int64_t)col * ldz] = acc[cb][t];
+          for (int rg = 0; rg < NG; ++rg) {
+            if (rg >= nrg) continue;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+              const int r = kGr * rg + 4 * RP * t + RP * lq;
+              TZ* dst = Zw + zcol[cb] + r;
+              if constexpr (whole) {
+                typename Vec<TZ, RP>::type v;
+#pragma unroll
+                for (int h = 0; h < RP; ++h) v[h] = acc[RP * rg + h][cb][t];
+                *reinterpret_cast<typename Vec<TZ, RP>::type*>(dst) = v;
+              } else {
+#pragma unroll
+                for (int h = 0; h < RP; ++h)
+                  if (r + h <= last) dst[h] = acc[RP * rg + h][cb][t];
+              }
+            }
+          }
         }
-    }
-    if (kb > 0) {
-      // the accumulator register t holds exactly the B operand (4 rows x 16 columns) of one K-step
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int rr = wr0 + 16 * rb + M::crow(lq, t);
-        TZ bo[MB];
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-          const int kr = 16 * mb + li;
-          const TZ bv = (TZ)Bt[min(rr, nrows - 1) + (int64_t)(kc0 + min(kr, kb - 1)) * ldb];
-          bo[mb] = (rr < nrows && kr < kb) ? bv : TZ(0);
-        }
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-          for (int cb = 0; cb < 4; ++cb)
-            pacc[mb][cb] = M::mma(bo[mb], acc[cb][t], pacc[mb][cb]);
       }
+    } else if (PF) {
+      load_b(k0, av);
     }
-  }
 
-  if (kb > 0) {
-    constexpr int kRows = MB * 16;
-    if (ka > 0) __syncthreads();  // W chunk no longer read: its LDS becomes the reduction buffer
+    if (kb_total > 0) {
+      // 16 rows of P at a time; the waves' partials go to one of two LDS
+      // buffers in turn (the second takes the place of W, which no wave reads
+      // after the first barrier), so one barrier separates two steps
+      TZ* red[2] = {reinterpret_cast<TZ*>(smem_raw + red_off), Ws};
+      TZ* Pt = P + (int64_t)tile * kb_total * nz;
+      s4 zp[BF ? 4 : 1][NCB];  // bfloat16: Z packed once
+      if constexpr (BF) {
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
+        for (int rb = 0; rb < 4; ++rb)
 #pragma unroll
-      for (int cb = 0; cb < 4; ++cb)
+          for (int cb = 0; cb < NCB; ++cb)
+            if (rb < RP * nrg) {
+              TZ v[4];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const int kr = 16 * mb + M::crow(lq, t);
-          red[(w * kRows + kr) * 64 + 16 * cb + li] = pacc[mb][cb][t];
+              for (int t = 0; t < 4; ++t) v[t] = acc[rb][cb][t];
+              zp[rb][cb] = pack_bf16(v);
+            }
+      }
+      int buf = 0;
+#pragma unroll 1
+      for (int kr0 = k0; kr0 < k1; kr0 += 16) {
+        TZ bn[4][4];
+        if (!PF) load_b(kr0, av);
+        else if (kr0 + 16 < k1) load_b(kr0 + 16, bn);
+        V pacc[NCB];
+#pragma unroll
+        for (int cb = 0; cb < NCB; ++cb) pacc[cb] = vzero<V>();
+#pragma unroll
+        for (int rb = 0; rb < 4; ++rb) {
+          if (rb >= RP * nrg) continue;
+          if constexpr (BF) {
+            const s4 bp = pack_bf16(av[rb]);
+#pragma unroll
+            for (int cb = 0; cb < NCB; ++cb) pacc[cb] = mma_bf16(bp, zp[rb][cb], pacc[cb]);
+          } else {
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+              for (int cb = 0; cb < NCB; ++cb) pacc[cb] = M::mma(av[rb][t], acc[rb][cb][t], pacc[cb]);
+          }
         }
-    __syncthreads();
-    TZ* Pt = P + (int64_t)tile * kb_total * nz;
-    for (int e = tid; e < kb * 64; e += kLpThreads) {
-      const int kr = e % kb, cw = e / kb;
-      const int col = c0 + cw;
-      if (col < nz) {
-        TZ sum = red[(0 * kRows + kr) * 64 + cw];
-        sum += red[(1 * kRows + kr) * 64 + cw];
-        sum += red[(2 * kRows + kr) * 64 + cw];
-        sum += red[(3 * kRows + kr) * 64 + cw];
-        Pt[(kc0 + kr) + (int64_t)col * kb_total] = sum;
+        if (PF) {
+#pragma unroll
+          for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) av[rb][t] = bn[rb][t];
+        }
+        // red[buf]: [WR][16 rows of P][kCw]
+        TZ* rd = red[buf];
+        buf ^= 1;
+#pragma unroll
+        for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+          for (int t = 0; t < 4; ++t) rd[(wr * 16 + M::crow(lq, t)) * kCw + kWc * wc + 16 * cb + li] = pacc[cb][t];
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < (16 * kCw + kLpThreads - 1) / kLpThreads; ++u) {
+          const int e = tid + u * kLpThreads;
+          const int kr = kr0 + (e & 15), c = e >> 4;
+          if ((16 * kCw % kLpThreads == 0 || e < 16 * kCw) && kr < k1 && c0 + c < nz) {
+            TZ sum = rd[(e & 15) * kCw + c];
+#pragma unroll
+            for (int x = 1; x < WR; ++x) sum += rd[(x * 16 + (e & 15)) * kCw + c];
+            Pt[kr + (int64_t)(c0 + c) * kb_total] = sum;
+          }
+        }
       }
     }
-  }
+  };
+  // both sides pass the same barriers
+  if (wrows >= 64) body(std::true_type());
+  else body(std::false_type());
 }
 
-
-// Fast kernel: tile heights, ka and kb are multiples of 16 (nz is free).  The
-// update is computed transposed, Z^T -= W^T A1^T, so that the 16 lanes of a
-// row group hold 16 consecutive rows of one column of Z: every load and store
-// of Z and A1 covers whole 128-byte lines, addressed as a lane-uniform base
-// plus one 32-bit lane offset (buffer addressing).  For the product the
-// updated block is turned around through a per-wave LDS buffer (the
-// contraction runs over rows, which MFMA takes on its 4-deep K side); B1 is
-// loaded coalesced and turned around the same way.  A chunk is 16 NCB
-// columns of Z (NCB = 1 for narrow right-hand sides, else 4).  Columns past
-// nz are computed on zeros and never stored; their loads are redirected to an
-// in-range column, so no access leaves the operands.  RP = 2 (4-byte Z, tile
+// Blocked kernel for wide Z without bfloat16 (tile heights, ka and kb
+// multiples of 16, whole 16-column blocks): per (tile, 64 columns), wave w on
+// rows 64 w .. of the tile in 16 RP-row blocks.  The update is computed
+// transposed, Z^T -= W^T A1^T, so that the 16 lanes of a row group hold
+// consecutive rows of one column of Z: every load and store of Z and A1
+// covers whole 128-byte lines of four columns, addressed as a lane-uniform
+// base plus one 32-bit lane offset (buffer addressing).  For the product the
+// updated block is turned around through a per-wave LDS buffer, and B1 is
+// loaded coalesced and turned around the same way.  RP = 2 (4-byte Z, tile
 // heights multiples of 32): each lane holds two consecutive rows, loaded and
-// stored as one 8-byte access, so 16 lanes still cover a whole 128-byte line;
-// the even and the odd rows form two 16-row MFMA blocks (the product's sum
-// over rows does not depend on their order).
+// stored as one 8-byte access; the even and the odd rows form two 16-row MFMA
+// blocks (the product's sum over rows does not depend on their order).
 constexpr int kZtLd = 17;  // padded row length of the per-wave 16 x 16 turn-around buffer
 
-template <typename TZ, typename SA, typename SB, int MB, int NKS, int NCB, int MODE, int RP, bool BF, bool BLK>
-__global__ __launch_bounds__(kLpThreads, (MB > 2 || NKS > 8) ? 2 : 3) void level_pass_fast_kernel(
+template <typename TZ, typename SA, typename SB, int MB, int NKS, int NCB, int RP>
+__global__ __launch_bounds__(kLpThreads, (MB > 2 || NKS > 8) ? 2 : 3) void level_pass_block_kernel(
     const Tile* __restrict__ tiles, int zchunks, int c_base, int bchunks, TZ* Z, int64_t ldz, int nz, const SA* __restrict__ A1,
     int64_t lda, const TZ* __restrict__ W, int64_t w_ld, int64_t w_pstride, int node_shift,
     const SB* __restrict__ B1, int64_t ldb, int kb_total, TZ* __restrict__ P, GroupStrides gs) {
@@ -196,7 +382,6 @@ __global__ __launch_bounds__(kLpThreads, (MB > 2 || NKS > 8) ? 2 : 3) void level
   constexpr int kBtLd = 16 * MB + 1;
   constexpr int kWave = 16 * kZtLd + 16 * kBtLd;
   constexpr bool prod = MB > 0;
-  static_assert(MODE != 2 || NCB == 1, "a chunk with a ragged column count is one 16-column block");
   extern __shared__ __align__(16) unsigned char smem_raw[];
   TZ* Ws = reinterpret_cast<TZ*>(smem_raw);   // W chunk [ka][kCw]
   TZ* red = reinterpret_cast<TZ*>(smem_raw);  // end of the product: [2][kb][kCw]
@@ -210,7 +395,6 @@ __global__ __launch_bounds__(kLpThreads, (MB > 2 || NKS > 8) ? 2 : 3) void level
   const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lq = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: addresses stay scalar
   const int c0 = c_base + zchunk * kCw;
-  const int ncz = MODE == 0 ? kCw : min(kCw, nz - c0);  // valid columns of this chunk
   const int wr0 = 64 * w;
   const int nrb = max(0, min(4 / RP, (nrows - wr0) >> (RP == 2 ? 5 : 4)));  // 16 RP-row blocks of this wave
   const int kc0 = bchunk * 64;
@@ -220,85 +404,36 @@ __global__ __launch_bounds__(kLpThreads, (MB > 2 || NKS > 8) ? 2 : 3) void level
   if (NKS > 0) {
     const int nd = tl.node >> node_shift;
     const TZ* Wn = W + (int64_t)(nd >> 1) * w_pstride + (int64_t)(nd & 1) * ka;
-    if constexpr (BF) {
-      // W converted to bfloat16 once, as the update's A operands: element
-      // (k, c) to group k / 16, block c / 16, lane (k % 4, c % 16), slot
-      // (k / 4) % 4, so that one 8-byte read gives a lane its four values
-      __bf16* Wb = reinterpret_cast<__bf16*>(Ws);
-      for (int e = tid; e < kCw * ka; e += kLpThreads) {
-        const int c = e % kCw, k = e / kCw;
-        const TZ v = (c < ncz) ? Wn[k + (int64_t)(c0 + c) * w_ld] : TZ(0);
-        Wb[((((k >> 4) * NCB + (c >> 4)) * 4 + (k & 3)) * 16 + (c & 15)) * 4 + ((k >> 2) & 3)] = (__bf16)v;
-      }
-    } else {
-      for (int e = tid; e < kCw * ka; e += kLpThreads) {
-        const int c = e % kCw, k = e / kCw;
-        Ws[e] = (c < ncz) ? Wn[k + (int64_t)(c0 + c) * w_ld] : TZ(0);
-      }
+    for (int e = tid; e < kCw * ka; e += kLpThreads) {
+      const int c = e % kCw, k = e / kCw;
+      Ws[e] = Wn[k + (int64_t)(c0 + c) * w_ld];
     }
   }
 
-  // first row of this wave in each operand (rows inside a tile are contiguous).
-  // BLK (product-only passes whose 64-column chunk would need byte offsets
-  // past 2^31, e.g. the FP64 matvec projections at N = 2^22) takes a buffer
-  // resource per 16-column block of Z and of B1, so offsets stay below 16
-  // columns of the leading dimension; otherwise one resource per operand.
-  static_assert(!BLK || NKS == 0, "per-block resources only in product-only passes");
-  constexpr bool kBlk = BLK;
-  constexpr int kZr = kBlk ? NCB : 1;
-  constexpr int kBr = kBlk && MB > 0 ? MB : 1;
-  __amdgpu_buffer_rsrc_t zr[kZr];
-#pragma unroll
-  for (int cb = 0; cb < kZr; ++cb) {
-    // MODE 1: blocks past the valid columns re-read the last valid one
-    const int blk = !kBlk ? 0 : MODE == 1 ? min(cb, (ncz >> 4) - 1) : cb;
-    zr[cb] = buf_rsrc(Z + group_row(tl.row0, gs.z) + wr0 + (int64_t)(c0 + 16 * blk) * ldz);
-  }
+  // first row of this wave in each operand (rows inside a tile are contiguous)
+  const auto zr = buf_rsrc(Z + group_row(tl.row0, gs.z) + wr0 + (int64_t)c0 * ldz);
   const auto ar = buf_rsrc(NKS > 0 ? A1 + group_row(tl.row0, gs.a) + wr0 : A1);  // A1 / B1 are null when unused
-  __amdgpu_buffer_rsrc_t br[kBr];
-#pragma unroll
-  for (int q = 0; q < kBr; ++q)
-    br[q] = buf_rsrc(prod ? B1 + group_row(tl.row0, gs.b) + wr0 + (int64_t)(kc0 + 16 * q) * ldb : B1);
-  const uint32_t zrow = (uint32_t)(RP * li) * (uint32_t)sizeof(TZ);
-  const uint32_t zl = zrow + (uint32_t)((int64_t)M::crow_l(lq) * ldz) * (uint32_t)sizeof(TZ);
+  const auto br = buf_rsrc(prod ? B1 + group_row(tl.row0, gs.b) + wr0 + (int64_t)kc0 * ldb : B1);
+  const uint32_t zl = (uint32_t)(RP * li + (int64_t)M::crow_l(lq) * ldz) * (uint32_t)sizeof(TZ);
   const uint32_t al = (uint32_t)(RP * li + (int64_t)lq * lda) * (uint32_t)sizeof(SA);
   const uint32_t bl = (uint32_t)(RP * li + (int64_t)lq * ldb) * (uint32_t)sizeof(SB);
   constexpr uint32_t kRbRows = 16 * RP;  // rows of one row block
   // Z(16 rb + li, c0 + 16 cb + crow(lq, t)) is register t of the Z^T accumulator
-  // block cb (RP = 2: rows 32 rb + 2 li + h of block h).  The lane-uniform
-  // column part is clamped into the chunk; a lane whose own column is past nz
-  // drops its lane part and reads the clamped column instead (its value is
-  // replaced by zero).
-  // MODE 0: every column of the chunk is valid; MODE 1: the valid columns
-  // are whole 16-column blocks (later blocks re-read the last valid one, a
-  // lane-uniform clamp); MODE 2: any count (per-lane test)
-  auto zok = [&](int cb, int t) -> bool {
-    if (MODE == 0) return true;
-    if (MODE == 1) return 16 * cb < ncz;
-    return 16 * cb + M::crow_u(t) + M::crow_l(lq) < ncz;
-  };
-  // the resource of block cb and the column offset inside it
-  auto zrs = [&](int cb) { return zr[kBlk ? cb : 0]; };
+  // block cb (RP = 2: rows 32 rb + 2 li + h of block h)
   auto zso = [&](int cb, int t) -> uint32_t {
-    const int col = MODE == 0   ? 16 * cb + M::crow_u(t)
-                    : MODE == 1 ? 16 * min(cb, (ncz >> 4) - 1) + M::crow_u(t)
-                                : min(16 * cb + M::crow_u(t), ncz - 1);
-    const int base = !kBlk ? 0 : MODE == 1 ? 16 * min(cb, (ncz >> 4) - 1) : 16 * cb;
-    return (uint32_t)((int64_t)(col - base) * ldz * (int64_t)sizeof(TZ));
+    return (uint32_t)((int64_t)(16 * cb + M::crow_u(t)) * ldz * (int64_t)sizeof(TZ));
   };
-  auto zvo = [&](int rb, int cb, int t) -> uint32_t {
-    return (MODE < 2 || zok(cb, t) ? zl : zrow) + kRbRows * (uint32_t)rb * (uint32_t)sizeof(TZ);
-  };
+  auto zvo = [&](int rb) -> uint32_t { return zl + kRbRows * (uint32_t)rb * (uint32_t)sizeof(TZ); };
   auto load_z = [&](int rb, V (&d0)[NCB], V (&d1)[NCB]) {
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb)
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         TZ v0, v1 = TZ(0);
-        if (RP == 2) Buf2<TZ>::load(zrs(cb), zvo(rb, cb, t), zso(cb, t), v0, v1);
-        else v0 = Buf<TZ>::load(zrs(cb), zvo(rb, cb, t), zso(cb, t));
-        d0[cb][t] = zok(cb, t) ? v0 : TZ(0);
-        d1[cb][t] = zok(cb, t) ? v1 : TZ(0);
+        if (RP == 2) Buf2<TZ>::load(zr, zvo(rb), zso(cb, t), v0, v1);
+        else v0 = Buf<TZ>::load(zr, zvo(rb), zso(cb, t));
+        d0[cb][t] = v0;
+        d1[cb][t] = v1;
       }
   };
   // B operand of the update: -A1(row, 4 ks + lq) for the lane's row(s)
@@ -322,14 +457,10 @@ __global__ __launch_bounds__(kLpThreads, (MB > 2 || NKS > 8) ? 2 : 3) void level
     for (int i = 0; i < 4 * MB; ++i) {
       const bool ok = 4 * i < kbc;  // uniform
       const uint32_t vo = bl + kRbRows * (uint32_t)rb * (uint32_t)sizeof(SB);
-      // column 4 i (inside block i / 4 of its own resource when kBlk), or
-      // column kc0 when past the valid ones
-      const int col = ok ? (kBlk ? 4 * (i % 4) : 4 * i) : 0;
-      const uint32_t so = (uint32_t)((int64_t)col * ldb * (int64_t)sizeof(SB));
-      const auto rs = kBlk && ok ? br[kBlk ? i / 4 : 0] : br[0];
+      const uint32_t so = (uint32_t)((int64_t)(ok ? 4 * i : 0) * ldb * (int64_t)sizeof(SB));
       SB x0, x1 = SB(0);
-      if (RP == 2) Buf2<SB>::load(rs, vo, so, x0, x1);
-      else x0 = Buf<SB>::load(rs, vo, so);
+      if (RP == 2) Buf2<SB>::load(br, vo, so, x0, x1);
+      else x0 = Buf<SB>::load(br, vo, so);
       d0[i] = ok ? (TZ)x0 : TZ(0);
       d1[i] = ok ? (TZ)x1 : TZ(0);
     }
@@ -343,26 +474,11 @@ __global__ __launch_bounds__(kLpThreads, (MB > 2 || NKS > 8) ? 2 : 3) void level
 
   // update of one 16-row MFMA block, and its contribution to the product
   auto update = [&](V (&acc)[NCB], const TZ (&acur)[NKS > 0 ? NKS : 1]) {
-    if constexpr (BF) {
-      // groups of four K-steps as one bfloat16 MFMA (NKS is a multiple of 4);
-      // the row's A values are packed once per group, W was packed when staged
-      const s4* Wp = reinterpret_cast<const s4*>(Ws);
 #pragma unroll
-      for (int g = 0; g < NKS / 4; ++g) {
-        TZ av4[4];
+    for (int ks = 0; ks < NKS; ++ks)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) av4[j] = acur[4 * g + j];
-        const s4 ap = pack_bf16(av4);
-#pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) acc[cb] = mma_bf16(Wp[((g * NCB + cb) * 4 + lq) * 16 + li], ap, acc[cb]);
-      }
-    } else {
-#pragma unroll
-      for (int ks = 0; ks < NKS; ++ks)
-#pragma unroll
-        for (int cb = 0; cb < NCB; ++cb)
-          acc[cb] = M::mma(Ws[(4 * ks + lq) * kCw + 16 * cb + li], acur[ks], acc[cb]);
-    }
+      for (int cb = 0; cb < NCB; ++cb)
+        acc[cb] = M::mma(Ws[(4 * ks + lq) * kCw + 16 * cb + li], acur[ks], acc[cb]);
   };
   auto stage_b = [&](const TZ (&bcur)[MB > 0 ? 4 * MB : 1]) {
 #pragma unroll
@@ -376,35 +492,15 @@ __global__ __launch_bounds__(kLpThreads, (MB > 2 || NKS > 8) ? 2 : 3) void level
     for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb) bv[kk][mb] = bt[(4 * kk + lq) * kBtLd + 16 * mb + li];
-    // bfloat16: the B1 operands packed once for every Z block
-    s4 bp[BF && MB > 0 ? MB : 1];
-    if constexpr (BF) {
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb) {
-        TZ b4v[4];
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) b4v[kk] = bv[kk][mb];
-        bp[mb] = pack_bf16(b4v);
-      }
-    }
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) {
 #pragma unroll
       for (int t = 0; t < 4; ++t) zt[li * kZtLd + M::crow(lq, t)] = acc[cb][t];
-      if constexpr (BF) {
-        TZ zv4[4];
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) zv4[kk] = zt[(4 * kk + lq) * kZtLd + li];
-        const s4 zp = pack_bf16(zv4);
+      for (int kk = 0; kk < 4; ++kk) {
+        const TZ zv = zt[(4 * kk + lq) * kZtLd + li];
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb) pacc[mb][cb] = mma_bf16(bp[mb], zp, pacc[mb][cb]);
-      } else {
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-          const TZ zv = zt[(4 * kk + lq) * kZtLd + li];
-#pragma unroll
-          for (int mb = 0; mb < MB; ++mb) pacc[mb][cb] = M::mma(bv[kk][mb], zv, pacc[mb][cb]);
-        }
+        for (int mb = 0; mb < MB; ++mb) pacc[mb][cb] = M::mma(bv[kk][mb], zv, pacc[mb][cb]);
       }
     }
   };
@@ -428,11 +524,10 @@ __global__ __launch_bounds__(kLpThreads, (MB > 2 || NKS > 8) ? 2 : 3) void level
 #pragma unroll
       for (int cb = 0; cb < NCB; ++cb)
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
-          if (zok(cb, t)) {
-            if (RP == 2) Buf2<TZ>::store(acc0[cb][t], acc1[cb][t], zrs(cb), zvo(rb, cb, t), zso(cb, t));
-            else Buf<TZ>::store(acc0[cb][t], zrs(cb), zvo(rb, cb, t), zso(cb, t));
-          }
+        for (int t = 0; t < 4; ++t) {
+          if (RP == 2) Buf2<TZ>::store(acc0[cb][t], acc1[cb][t], zr, zvo(rb), zso(cb, t));
+          else Buf<TZ>::store(acc0[cb][t], zr, zvo(rb), zso(cb, t));
+        }
     }
     if (prod) {
       product(acc0);
@@ -472,17 +567,93 @@ __global__ __launch_bounds__(kLpThreads, (MB > 2 || NKS > 8) ? 2 : 3) void level
     TZ* Pt = P + (int64_t)tile * kb_total * nz;
     for (int e = tid; e < kb * kCw; e += kLpThreads) {
       const int kr = e % kb, cw = e / kb;
-      if (cw < ncz && kr < kbc)
+      if (kr < kbc)
         Pt[(kc0 + kr) + (int64_t)(c0 + cw) * kb_total] = red[kr * kCw + cw] + red[(kb + kr) * kCw + cw];
     }
   }
 }
 
-template <typename TZ, typename SA, typename SB, int MB, int NKS, int NCB, int MODE, int RP, bool BF, bool BLK>
-static hipError_t launch_part(hipStream_t s, int ntiles, int zchunks, int c_base, int nz, int bchunks,
-                              const Tile* tiles, TZ* Z, int64_t ldz, const SA* A1, int64_t lda, const TZ* W,
-                              int64_t w_ld, int64_t w_pstride, int node_shift, const SB* B1, int64_t ldb, int kb, TZ* P,
+
+template <typename TZ, typename SA, typename SB, int WC, int NCB, bool FULL, bool BF>
+static hipError_t launch_rows_part(hipStream_t s, int ntiles, int zchunks, int c_base, int bchunks, int kbc,
+                                   const Tile* tiles, TZ* Z, int64_t ldz, int nz, const SA* A1, int64_t lda, int ka,
+                                   const TZ* W, int64_t w_ld, int64_t w_pstride, int node_shift, const SB* B1,
+                                   int64_t ldb, int kb, TZ* P, GroupStrides gs) {
+  if (zchunks == 0) return hipSuccess;
+  constexpr int WR = 4 / WC, kCw = 16 * NCB * WC;
+  const size_t red = kb > 0 ? sizeof(TZ) * WR * 16 * kCw : 0;
+  const size_t wsz = std::max(red, (BF ? 2 : sizeof(TZ)) * (size_t)kCw * ((ka + 15) & ~15));
+  const int64_t grid = (int64_t)ntiles * zchunks * bchunks;
+  if (grid > 0x7fffffff) return hipErrorInvalidValue;
+  auto k = level_pass_rows_kernel<TZ, SA, SB, WC, NCB, FULL, BF>;
+  hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(wsz + red));
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(kLpThreads), wsz + red, s, tiles, zchunks, c_base, bchunks, kbc, Z,
+                     ldz, nz, A1, lda, ka, W, w_ld, w_pstride, node_shift, B1, ldb, kb, P, gs, (int)wsz);
+  return hipGetLastError();
+}
+
+// Columns c_base .. nz of Z in chunks of 64, then the rest as one narrower
+// chunk, so that (up to 15 columns) no wave works on columns that do not exist.
+template <typename TZ, typename SA, typename SB, int WC, bool FULL, bool BF>
+static hipError_t launch_rows_chunks(hipStream_t s, int ntiles, int c_base, const Tile* tiles, TZ* Z, int64_t ldz,
+                                     int nz, const SA* A1, int64_t lda, int ka, const TZ* W, int64_t w_ld,
+                                     int64_t w_pstride, int node_shift, const SB* B1, int64_t ldb, int kb, TZ* P,
+                                     GroupStrides gs) {
+  // product-only passes have no update to repeat: their B1 columns are split
+  // over workgroups too
+  const int kbc = ka > 0 ? std::max(kb, 1) : 64;
+  const int bchunks = kb > 0 ? (kb + kbc - 1) / kbc : 1;
+  const int n64 = (nz - c_base) / 64, rest = ((nz - c_base) % 64 + 15) / 16;
+  hipError_t e = hipSuccess;
+#define HODLR_LPR(NCBV, CHUNKS, BASE)                                                                                \
+  e = launch_rows_part<TZ, SA, SB, WC, NCBV, FULL, BF>(s, ntiles, CHUNKS, BASE, bchunks, kbc, tiles, Z, ldz, nz, A1, \
+                                                       lda, ka, W, w_ld, w_pstride, node_shift, B1, ldb, kb, P, gs)
+  HODLR_LPR(4 / WC, n64, c_base);
+  if (e != hipSuccess || rest == 0) return e;
+  const int base = c_base + 64 * n64;
+  if constexpr (WC == 1) {
+    if (rest == 1) HODLR_LPR(1, 1, base);
+    else if (rest == 2) HODLR_LPR(2, 1, base);
+    else if (rest == 3) HODLR_LPR(3, 1, base);
+    else HODLR_LPR(4, 1, base);
+  } else if constexpr (WC == 2) {
+    if (rest <= 2) HODLR_LPR(1, 1, base);
+    else HODLR_LPR(2, 1, base);
+  } else {
+    HODLR_LPR(1, 1, base);
+  }
+#undef HODLR_LPR
+  return e;
+}
+
+template <typename TZ, typename SA, typename SB, bool BF>
+static hipError_t launch_rows(hipStream_t s, int ntiles, int c_base, const Tile* tiles, TileShape sh, TZ* Z,
+                              int64_t ldz, int nz, const SA* A1, int64_t lda, int ka, const TZ* W, int64_t w_ld,
+                              int64_t w_pstride, int node_shift, const SB* B1, int64_t ldb, int kb, TZ* P,
                               GroupStrides gs) {
+#define HODLR_LPS(WCV)                                                                                             \
+  return sh.mult(64) ? launch_rows_chunks<TZ, SA, SB, WCV, true, BF>(s, ntiles, c_base, tiles, Z, ldz, nz, A1, lda, \
+                                                                     ka, W, w_ld, w_pstride, node_shift, B1, ldb,   \
+                                                                     kb, P, gs)                                     \
+                     : launch_rows_chunks<TZ, SA, SB, WCV, false, BF>(s, ntiles, c_base, tiles, Z, ldz, nz, A1, lda, \
+                                                                      ka, W, w_ld, w_pstride, node_shift, B1, ldb,  \
+                                                                      kb, P, gs)
+  // waves over columns only where every one of them has 16 columns of its own
+  // (a projection of one vector on 128-row tiles: 333 us with two waves on the
+  // same 16 columns, 231 us with those two idle)
+  const int cols = nz - c_base;
+  if (sh.rows <= 64 && cols > 32) HODLR_LPS(4);
+  if (sh.rows <= 128 && cols > 16) HODLR_LPS(2);
+  HODLR_LPS(1);
+#undef HODLR_LPS
+}
+
+template <typename TZ, typename SA, typename SB, int MB, int NKS, int NCB, int RP>
+static hipError_t launch_block_part(hipStream_t s, int ntiles, int zchunks, int c_base, int nz, int bchunks,
+                                    const Tile* tiles, TZ* Z, int64_t ldz, const SA* A1, int64_t lda, const TZ* W,
+                                    int64_t w_ld, int64_t w_pstride, int node_shift, const SB* B1, int64_t ldb, int kb,
+                                    TZ* P, GroupStrides gs) {
   if (zchunks == 0) return hipSuccess;
   constexpr int kCw = 16 * NCB;
   const size_t smem_main = sizeof(TZ) * (kCw * 4 * (size_t)NKS + 4 * (16 * kZtLd + 16 * (16 * MB + 1)));
@@ -490,7 +661,7 @@ static hipError_t launch_part(hipStream_t s, int ntiles, int zchunks, int c_base
   const size_t smem = smem_main > smem_red ? smem_main : smem_red;
   const int64_t grid = (int64_t)ntiles * zchunks * bchunks;
   if (grid > 0x7fffffff) return hipErrorInvalidValue;
-  auto k = level_pass_fast_kernel<TZ, SA, SB, MB, NKS, NCB, MODE, RP, BF, BLK>;
+  auto k = level_pass_block_kernel<TZ, SA, SB, MB, NKS, NCB, RP>;
   hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(kLpThreads), smem, s, tiles, zchunks, c_base, bchunks, Z, ldz, nz,
@@ -498,42 +669,35 @@ static hipError_t launch_part(hipStream_t s, int ntiles, int zchunks, int c_base
   return hipGetLastError();
 }
 
-// Columns of Z in up to three launches: chunks of 64, then the whole 16-column
-// blocks that are left as one narrower chunk, then a last partial block
-// (per-lane column test).  Every launch computes only columns that exist.
-template <typename TZ, typename SA, typename SB, int MB, int NKS, int RP, bool BF, bool BLK>
-static hipError_t launch_fast(hipStream_t s, int ntiles, int nz, int bchunks, const Tile* tiles, TZ* Z, int64_t ldz,
-                              const SA* A1, int64_t lda, const TZ* W, int64_t w_ld, int64_t w_pstride,
-                              int node_shift, const SB* B1, int64_t ldb, int kb, TZ* P, GroupStrides gs) {
-  const int n64 = nz / 64, nb = (nz % 64) / 16, tail = nz % 16;
-  hipError_t e = launch_part<TZ, SA, SB, MB, NKS, 4, 0, RP, BF, BLK>(s, ntiles, n64, 0, nz, bchunks, tiles, Z, ldz, A1, lda, W,
-                                                         w_ld, w_pstride, node_shift, B1, ldb, kb, P, gs);
+// The first nblk 16-column blocks of Z: chunks of 64 columns, then the blocks
+// that are left as one narrower chunk.
+template <typename TZ, typename SA, typename SB, int MB, int NKS, int RP>
+static hipError_t launch_block_chunks(hipStream_t s, int ntiles, int nblk, int nz, int bchunks, const Tile* tiles,
+                                      TZ* Z, int64_t ldz, const SA* A1, int64_t lda, const TZ* W, int64_t w_ld,
+                                      int64_t w_pstride, int node_shift, const SB* B1, int64_t ldb, int kb, TZ* P,
+                                      GroupStrides gs) {
+  const int n64 = nblk / 4, nb = nblk % 4;
+  hipError_t e = launch_block_part<TZ, SA, SB, MB, NKS, 4, RP>(s, ntiles, n64, 0, nz, bchunks, tiles, Z, ldz, A1, lda,
+                                                               W, w_ld, w_pstride, node_shift, B1, ldb, kb, P, gs);
   if (e != hipSuccess) return e;
-  const int cb = 64 * n64;
-#define HODLR_LPB(NCBV)                                                                                          \
-  e = launch_part<TZ, SA, SB, MB, NKS, NCBV, 0, RP, BF, BLK>(s, ntiles, 1, cb, nz, bchunks, tiles, Z, ldz, A1, lda, W, w_ld,  \
-                                                 w_pstride, node_shift, B1, ldb, kb, P, gs)
+#define HODLR_LPB(NCBV)                                                                                            \
+  return launch_block_part<TZ, SA, SB, MB, NKS, NCBV, RP>(s, ntiles, 1, 64 * n64, nz, bchunks, tiles, Z, ldz, A1,   \
+                                                          lda, W, w_ld, w_pstride, node_shift, B1, ldb, kb, P, gs)
   if (nb == 1) HODLR_LPB(1);
-  else if (nb == 2) HODLR_LPB(2);
-  else if (nb == 3) HODLR_LPB(3);
+  if (nb == 2) HODLR_LPB(2);
+  if (nb == 3) HODLR_LPB(3);
 #undef HODLR_LPB
-  if (e != hipSuccess) return e;
-  return launch_part<TZ, SA, SB, MB, NKS, 1, 2, RP, BF, BLK>(s, ntiles, tail ? 1 : 0, cb + 16 * nb, nz, bchunks, tiles, Z, ldz, A1,
-                                                lda, W, w_ld, w_pstride, node_shift, B1, ldb, kb, P, gs);
+  return e;
 }
 
-template <typename TZ, typename SA, typename SB, int MB, int RP, bool BF, bool BLK>
-static hipError_t launch_fast_nks(int nks, hipStream_t s, int ntiles, int nz, int bchunks, const Tile* tiles, TZ* Z,
-                                  int64_t ldz, const SA* A1, int64_t lda, const TZ* W, int64_t w_ld,
-                                  int64_t w_pstride, int node_shift, const SB* B1, int64_t ldb, int kb, TZ* P,
-                                  GroupStrides gs) {
-#define HODLR_LPF(NKSV)                                                                                       \
-  return launch_fast<TZ, SA, SB, MB, NKSV, RP, BF, BLK>(s, ntiles, nz, bchunks, tiles, Z, ldz, A1, lda, W, w_ld, w_pstride,      \
-                                                 node_shift, B1, ldb, kb, P, gs)
-  if constexpr (BLK) {  // product-only
-    if (nks != 0) return hipErrorInvalidValue;
-    HODLR_LPF(0);
-  } else {
+template <typename TZ, typename SA, typename SB, int MB, int RP>
+static hipError_t launch_block_nks(int nks, hipStream_t s, int ntiles, int nblk, int nz, int bchunks,
+                                   const Tile* tiles, TZ* Z, int64_t ldz, const SA* A1, int64_t lda, const TZ* W,
+                                   int64_t w_ld, int64_t w_pstride, int node_shift, const SB* B1, int64_t ldb, int kb,
+                                   TZ* P, GroupStrides gs) {
+#define HODLR_LPF(NKSV)                                                                                            \
+  return launch_block_chunks<TZ, SA, SB, MB, NKSV, RP>(s, ntiles, nblk, nz, bchunks, tiles, Z, ldz, A1, lda, W, w_ld, \
+                                                       w_pstride, node_shift, B1, ldb, kb, P, gs)
   switch (nks) {
     case 0: HODLR_LPF(0);
     case 4: HODLR_LPF(4);
@@ -541,19 +705,17 @@ static hipError_t launch_fast_nks(int nks, hipStream_t s, int ntiles, int nz, in
     case 12: HODLR_LPF(12);
     default: HODLR_LPF(16);
   }
-  }
 #undef HODLR_LPF
 }
 
-template <typename TZ, typename SA, typename SB, int RP, bool BF, bool BLK = false>
-static hipError_t launch_fast_all(hipStream_t s, int ntiles, const Tile* tiles, TZ* Z, int64_t ldz, int nz,
-                                  const SA* A1, int64_t lda, int ka, const TZ* W, int64_t w_ld, int64_t w_pstride,
-                                  int node_shift, const SB* B1, int64_t ldb, int kb, TZ* P, GroupStrides gs) {
+template <typename TZ, typename SA, typename SB, int RP>
+static hipError_t launch_block(hipStream_t s, int ntiles, const Tile* tiles, TZ* Z, int64_t ldz, int nblk, int nz,
+                               const SA* A1, int64_t lda, int ka, const TZ* W, int64_t w_ld, int64_t w_pstride,
+                               int node_shift, const SB* B1, int64_t ldb, int kb, TZ* P, GroupStrides gs) {
   const int bchunks = kb > 0 ? (kb + 63) / 64 : 1;
-  const int nks = ka / 4;
-#define HODLR_LPM(MBV)                                                                                            \
-  return launch_fast_nks<TZ, SA, SB, MBV, RP, BF, BLK>(nks, s, ntiles, nz, bchunks, tiles, Z, ldz, A1, lda, W, w_ld,           \
-                                                w_pstride, node_shift, B1, ldb, kb, P, gs)
+#define HODLR_LPM(MBV)                                                                                              \
+  return launch_block_nks<TZ, SA, SB, MBV, RP>(ka / 4, s, ntiles, nblk, nz, bchunks, tiles, Z, ldz, A1, lda, W, w_ld, \
+                                               w_pstride, node_shift, B1, ldb, kb, P, gs)
   switch (kb > 0 ? std::min(kb, 64) / 16 : 0) {
     case 0: HODLR_LPM(0);
     case 1: HODLR_LPM(1);
@@ -565,74 +727,62 @@ static hipError_t launch_fast_all(hipStream_t s, int ntiles, const Tile* tiles, 
 }
 
 template <typename TZ, typename SA, typename SB>
-hipError_t launch_level_pass(hipStream_t s, int ntiles, const Tile* tiles, int tiles_aligned, TZ* Z, int64_t ldz,
-                             int nz, const SA* A1, int64_t lda, int ka, const TZ* W, int64_t w_ld,
-                             int64_t w_pstride, int node_shift, const SB* B1, int64_t ldb, int kb, TZ* P,
-                             GroupStrides gs, int bf) {
+hipError_t launch_level_pass(hipStream_t s, int ntiles, const Tile* tiles, TileShape sh, TZ* Z, int64_t ldz, int nz,
+                             const SA* A1, int64_t lda, int ka, const TZ* W, int64_t w_ld, int64_t w_pstride,
+                             int node_shift, const SB* B1, int64_t ldb, int kb, TZ* P, GroupStrides gs, int bf) {
   if (ntiles == 0 || nz == 0 || (ka == 0 && kb == 0)) return hipSuccess;
-  const int zchunks = (nz + 63) / 64;
-  const int bchunks = kb > 0 ? (kb + 63) / 64 : 1;
-  if (ka > 0 && bchunks > 1) return hipErrorInvalidValue;  // an update must run once per element
-  if (ka > 64) return hipErrorInvalidValue;
-  const int64_t grid = (int64_t)ntiles * zchunks * bchunks;
-  if (grid > 0x7fffffff) return hipErrorInvalidValue;
-  // byte offsets inside a 64-column chunk must stay below 2^31 for the buffer
-  // addressing; product-only passes may instead address 16-column blocks
-  const bool small_ld = 64 * ldz * (int64_t)sizeof(TZ) < (1ll << 31) && 64 * lda * (int64_t)sizeof(SA) < (1ll << 31) &&
-                        64 * ldb * (int64_t)sizeof(SB) < (1ll << 31);
-  const bool block_ld = ka == 0 && 16 * ldz * (int64_t)sizeof(TZ) < (1ll << 31) &&
-                        16 * ldb * (int64_t)sizeof(SB) < (1ll << 31);
-  if ((tiles_aligned & 1) && !small_ld && block_ld && kb % 16 == 0)
-    return launch_fast_all<TZ, SA, SB, 1, false, true>(s, ntiles, tiles, Z, ldz, nz, A1, lda, ka, W, w_ld, w_pstride,
-                                                       node_shift, B1, ldb, kb, P, gs);
-  if ((tiles_aligned & 1) && small_ld && ka % 16 == 0 && kb % 16 == 0) {
-    if constexpr (sizeof(TZ) == 4) {
-      // 4-byte elements, tile heights multiples of 32, even leading dimensions and
-      // 16-byte aligned operands (every paired access is naturally aligned): two rows per lane
-      auto al16 = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
-      const bool pair_ok = ldz % 2 == 0 && (ka == 0 || lda % 2 == 0) && (kb == 0 || ldb % 2 == 0) && al16(Z) &&
-                           (ka == 0 || al16(A1)) && (kb == 0 || al16(B1));
-      // bfloat16 products only where the factorization uses them (Z and A1 both Y)
-      constexpr bool kBf = std::is_same<SA, TZ>::value;
-      if ((tiles_aligned & 2) && pair_ok) {
-        if (kBf && bf)
-          return launch_fast_all<TZ, SA, SB, 2, true>(s, ntiles, tiles, Z, ldz, nz, A1, lda, ka, W, w_ld, w_pstride,
-                                                      node_shift, B1, ldb, kb, P, gs);
-        return launch_fast_all<TZ, SA, SB, 2, false>(s, ntiles, tiles, Z, ldz, nz, A1, lda, ka, W, w_ld, w_pstride,
-                                                     node_shift, B1, ldb, kb, P, gs);
-      }
-      if (kBf && bf)
-        return launch_fast_all<TZ, SA, SB, 1, true>(s, ntiles, tiles, Z, ldz, nz, A1, lda, ka, W, w_ld, w_pstride,
-                                                    node_shift, B1, ldb, kb, P, gs);
+  if (ka > 64 || sh.rows < 1 || sh.rows > kTileRows) return hipErrorInvalidValue;
+  // whole 16 x 16 x 16 blocks, and byte offsets inside a 64-column chunk below
+  // 2^31 (the buffer addressing of the blocked kernel)
+  const bool blocks = sh.mult(16) && ka % 16 == 0 && kb % 16 == 0 && 64 * ldz * (int64_t)sizeof(TZ) < (1ll << 31) &&
+                      64 * lda * (int64_t)sizeof(SA) < (1ll << 31) && 64 * ldb * (int64_t)sizeof(SB) < (1ll << 31);
+  int c_base = 0;
+  if (blocks) {
+    // bfloat16 products only where the factorization uses them (Z and A1 both
+    // Y), where the row kernel moves 16 bytes a lane and nothing but W and P
+    // through LDS (N = 2^19, rank 64: 5.69 ms a factorization, 6.67 ms with the
+    // turn-arounds of the blocked kernel); other shapes of a BF16
+    // factorization are computed in FP32
+    if constexpr (sizeof(TZ) == 4 && std::is_same<SA, TZ>::value) {
+      if (bf)
+        return launch_rows<TZ, SA, SB, true>(s, ntiles, 0, tiles, sh, Z, ldz, nz, A1, lda, ka, W, w_ld, w_pstride,
+                                             node_shift, B1, ldb, kb, P, gs);
     }
-    return launch_fast_all<TZ, SA, SB, 1, false>(s, ntiles, tiles, Z, ldz, nz, A1, lda, ka, W, w_ld, w_pstride,
-                                                 node_shift, B1, ldb, kb, P, gs);
+    // the blocked kernel from 17 columns on: it streams Z in 16-row blocks and
+    // is bound by HBM (N = 2^20, rank 32, 2 r r_l columns: FP64 10.56 ms a
+    // factorization against 12.06 ms with the row kernel, FP32 6.49 against
+    // 6.96); one 16-column block leaves it waiting on loads, which the row
+    // kernel keeps in flight (solve passes 1.29 against 1.40 ms, one vector)
+    if (nz > 16) {
+      c_base = nz / 16 * 16;
+      hipError_t e;
+      // 4-byte elements, tile heights multiples of 32, even leading dimensions
+      // and 16-byte aligned operands (every paired access is naturally
+      // aligned): two rows per lane
+      auto al16 = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
+      const bool pair = sizeof(TZ) == 4 && sh.mult(32) && ldz % 2 == 0 && (ka == 0 || lda % 2 == 0) &&
+                        (kb == 0 || ldb % 2 == 0) && al16(Z) && (ka == 0 || al16(A1)) && (kb == 0 || al16(B1));
+      bool done = false;
+      if constexpr (sizeof(TZ) == 4) {
+        if (pair) {
+          e = launch_block<TZ, SA, SB, 2>(s, ntiles, tiles, Z, ldz, nz / 16, nz, A1, lda, ka, W, w_ld, w_pstride,
+                                          node_shift, B1, ldb, kb, P, gs);
+          done = true;
+        }
+      }
+      if (!done)
+        e = launch_block<TZ, SA, SB, 1>(s, ntiles, tiles, Z, ldz, nz / 16, nz, A1, lda, ka, W, w_ld, w_pstride,
+                                        node_shift, B1, ldb, kb, P, gs);
+      if (e != hipSuccess || c_base == nz) return e;
+    }
   }
-  const int mbn = kb > 0 ? (min(kb, 64) + 15) / 16 : 1;
-  const size_t smem_red = kb > 0 ? sizeof(TZ) * 4 * 16 * mbn * 64 : 0;
-  const size_t smem_w = ka > 0 ? sizeof(TZ) * 64 * (size_t)((ka + 3) / 4 * 4) : 0;
-  const size_t smem = smem_red > smem_w ? smem_red : smem_w;
-#define HODLR_LP(MBV)                                                                                        \
-  {                                                                                                          \
-    auto k = level_pass_kernel<TZ, SA, SB, MBV>;                                                             \
-    hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem); \
-    if (e != hipSuccess) return e;                                                                           \
-    hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(kLpThreads), smem, s, tiles, zchunks, bchunks, Z, ldz, nz, \
-                       A1, lda, ka, W, w_ld, w_pstride, node_shift, B1, ldb, kb, P, gs);                                \
-  }
-  switch (mbn) {
-    case 1: HODLR_LP(1) break;
-    case 2: HODLR_LP(2) break;
-    case 3: HODLR_LP(3) break;
-    default: HODLR_LP(4) break;
-  }
-#undef HODLR_LP
-  return hipGetLastError();
+  return launch_rows<TZ, SA, SB, false>(s, ntiles, c_base, tiles, sh, Z, ldz, nz, A1, lda, ka, W, w_ld, w_pstride,
+                                        node_shift, B1, ldb, kb, P, gs);
 }
 
-#define HODLR_LP_INST(TZ, SA, SB)                                                                             \
-  template hipError_t launch_level_pass<TZ, SA, SB>(hipStream_t, int, const Tile*, int, TZ*, int64_t, int, const SA*, \
-                                                    int64_t, int, const TZ*, int64_t, int64_t, int,           \
+#define HODLR_LP_INST(TZ, SA, SB)                                                                                  \
+  template hipError_t launch_level_pass<TZ, SA, SB>(hipStream_t, int, const Tile*, TileShape, TZ*, int64_t, int,     \
+                                                    const SA*, int64_t, int, const TZ*, int64_t, int64_t, int,      \
                                                     const SB*, int64_t, int, TZ*, GroupStrides, int);
 HODLR_LP_INST(double, double, double)
 HODLR_LP_INST(float, float, double)

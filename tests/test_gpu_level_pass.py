@@ -1,0 +1,62 @@
+"""Level passes at the edges of their tiles: tile heights around 64, 128 and
+256 rows (whole, one more, one less, a single row in the last tile), ranks and
+right-hand-side counts around multiples of 16, against the CPU oracle with the
+FP64 parity bar of the suite (1e-12 per column); the low-precision factors at
+100 unit roundoffs of their operands (the matrices are well conditioned)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda"
+SHAPES = {
+    "64": (64, [16, 16, 16]),
+    "65_63": ([65, 63, 64, 1, 129, 64, 128, 66], [15, 17, 1]),
+    "128": (128, [24, 8, 33]),
+    "129_127": ([129, 127, 128, 256, 255, 1, 192, 193], [64, 63, 1]),
+    "192": (192, [32, 48, 16]),
+    "256": (256, [31, 20, 64]),
+    "16": (16, [5, 16, 13]),
+}
+
+
+def _rel(a, b):
+    nb = np.linalg.norm(b, axis=0)
+    return float(np.max(np.linalg.norm(a - b, axis=0) / np.where(nb > 0, nb, 1.0)))
+
+
+def _case(name, dtype=torch.float64):
+    leaves, ranks = SHAPES[name]
+    off = None
+    if isinstance(leaves, list):
+        off = np.concatenate([[0], np.cumsum(leaves)]).astype(np.int64)
+        n, leaf = int(off[-1]), 0
+    else:
+        n, leaf = 8 * leaves, leaves
+    inp = W.synthetic(n, leaf, ranks, seed=len(name), leaf_offsets=off, dtype=dtype)
+    from paper_2208_06290_amd import hodlr
+    return hodlr, O.from_inputs(inp), hodlr.HODLRMatrix.from_inputs(inp.to(DEV))
+
+
+@pytest.mark.parametrize("name", list(SHAPES))
+@pytest.mark.parametrize("nrhs", [1, 16, 17, 33, 63, 65])
+def test_solve_adjoint_matvec(name, nrhs):
+    hodlr, H, A = _case(name)
+    B = np.random.default_rng(nrhs).standard_normal((H.N, nrhs))
+    b = torch.as_tensor(np.ascontiguousarray(B.T), device=DEV)
+    F = hodlr.factor(A, "fp64")
+    assert _rel(F.solve(b).cpu().numpy().T, O.solve(O.factor(H), B)) < 1e-12
+    assert _rel(F.solve_adjoint(b).cpu().numpy().T, O.solve_adjoint(H, B)) < 1e-12
+    assert _rel(A.matvec(b).cpu().numpy().T, O.matvec(H, B)) < 1e-12
+
+
+@pytest.mark.parametrize("name", list(SHAPES))
+@pytest.mark.parametrize("prec,unit", [("fp64", 1e-14), ("fp32", 2.0 ** -24), ("bf16", 2.0 ** -8)])
+def test_y_big(name, prec, unit):
+    hodlr, H, A = _case(name)
+    Y = hodlr.factor(A, prec).y_big().cpu().numpy().T
+    assert _rel(Y, O.y_big(O.factor(H))) < 100 * unit
