@@ -28,6 +28,11 @@
  * the device) for the last call on every stream before it overwrites the
  * factors, and later calls wait for it.
  *
+ * Device memory: blocks that a factorization, a workspace or a call's
+ * temporaries no longer need (their work has finished) are kept for the next
+ * ones, at most 4 GiB per device; a block not reused by the 64 releases after
+ * it is freed, and all are freed when an allocation fails.
+ *
  * Errors: negative status = invalid argument / resource error, detected
  * before any kernel is launched where possible; nothing is written then.
  * Positive status = numerical verdict (see each call).
