@@ -3,23 +3,17 @@
 //
 //   K_g = [[V_a^T Y_a, I], [I, V_b^T Y_b]]   for the children a, b of parent g
 //
-// The products V^T Y arrive as per-tile partial sums (level pass) or as
-// segment sums of them; they are summed here in fixed order.
+// The products V^T Y arrive as per-tile partial sums (level pass), summed in
+// fixed order (segment_reduce) to one item per node.
 //
 // couple_factor: one workgroup per parent; K is formed in LDS from the
-//   children's reduced products, the right-hand sides
-//   [V_a^T Y_big(I_a, 1:R_l); V_b^T Y_big(I_b, 1:R_l)] of eq. "e:node1" are
-//   written to W, and K is LU-factored with partial pivoting (largest
-//   magnitude, lowest row on ties): by all four waves with K in registers
-//   when 2r <= 64, else by one wave in LDS.  The LU of K is stored
-//   zero-padded to kp x kp (kp = 2r rounded up to 16) so the block solver
-//   needs no bounds checks; couple_dinv then forms the inverted 16 x 16
-//   diagonal blocks of L and U, and the MFMA block solver overwrites W with
-//   K^{-1} W.
-// couple_solve: one wave per parent; w = K^{-1} [V_a^T x_a; V_b^T x_b]
-//   (eq. "e:node3") or the transposed solve used by the adjoint.
-// Lanes own rows of the right-hand side (2r <= 128 -> two rows per lane) and
-// the pivot value of each elimination step is broadcast with readlane.
+//   children's products and inverted by a blocked Gauss-Jordan elimination with
+//   partial pivoting, K^{-1} is stored (kp x kp, kp = 2r rounded up to 16, zero
+//   padding), and W = K^{-1} rhs, the
+//   right-hand sides [V_a^T Y_big(I_a, 1:R_l); V_b^T Y_big(I_b, 1:R_l)] of
+//   eq. "e:node1", is formed on MFMA.
+// couple_solve: w = K^{-1} [V_a^T x_a; V_b^T x_b] (eq. "e:node3"), or the
+//   transposed product used by the adjoint.
 #include "mfma.h"
 #include "wave.h"
 
@@ -68,16 +62,6 @@ hipError_t launch_segment_reduce(hipStream_t s, int nsegs, const int2* d_desc, i
 template hipError_t launch_segment_reduce<double>(hipStream_t, int, const int2*, int64_t, const double*, double*, int);
 template hipError_t launch_segment_reduce<float>(hipStream_t, int, const int2*, int64_t, const float*, float*, int);
 
-// sum over the segments of `node`: element (i, c) of an r x ncols col-major block
-template <typename T>
-__device__ __forceinline__ T seg_sum(const T* __restrict__ segs, const int32_t* __restrict__ seg_start, int node,
-                                     int64_t elems, int64_t idx) {
-  const int s0 = seg_start[node], s1 = seg_start[node + 1];
-  T acc = T(0);
-  for (int sg = s0; sg < s1; ++sg) acc += segs[(int64_t)sg * elems + idx];
-  return acc;
-}
-
 template <typename T>
 __device__ __forceinline__ T bcast(T v, int srclane);
 template <>
@@ -92,216 +76,7 @@ __device__ __forceinline__ float bcast<float>(float v, int srclane) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), srclane));
 }
 
-constexpr int kWlsBatch = 16;
-
-// One wave solves K z = y for NC right-hand-side columns held as x[slot][c]
-// (row = slot * 64 + lane).  Kf: LU factor (col-major, leading dimension ld),
-// kud: reciprocal diagonal.  Rows >= n2 are ignored.
-template <typename T, int NC, int TRANS>
-__device__ __forceinline__ void wave_lu_solve(T (&x)[2][NC], const T* Kf, const T* kud, int n2, int ld, int lane) {
-  // The factor entries a step needs do not depend on x: they are loaded
-  // kWlsBatch steps at a time (one memory latency per batch instead of per
-  // step); rows past n2 load a clamped row and are never used.
-  constexpr int B = kWlsBatch;
-  const int rr[2] = {lane, min(64 + lane, n2 - 1)};
-  auto step_lower = [&](int j, const T (&f)[2]) {  // x(rows > j) -= f x_j (unit diagonal)
-    const int sj = j >> 6, lj = j & 63;
-    T xj[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) xj[c] = bcast(sj ? x[1][c] : x[0][c], lj);
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const int row = s * 64 + lane;
-      if (row > j && row < n2) {
-#pragma unroll
-        for (int c = 0; c < NC; ++c) x[s][c] -= f[s] * xj[c];
-      }
-    }
-  };
-  auto step_upper = [&](int j, const T (&f)[2], T dinv, bool below) {  // x_j *= 1/d_j; x(rows beyond j) -= f x_j
-    const int sj = j >> 6, lj = j & 63;
-    T xj[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) xj[c] = bcast(sj ? x[1][c] : x[0][c], lj) * dinv;
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const int row = s * 64 + lane;
-      if (row == j) {
-#pragma unroll
-        for (int c = 0; c < NC; ++c) x[s][c] = xj[c];
-      } else if (below ? (row > j && row < n2) : (row < j)) {
-#pragma unroll
-        for (int c = 0; c < NC; ++c) x[s][c] -= f[s] * xj[c];
-      }
-    }
-  };
-  auto step_lower_back = [&](int j, const T (&f)[2]) {  // x(rows < j) -= f x_j (unit diagonal)
-    const int sj = j >> 6, lj = j & 63;
-    T xj[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) xj[c] = bcast(sj ? x[1][c] : x[0][c], lj);
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const int row = s * 64 + lane;
-      if (row < j) {
-#pragma unroll
-        for (int c = 0; c < NC; ++c) x[s][c] -= f[s] * xj[c];
-      }
-    }
-  };
-  // f[q][s] = entry (row s, step j0 + q): column j of the factor (colmajor) or row j (transposed)
-  auto load = [&](int j0, T (&f)[B][2], T (&dv)[B], bool colmajor, int dir) {
-#pragma unroll
-    for (int q = 0; q < B; ++q) {
-      const int j = min(max(j0 + dir * q, 0), n2 - 1);
-#pragma unroll
-      for (int s = 0; s < 2; ++s) f[q][s] = colmajor ? Kf[rr[s] + (int64_t)j * ld] : Kf[j + (int64_t)rr[s] * ld];
-      dv[q] = kud[j];
-    }
-  };
-  T f[B][2], dv[B];
-  if (!TRANS) {
-    // L (unit lower) then U
-    for (int j0 = 0; j0 < n2; j0 += B) {
-      load(j0, f, dv, true, 1);
-#pragma unroll
-      for (int q = 0; q < B; ++q)
-        if (j0 + q < n2) step_lower(j0 + q, f[q]);
-    }
-    for (int j0 = n2 - 1; j0 >= 0; j0 -= B) {
-      load(j0, f, dv, true, -1);
-#pragma unroll
-      for (int q = 0; q < B; ++q)
-        if (j0 - q >= 0) step_upper(j0 - q, f[q], dv[q], false);
-    }
-  } else {
-    // U^T (lower, non-unit) then L^T (unit upper)
-    for (int j0 = 0; j0 < n2; j0 += B) {
-      load(j0, f, dv, false, 1);
-#pragma unroll
-      for (int q = 0; q < B; ++q)
-        if (j0 + q < n2) step_upper(j0 + q, f[q], dv[q], true);
-    }
-    for (int j0 = n2 - 1; j0 >= 0; j0 -= B) {
-      load(j0, f, dv, false, -1);
-#pragma unroll
-      for (int q = 0; q < B; ++q)
-        if (j0 - q >= 0) step_lower_back(j0 - q, f[q]);
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// couple_factor
-// ---------------------------------------------------------------------------
-constexpr int kCfThreads = 256;
-
-// LU with partial pivoting of the n2 x n2 (n2 <= 64) matrix K (LDS, col-major)
-// by the four waves of the workgroup with the matrix in registers: lane i
-// holds row i, wave w columns 16w .. 16w+15.  Rows are not moved while
-// factoring; each lane tracks the position of its row.  At step j the wave
-// owning column j picks the largest |K(., j)| among unpivoted rows (lowest
-// position on ties, a NaN counts as infinite) and publishes the multipliers
-// through LDS (double buffered: one barrier per step); every wave then takes
-// the pivot row from its own registers with readlane and updates its columns.
-// Steps run in blocks of 16 (the owner's column is then a compile-time
-// register index); a wave whose columns all lie left of the current block
-// has nothing to update, a wave right of it updates all 16 columns without
-// per-column tests.  On return K holds L\U in pivoted order, spiv[j] the
-// LAPACK-style interchange of step j and sperm[i] the original row at
-// position i.
-template <typename T>
-__device__ __forceinline__ void block_lu(T* K, int n2, int lane, int w, int* spiv, int* sperm,
-                                         unsigned long long* info, unsigned long long info_base) {
-  __shared__ T s_l[2][64];
-  __shared__ int s_pl[2][2];  // pivot lane, pivot value nonzero
-  T kc[16];
-#pragma unroll
-  for (int c = 0; c < 16; ++c) {
-    const int col = 16 * w + c;
-    kc[c] = (lane < n2 && col < n2) ? K[lane + col * n2] : T(0);
-  }
-  int mypos = lane;
-  bool done = lane >= n2;
-  const int nb = (n2 + 15) >> 4;
-  for (int jb = 0; jb < nb; ++jb) {
-#pragma unroll
-    for (int jj = 0; jj < 16; ++jj) {
-      const int j = 16 * jb + jj;
-      if (j < n2) {  // uniform
-        const int sb = jj & 1;
-        if (w == jb) {
-          const T kj = kc[jj];
-          T v = done ? T(-1) : fabs(kj);
-          if (!done && !(v == v)) v = T(INFINITY);
-          T vmax;
-          int bk;  // pivot position (uniform)
-          wave_argmax(v, done ? 0x7fffffff : mypos, vmax, bk);
-          const unsigned long long sel = __ballot(!done && mypos == bk);
-          const int plane = __builtin_amdgcn_readfirstlane((int)__builtin_ctzll(sel));
-          const T pv = bcast(kj, plane);
-          const bool nz = pv != T(0);
-          s_l[sb][lane] = (!done && lane != plane && nz) ? kj * (T(1) / pv) : T(0);
-          if (lane == 0) {
-            s_pl[sb][0] = plane;
-            s_pl[sb][1] = nz;
-            spiv[j] = bk;
-            if (!nz) atomicMin(info, info_base | (unsigned long long)j);
-          }
-        }
-        __syncthreads();
-        const int plane = __builtin_amdgcn_readfirstlane(s_pl[sb][0]);
-        const bool nz = s_pl[sb][1] != 0;
-        const T l = s_l[sb][lane];
-        const bool me = lane == plane;
-        const bool upd = !done && !me && nz;
-        const int bk = __builtin_amdgcn_readfirstlane(__shfl(mypos, plane, 64));
-        if (!done && !me && mypos == j) mypos = bk;  // the row displaced by the interchange
-        if (me) {
-          done = true;
-          mypos = j;
-        }
-        if (w == jb) {
-          kc[jj] = upd ? l : kc[jj];
-#pragma unroll
-          for (int c = jj + 1; c < 16; ++c) {
-            const T pc = bcast(kc[c], plane);
-            kc[c] = upd ? kc[c] - l * pc : kc[c];
-          }
-        } else if (w > jb) {
-#pragma unroll
-          for (int c = 0; c < 16; ++c) {
-            const T pc = bcast(kc[c], plane);
-            kc[c] = upd ? kc[c] - l * pc : kc[c];
-          }
-        }
-      }
-    }
-  }
-  __syncthreads();  // every wave has read K before it is overwritten
-#pragma unroll
-  for (int c = 0; c < 16; ++c) {
-    const int col = 16 * w + c;
-    if (lane < n2 && col < n2) K[mypos + col * n2] = kc[c];
-  }
-  if (w == 0 && lane < n2) sperm[mypos] = lane;
-}
-
-// K_g (eq. "e:k") in LDS, col-major n2 x n2, from the children's reduced
-// products: item columns Rp .. Rp + r - 1 hold V_a^T Y_a (r x r)
-template <typename T>
-__device__ __forceinline__ void form_k(T* K, const T* Pa, const T* Pb, int r, int Rp, int tid) {
-  const int n2 = 2 * r;
-#pragma unroll 4
-  for (int e = tid; e < n2 * n2; e += kCfThreads) {
-    const int i = e % n2, j = e / n2;
-    const bool da = i < r && j < r, db = i >= r && j >= r;
-    const T va = Pa[min(i, r - 1) + (int64_t)(Rp + min(j, r - 1)) * r];
-    const T vb = Pb[max(i - r, 0) + (int64_t)(Rp + max(j - r, 0)) * r];
-    const T id = (i < r ? j - r == i : i - r == j) ? T(1) : T(0);
-    K[i + j * n2] = da ? va : (db ? vb : id);
-  }
-}
+constexpr int kCfMaxRows = 128;  // rows of a padded K (r <= 64)
 
 // Element e = tid + u * NT (u = 0, 1, ...) of an n2-row column-major block as
 // (row, column), stepped without a division per element.
@@ -323,920 +98,644 @@ struct BlockWalk {
   }
 };
 
-// form_k for the inverse route (n2 * n2 <= NT * NPT): every thread issues its
-// NPT loads in batches of NB, each entry read from the one product it comes
-// from
-template <typename T, int NT, int NPT, int NB>
-__device__ __forceinline__ void form_k_batched(T* K, const T* Pa, const T* Pb, int r, int Rp, int tid) {
-  static_assert(NPT % NB == 0, "whole batches");
-  const int n2 = 2 * r;
-  asm volatile("" : "+v"(tid));
-  BlockWalk it(tid, NT, n2);
-  for (int u0 = 0; u0 < NPT; u0 += NB) {
-    T v[NB];
-    BlockWalk st = it;
-#pragma unroll
-    for (int u = 0; u < NB; ++u) {
-      const int i = it.k, j = it.c;
-      T x = (i < r ? j - r == i : i - r == j) ? T(1) : T(0);
-      if (j < n2) {
-        if (i < r && j < r) x = Pa[i + (int64_t)(Rp + j) * r];
-        else if (i >= r && j >= r) x = Pb[(i - r) + (int64_t)(Rp + j - r) * r];
-      }
-      v[u] = x;
-      it.next();
-    }
-#pragma unroll
-    for (int u = 0; u < NB; ++u) {
-      if (st.c < n2) K[st.k + st.c * n2] = v[u];
-      st.next();
-    }
-  }
-}
-
-// One 64-column chunk of the right-hand sides [W_a; W_b] (columns c0 ..
-// c0 + 63 of the children's products, zero past Rp): NPT values per thread
-// loaded in one batch (64 * n2 <= NT * NPT), then stored to LDS as
-// [column][row] with ld n2 + 1.
-template <typename T, int NT, int NPT>
-struct RhsChunk {
-  T v[NPT];
-  __device__ __forceinline__ void load(const T* Pa, const T* Pb, int r, int Rp, int c0, int tid) {
-    // an opaque copy of tid: the per-element addresses are not hoisted out of
-    // the caller's chunk loop (they would stay live in registers)
-    asm volatile("" : "+v"(tid));
-    BlockWalk it(tid, NT, 2 * r);
-#pragma unroll
-    for (int u = 0; u < NPT; ++u) {
-      const int k = it.k, col = c0 + it.c;
-      T x = T(0);
-      if (it.c < 64 && col < Rp) x = k < r ? Pa[k + (int64_t)col * r] : Pb[(k - r) + (int64_t)col * r];
-      v[u] = x;
-      it.next();
-    }
-  }
-  __device__ __forceinline__ void store(T* Rs, int r, int tid) const {
-    const int n2 = 2 * r, ldr = n2 + 1;
-    BlockWalk it(tid, NT, n2);
-#pragma unroll
-    for (int u = 0; u < NPT; ++u) {
-      if (it.c < 64) Rs[it.c * ldr + it.k] = v[u];
-      it.next();
-    }
-  }
+// One panel of the in-place Gauss-Jordan elimination: columns 16 jb .. + 15 of
+// K (LDS, column-major, ld ldk) by one wave, lane i holding rows i and (NS = 2)
+// 64 + i of the panel in registers.  Step j takes the largest |K(., j)| among
+// rows not pivoted yet (the lowest current position on ties, a NaN counts as
+// infinite: the rule of LU with partial pivoting) and exchanges column j with
+// the pivot's unit vector: K(i, c) -= K(i, j) / pv * K(p, c) for the other rows
+// and columns of the panel, K(i, j) = -K(i, j) / pv.  The pivot row is divided
+// by its pivot when the panel ends (the later steps are linear in it); its
+// entry j is 1 until then.
+//
+// A step is one dependency chain (about 0.25 us in FP64), so nothing but the
+// chain is left in it: the moduli are compared as integers, high words first
+// (six one-instruction steps; low words and positions only on a tie), every
+// lane divides its own candidate while the maximum is found, and what is
+// recorded of a pivot stays in its lane until the panel ends.  The loop is
+// rolled: the columns rotate, step j works on x[0] and the elimination of
+// x[c + 1] is written to x[c], so they are back in place after 16 steps.
+//   s_pos  row -> current position (the step it was pivoted at, once pivoted)
+//   s_pan  row -> panel in which it was pivoted (-1: not yet)
+//   s_prow step -> pivot row
+//   spiv, sud (global): LAPACK-style interchange (plus p0) and 1 / pivot of step j
+// Columns j >= nid are unit vectors e_j: nothing to search.  A zero pivot in
+// column j is reported as column j - (j >= cut ? skip : 0) + c0 of K.
+struct PanelInfo {
+  unsigned long long* info;
+  unsigned long long base;
+  int cut, skip, c0;
 };
-
-// Gauss-Jordan elimination with partial pivoting on [K | I] for n2 <= 64,
-// n2 % 16 == 0, with the same register layout and pivot rule as block_lu
-// (lane i holds row i, wave w columns 16w .. 16w+15 of K and of the augmented
-// block).  Step j eliminates column j from every other row, including the
-// rows pivoted earlier.  The pivot rows are divided by their pivots only at
-// the end (a row scaled later is the same multiple of the row scaled at once
-// through every later elimination, which is linear in it), so each step is
-// one multiply-add per entry; rows not yet pivoted are not affected, so the
-// pivots are those of scaling at once.  Afterwards the augmented row of the
-// row pivoted at step j, divided by its pivot, is row j of K^{-1}, written to
-// K (col-major).
-// spiv[j] records the position the row pivoted at step j came from (an
-// interchange with position j, as LAPACK's ipiv) and spv[j] its pivot value:
-// the pivots are those of LU with partial pivoting, so they give det K.
-template <typename T>
-__device__ __forceinline__ void block_gj(T* K, int n2, int lane, int w, int* spiv, T* spv, unsigned long long* info,
-                                         unsigned long long info_base) {
-  __shared__ T s_l[2][64];
-  __shared__ int s_pl[2][2];  // pivot lane, pivot position
-  T kc[16], ac[16];
+template <typename T, int NS>
+__device__ __forceinline__ void gj_panel(T* K, int ldk, int kp, int nid, int jb, int lane, int* s_pos, int* s_pan,
+                                         int* s_prow, int32_t* spiv, int p0, T* sud, PanelInfo pi) {
+  T x[NS][16];
+  int pos[NS], from[NS];  // current position; position at the time it was pivoted
+  bool open[NS], here[NS], zero[NS];
+  T myrp[NS];
 #pragma unroll
-  for (int c = 0; c < 16; ++c) {
-    const int col = 16 * w + c;
-    kc[c] = (lane < n2 && col < n2) ? K[lane + col * n2] : T(0);
-    ac[c] = (lane < n2 && lane == col) ? T(1) : T(0);
-  }
-  int mypos = lane;
-  bool done = lane >= n2;
-  const int nb = n2 >> 4;
-  // pivot search of column j (value kj of the lane's row), by the wave that
-  // owns the column: the multipliers and the pivot go to slot sb
-  auto pivot = [&](int j, T kj, int sb) {
-    T v = done ? T(-1) : fabs(kj);
-    if (!done && !(v == v)) v = T(INFINITY);
-    T vmax;
-    int bk;  // pivot position (uniform)
-    wave_argmax(v, done ? 0x7fffffff : mypos, vmax, bk);
-    const unsigned long long sel = __ballot(!done && mypos == bk);
-    const int plane = __builtin_amdgcn_readfirstlane((int)__builtin_ctzll(sel));
-    const T pv = bcast(kj, plane);
-    const bool nz = pv != T(0);
-    const T rp = T(1) / pv;
-    // multipliers of the other rows; the pivot row keeps its values (scaled at the end)
-    s_l[sb][lane] = (lane < n2 && nz && lane != plane) ? kj * rp : T(0);
-    if (lane == 0) {
-      s_pl[sb][0] = plane;
-      s_pl[sb][1] = bk;
-      spiv[j] = bk;
-      spv[j] = pv;
-      if (!nz) atomicMin(info, info_base | (unsigned long long)j);
-    }
-  };
-  for (int jb = 0; jb < nb; ++jb) {
-#pragma unroll
-    for (int jj = 0; jj < 16; ++jj) {
-      const int j = 16 * jb + jj;
-      const int sb = jj & 1;
-      // the first column of a block; the others were searched ahead (below)
-      if (jj == 0 && w == jb) pivot(j, kc[0], sb);
-      __syncthreads();
-      // after a zero pivot (reported) every multiplier is zero and the rows
-      // stay as they are
-      const int plane = __builtin_amdgcn_readfirstlane(s_pl[sb][0]);
-      const int bk = __builtin_amdgcn_readfirstlane(s_pl[sb][1]);
-      const T l = s_l[sb][lane];
-      const bool me = lane == plane;
-      if (!done && !me && mypos == j) mypos = bk;  // the row displaced by the interchange
-      if (me) {
-        done = true;
-        mypos = j;
-      }
-      auto elim = [&](T& x) {
-        const T p = bcast(x, plane);
-        x = x - l * p;  // l = 0 in the pivot row
-      };
-      // columns left of j are zero in the pivot row: nothing to do there.
-      // The owner eliminates column j + 1 first and searches its pivot
-      // before the rest of its work, so that search is off the other waves'
-      // critical path.
-      if (w == jb) {
-        if (jj < 15) {
-          elim(kc[jj + 1]);
-          pivot(j + 1, kc[jj + 1], sb ^ 1);
-        }
-#pragma unroll
-        for (int c = jj + 2; c < 16; ++c) elim(kc[c]);
-      } else if (w > jb) {
-#pragma unroll
-        for (int c = 0; c < 16; ++c) elim(kc[c]);
-      }
-#pragma unroll
-      for (int c = 0; c < 16; ++c) elim(ac[c]);
-    }
-  }
-  __syncthreads();  // every wave has read K before it is overwritten
-  // the row pivoted at step mypos, divided by its pivot (left as it is after a
-  // zero pivot, which is reported)
-  const T pvm = lane < n2 ? spv[mypos] : T(1);
-  const T sc = pvm != T(0) ? T(1) / pvm : T(1);
-#pragma unroll
-  for (int c = 0; c < 16; ++c) {
-    const int col = 16 * w + c;
-    if (lane < n2 && col < n2) K[mypos + col * n2] = ac[c] * sc;
-  }
-}
-
-template <typename T>
-__global__ __launch_bounds__(kCfThreads) void couple_factor_kernel(int r, int kp, int Rp, const T* __restrict__ segs,
-                                                                   const int32_t* __restrict__ seg_start,
-                                                                   T* __restrict__ Klu, int32_t* __restrict__ Kpiv,
-                                                                   int32_t* __restrict__ Kperm,
-                                                                   T* __restrict__ Kud,
-                                                                   T* __restrict__ W, unsigned long long* info,
-                                                                   int level, int L) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  T* K = reinterpret_cast<T*>(smem_raw);  // n2 x n2, col-major
-  __shared__ int spiv[2 * HODLR_MAX_RANK];
-  __shared__ int sperm[2 * HODLR_MAX_RANK];
-
-  const int g = blockIdx.x;
-  const int a = 2 * g, b = 2 * g + 1;
-  const int n2 = 2 * r;
-  const int ncin = Rp + r;  // columns of the children's products: [W rhs | T]
-  const int64_t elems = (int64_t)r * ncin;
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-
-  // the children's products have been reduced to one item per node
-  const T* Pa = segs + (int64_t)seg_start[a] * elems;
-  const T* Pb = segs + (int64_t)seg_start[b] * elems;
-  form_k(K, Pa, Pb, r, Rp, tid);
-  __syncthreads();
-  // right-hand sides of eq. "e:node1", unpermuted (the block solver applies the pivots)
-  {
-    T* Wg = W + (int64_t)g * n2 * Rp;
-#pragma unroll 4
-    for (int e = tid; e < n2 * Rp; e += kCfThreads) {
-      const int i = e % n2, cc = e / n2;
-      Wg[e] = (i < r ? Pa : Pb)[(i % r) + (int64_t)cc * r];
-    }
-  }
-  if (n2 <= 64) {
-    block_lu(K, n2, lane, wid, spiv, sperm, info, ((unsigned long long)(L - level) << 44) | ((unsigned long long)g << 16));
-  } else {
-    // LU with partial pivoting, 64 < 2r <= 128: per column, wave 0 takes the
-    // pivot (rows over lanes, two rows a lane), exchanges the rows and scales
-    // the column below the pivot; then the four waves update the trailing
-    // columns, wave w the columns c = w (mod 4) right of j.  Every entry gets
-    // the same operations in the same order as in a sequential elimination.
-    __shared__ T lcol[2 * HODLR_MAX_RANK];
-    __shared__ T prow[2 * HODLR_MAX_RANK];
-    __shared__ int zero_pivot;
-    for (int j = 0; j < n2; ++j) {
-      if (wid == 0) {
-        T best = T(-1);
-        int bi = 0x7fffffff;
-#pragma unroll
-        for (int sl = 0; sl < 2; ++sl) {
-          const int row = sl * 64 + lane;
-          if (row >= j && row < n2) {
-            T v = fabs(K[row + j * n2]);
-            if (!(v == v)) v = T(INFINITY);
-            if (v > best || (v == best && row < bi)) {
-              best = v;
-              bi = row;
-            }
-          }
-        }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-          const T ov = __shfl_xor(best, off, 64);
-          const int oi = __shfl_xor(bi, off, 64);
-          if (ov > best || (ov == best && oi < bi)) {
-            best = ov;
-            bi = oi;
-          }
-        }
-        const int p = (bi < n2) ? bi : j;
-        if (lane == 0) {
-          spiv[j] = p;
-          if (K[p + j * n2] == T(0))
-            atomicMin(info, ((unsigned long long)(L - level) << 44) | ((unsigned long long)g << 16) |
-                                (unsigned long long)j);
-        }
-        if (p != j) {
-#pragma unroll
-          for (int sl = 0; sl < 2; ++sl) {
-            const int c = sl * 64 + lane;
-            if (c < n2) {
-              const T t0 = K[j + c * n2];
-              K[j + c * n2] = K[p + c * n2];
-              K[p + c * n2] = t0;
-            }
-          }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        const T pivot = K[j + j * n2];
-        const T rinv = pivot != T(0) ? T(1) / pivot : T(0);
-        if (lane == 0) zero_pivot = pivot == T(0);  // no elimination step then
-#pragma unroll
-        for (int sl = 0; sl < 2; ++sl) {
-          const int row = sl * 64 + lane;
-          if (row < n2) {
-            // the multipliers below the pivot (zero when the pivot is zero: no update)
-            const T l = row > j ? K[row + j * n2] * rinv : T(0);
-            lcol[row] = l;
-            if (row > j && pivot != T(0)) K[row + j * n2] = l;
-            prow[row] = K[j + row * n2];  // the pivot row (entry c at prow[c])
-          }
-        }
-      }
-      __syncthreads();
-      if (!zero_pivot) {
-        // four of the wave's columns per round, their loads issued together
-        // (rows past n2 read a clamped row and write nothing)
-        const int r0 = lane, r1 = min(64 + lane, n2 - 1);
-        const bool w0 = r0 > j && r0 < n2, w1 = 64 + lane > j && 64 + lane < n2;
-        const T l0 = lcol[r0], l1 = lcol[r1];
-        int c = j + 1 + wid;
-        for (; c + 12 < n2; c += 16) {
-          T a[4], b[4], pc[4];
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            pc[q] = prow[c + 4 * q];
-            a[q] = K[r0 + (c + 4 * q) * n2];
-            b[q] = K[r1 + (c + 4 * q) * n2];
-          }
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            if (w0) K[r0 + (c + 4 * q) * n2] = a[q] - l0 * pc[q];
-            if (w1) K[r1 + (c + 4 * q) * n2] = b[q] - l1 * pc[q];
-          }
-        }
-        for (; c < n2; c += 4) {
-          const T pc = prow[c];
-          const T a = K[r0 + c * n2], b = K[r1 + c * n2];
-          if (w0) K[r0 + c * n2] = a - l0 * pc;
-          if (w1) K[r1 + c * n2] = b - l1 * pc;
-        }
-      }
-      __syncthreads();
-    }
-  }
-  __syncthreads();
-  // store the factors (zero-padded kp x kp), the composed permutation and the reciprocal diagonal
-  T* Kg = Klu + (int64_t)g * kp * kp;
-  for (int e = tid; e < kp * kp; e += kCfThreads) {
-    const int i = e % kp, j = e / kp;
-    Kg[e] = (i < n2 && j < n2) ? K[i + j * n2] : T(0);
-  }
-  if (n2 > 64 && tid == 0) {  // (block_lu records the row order itself)
-    for (int i = 0; i < n2; ++i) sperm[i] = i;
-    for (int j = 0; j < n2; ++j) {
-      int p = spiv[j];
-      int t0 = sperm[j];
-      sperm[j] = sperm[p];
-      sperm[p] = t0;
-    }
-  }
-  __syncthreads();
-  for (int i = tid; i < kp; i += kCfThreads) {
-    Kpiv[(int64_t)g * kp + i] = i < n2 ? spiv[i] : i;
-    Kperm[(int64_t)g * kp + i] = i < n2 ? sperm[i] : i;
-    Kud[(int64_t)g * kp + i] = i < n2 ? T(1) / K[i + i * n2] : T(1);
-  }
-}
-
-// Inverses of the 16 x 16 diagonal blocks of L and U of every factored K
-// (padded part: identity), for the block solver.  A kernel of its own: the
-// unrolled substitutions need many registers, which would cap the occupancy of
-// the factorization.  Thread (which, kb, cc) forms column cc of block kb.
-template <typename T>
-__global__ __launch_bounds__(kCfThreads) void couple_dinv_kernel(int n2, int kp, const T* __restrict__ Klu,
-                                                                 T* __restrict__ Kinv) {
-  const int g = blockIdx.x, tid = threadIdx.x;
-  const int nbd = kp >> 4;
-  const int which = tid >> 7;  // 0: L, 1: U
-  const int kb = (tid >> 4) & 7, cc = tid & 15;
-  if (kb >= nbd) return;
-  const int g0 = 16 * kb;
-  const T* Kg = Klu + (int64_t)g * kp * kp + g0 + (int64_t)g0 * kp;  // zero-padded kp x kp, col-major
-  auto Kel = [&](int i, int j) -> T { return Kg[i + j * kp]; };
-  T x[16];
-  if (which == 0) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      T sv = (i == cc) ? T(1) : T(0);
-#pragma unroll
-      for (int jj = 0; jj < i; ++jj) sv -= Kel(i, jj) * x[jj];
-      x[i] = (i >= cc) ? sv : T(0);
-    }
-  } else {
-#pragma unroll
-    for (int i = 15; i >= 0; --i) {
-      T sv = (i == cc) ? T(1) : T(0);
-#pragma unroll
-      for (int jj = i + 1; jj < 16; ++jj) sv -= Kel(i, jj) * x[jj];
-      const T d = (g0 + i < n2) ? Kel(i, i) : T(1);
-      x[i] = (i <= cc) ? sv / d : T(0);
-    }
-  }
-  T* dst = Kinv + ((int64_t)g * 2 + which) * nbd * 256 + kb * 256;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) dst[i * 16 + cc] = x[i];
-}
-
-// Coupling factor for 2r <= 64, 2r % 16 == 0: K^{-1} by block_gj, stored
-// (2r x 2r, col-major) for the solves, and W = K^{-1} rhs written directly:
-// the products run on MFMA in 64-column chunks, transposed
-// (W^T = rhs^T K^{-T}) so that lanes hold consecutive rows of W; wave w forms
-// rows 16w .. 16w+15 with its part of K^{-1} held in registers, and the
-// right-hand-side chunk is staged in LDS (where K was).
-template <typename T>
-__global__ __launch_bounds__(kCfThreads) void couple_factor_inv_kernel(int r, int Rp, const T* __restrict__ segs,
-                                                                       const int32_t* __restrict__ seg_start,
-                                                                       T* __restrict__ Kinv, int32_t* __restrict__ Kpiv,
-                                                                       T* __restrict__ Kud, T* __restrict__ W,
-                                                                       unsigned long long* info, int level, int L) {
-  using M = Mfma<T>;
-  using V = typename M::V;
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  T* K = reinterpret_cast<T*>(smem_raw);  // n2 x n2 col-major, then the rhs chunk [c][k] (ld n2 + 1)
-  const int g = blockIdx.x;
-  const int a = 2 * g, b = 2 * g + 1;
-  const int n2 = 2 * r;
-  const int ncin = Rp + r;
-  const int64_t elems = (int64_t)r * ncin;
-  const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lq = lane >> 4;
-  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const T* Pa = segs + (int64_t)seg_start[a] * elems;
-  const T* Pb = segs + (int64_t)seg_start[b] * elems;
-  __shared__ int s_piv[64];
-  __shared__ T s_pv[64];
-  form_k_batched<T, kCfThreads, 16, 8>(K, Pa, Pb, r, Rp, tid);
-  __syncthreads();
-  block_gj(K, n2, lane, wid, s_piv, s_pv, info, ((unsigned long long)(L - level) << 44) | ((unsigned long long)g << 16));
-  __syncthreads();
-  T* Kg = Kinv + (int64_t)g * n2 * n2;
-  for (int e = tid; e < n2 * n2; e += kCfThreads) Kg[e] = K[e];
-  // interchanges and reciprocal pivots, as the LU route stores them (for det K)
-  if (tid < n2) {
-    Kpiv[(int64_t)g * n2 + tid] = s_piv[tid];
-    Kud[(int64_t)g * n2 + tid] = T(1) / s_pv[tid];
-  }
-  // B operand: K^{-1}(16 wid + li, 4 ks + lq)
-  const bool act = 16 * wid < n2;  // uniform
-  T bk[16];
-#pragma unroll
-  for (int ks = 0; ks < 16; ++ks) bk[ks] = (act && 4 * ks < n2) ? K[(16 * wid + li) + (4 * ks + lq) * n2] : T(0);
-  __syncthreads();  // K's LDS is reused for the right-hand sides
-  T* Rs = K;
-  const int ldr = n2 + 1;
-  T* Wg = W + (int64_t)g * n2 * Rp;
-  for (int c0 = 0; c0 < Rp; c0 += 64) {
-    {
-      RhsChunk<T, kCfThreads, 16> rhs;
-      rhs.load(Pa, Pb, r, Rp, c0, tid);
-      rhs.store(Rs, r, tid);
-    }
-    __syncthreads();
-    if (act) {
-      V acc[4];
-#pragma unroll
-      for (int mb = 0; mb < 4; ++mb) acc[mb] = vzero<V>();
-#pragma unroll
-      for (int ks = 0; ks < 16; ++ks) {
-        if (4 * ks < n2) {  // uniform
-#pragma unroll
-          for (int mb = 0; mb < 4; ++mb) acc[mb] = M::mma(Rs[(16 * mb + li) * ldr + 4 * ks + lq], bk[ks], acc[mb]);
-        }
-      }
-      const int i = 16 * wid + li;
-#pragma unroll
-      for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const int c = c0 + 16 * mb + M::crow(lq, t);
-          if (c < Rp) Wg[i + (int64_t)c * n2] = acc[mb][t];
-        }
-    }
-    __syncthreads();
-  }
-}
-
-// Gauss-Jordan elimination as block_gj for 64 < n2 <= 128 (n2 % 16 == 0):
-// eight waves, wave w holding columns 16w .. 16w+15 of K and of the
-// augmented block, lane i holding rows i (slot 0) and 64 + i (slot 1).  The
-// pivot of column j is the largest modulus among the rows not pivoted yet,
-// the lowest current position on ties (the rule of LU with partial
-// pivoting); spiv / spv, the deferred scaling of the pivot rows and their
-// final placement as block_gj.
-template <typename T>
-__device__ __forceinline__ void block_gj2(T* K, int n2, int lane, int w, int* spiv, T* spv, unsigned long long* info,
-                                          unsigned long long info_base) {
-  __shared__ T s_l[2][128];
-  __shared__ int s_pl[2][3];  // pivot lane, pivot slot, pivot position
-  T kc[2][16], ac[2][16];
-#pragma unroll
-  for (int sl = 0; sl < 2; ++sl)
-#pragma unroll
-    for (int c = 0; c < 16; ++c) {
-      const int row = 64 * sl + lane, col = 16 * w + c;
-      kc[sl][c] = (row < n2 && col < n2) ? K[row + col * n2] : T(0);
-      ac[sl][c] = (row < n2 && row == col) ? T(1) : T(0);
-    }
-  int mypos[2] = {lane, 64 + lane};
-  bool done[2] = {lane >= n2, 64 + lane >= n2};
-  const int nb = n2 >> 4;
-  // pivot search of column j (values k0, k1 of the lane's two rows), by the
-  // wave that owns the column: multipliers and pivot to slot sb
-  auto pivot = [&](int j, T k0, T k1, int sb) {
-    const T kj[2] = {k0, k1};
-    T v[2];
-    int key[2];
-#pragma unroll
-    for (int sl = 0; sl < 2; ++sl) {
-      T a = fabs(kj[sl]);
-      if (!(a == a)) a = T(INFINITY);
-      v[sl] = done[sl] ? T(-1) : a;
-      key[sl] = done[sl] ? 0x7fffffff : mypos[sl];
-    }
-    const int bs = (v[1] > v[0] || (v[1] == v[0] && key[1] < key[0])) ? 1 : 0;
-    const T vb = bs ? v[1] : v[0];
-    const int kb = bs ? key[1] : key[0];
-    T vmax;
-    int bk;  // position of the pivot row (uniform)
-    wave_argmax(vb, kb, vmax, bk);
-    const unsigned long long sel = __ballot(kb == bk);  // positions of rows not pivoted are distinct
-    const int plane = __builtin_amdgcn_readfirstlane((int)__builtin_ctzll(sel));
-    const int pslot = __builtin_amdgcn_readlane(bs, plane);
-    const T pv = bcast(pslot ? kj[1] : kj[0], plane);
-    const bool nz = pv != T(0);
-    const T rp = T(1) / pv;
-#pragma unroll
-    for (int sl = 0; sl < 2; ++sl) {
-      const int row = 64 * sl + lane;
-      if (row < n2) s_l[sb][row] = (nz && !(lane == plane && sl == pslot)) ? kj[sl] * rp : T(0);
-    }
-    if (lane == 0) {
-      s_pl[sb][0] = plane;
-      s_pl[sb][1] = pslot;
-      s_pl[sb][2] = bk;
-      spiv[j] = bk;
-      spv[j] = pv;
-      if (!nz) atomicMin(info, info_base | (unsigned long long)j);
-    }
-  };
-  for (int jb = 0; jb < nb; ++jb) {
-#pragma unroll
-    for (int jj = 0; jj < 16; ++jj) {
-      const int j = 16 * jb + jj;
-      const int sb = jj & 1;
-      // the first column of a block; the others were searched ahead (below)
-      if (jj == 0 && w == jb) pivot(j, kc[0][0], kc[1][0], sb);
-      __syncthreads();
-      // after a zero pivot (reported) every multiplier is zero and the rows
-      // stay as they are
-      const int plane = __builtin_amdgcn_readfirstlane(s_pl[sb][0]);
-      const int pslot = __builtin_amdgcn_readfirstlane(s_pl[sb][1]);
-      const int bk = __builtin_amdgcn_readfirstlane(s_pl[sb][2]);
-      T l[2];
-      bool me[2];
-#pragma unroll
-      for (int sl = 0; sl < 2; ++sl) {
-        l[sl] = s_l[sb][min(64 * sl + lane, n2 - 1)];
-        me[sl] = lane == plane && sl == pslot;
-      }
-#pragma unroll
-      for (int sl = 0; sl < 2; ++sl) {
-        if (!done[sl] && !me[sl] && mypos[sl] == j) mypos[sl] = bk;  // the row displaced by the interchange
-        if (me[sl]) {
-          done[sl] = true;
-          mypos[sl] = j;
-        }
-      }
-      auto elim_col = [&](T (&m)[2][16], int c) {
-        const T p = bcast(pslot ? m[1][c] : m[0][c], plane);
-#pragma unroll
-        for (int sl = 0; sl < 2; ++sl) m[sl][c] = m[sl][c] - l[sl] * p;  // l = 0 in the pivot row
-      };
-      // the owner eliminates column j + 1 first and searches its pivot
-      // before the rest of its work
-      if (w == jb) {
-        if (jj < 15) {
-          elim_col(kc, jj + 1);
-          pivot(j + 1, kc[0][jj + 1], kc[1][jj + 1], sb ^ 1);
-        }
-#pragma unroll
-        for (int c = jj + 2; c < 16; ++c) elim_col(kc, c);
-      } else if (w > jb) {
-#pragma unroll
-        for (int c = 0; c < 16; ++c) elim_col(kc, c);
-      }
-#pragma unroll
-      for (int c = 0; c < 16; ++c) elim_col(ac, c);
-    }
-  }
-  __syncthreads();  // every wave has read K before it is overwritten
-#pragma unroll
-  for (int sl = 0; sl < 2; ++sl) {
+  for (int sl = 0; sl < NS; ++sl) {
     const int row = 64 * sl + lane;
-    const T pvm = row < n2 ? spv[mypos[sl]] : T(1);
-    const T sc = pvm != T(0) ? T(1) / pvm : T(1);
+    const bool in = row < kp;
 #pragma unroll
-    for (int c = 0; c < 16; ++c) {
-      const int col = 16 * w + c;
-      if (row < n2 && col < n2) K[mypos[sl] + col * n2] = ac[sl][c] * sc;
+    for (int c = 0; c < 16; ++c) x[sl][c] = in ? K[row + (16 * jb + c) * ldk] : T(0);
+    pos[sl] = in ? s_pos[row] : 0x7fffffff;
+    open[sl] = in && s_pan[row] < 0;
+    here[sl] = zero[sl] = false;
+    myrp[sl] = T(1);
+    from[sl] = 0;
+  }
+#pragma unroll 1
+  for (int j = 16 * jb; j < 16 * jb + 16; ++j) {
+    int plane = j & 63, pslot = j >> 6, bk = j;
+    bool nz = true;
+    T rpv = T(1);
+    if (j < nid) {  // uniform
+      uint32_t hi[NS], lo[NS];
+      T rp[NS];
+#pragma unroll
+      for (int sl = 0; sl < NS; ++sl) {
+        modulus_words(x[sl][0], open[sl], hi[sl], lo[sl]);
+        rp[sl] = T(1) / x[sl][0];
+      }
+      // keeps the divisions ahead of the search, whose waits they fill
+      if constexpr (NS == 1) asm volatile("" : "+v"(rp[0]));
+      else asm volatile("" : "+v"(rp[0]), "+v"(rp[NS - 1]));
+      const uint32_t mx = wave_max(NS == 2 ? max(hi[0], hi[NS - 1]) : hi[0]);
+      unsigned long long hit[NS];
+      int nhit = 0;
+#pragma unroll
+      for (int sl = 0; sl < NS; ++sl) {
+        hit[sl] = __ballot(hi[sl] == mx);
+        nhit += __builtin_popcountll(hit[sl]);
+      }
+      if (nhit > 1) {  // uniform: low words, then the lowest position
+        if constexpr (sizeof(T) == 8) {
+          uint32_t c0 = hi[0] == mx ? lo[0] : 0u;
+          if (NS == 2) c0 = max(c0, hi[NS - 1] == mx ? lo[NS - 1] : 0u);
+          const uint32_t ml = wave_max(c0);
+#pragma unroll
+          for (int sl = 0; sl < NS; ++sl) hit[sl] = __ballot(hi[sl] == mx && lo[sl] == ml);
+        }
+        int c = 0x7fffffff;
+#pragma unroll
+        for (int sl = 0; sl < NS; ++sl) c = min(c, (hit[sl] >> lane) & 1 ? pos[sl] : 0x7fffffff);
+        const int mp = wave_min(c);
+#pragma unroll
+        for (int sl = 0; sl < NS; ++sl) hit[sl] &= __ballot(pos[sl] == mp);
+      }
+      pslot = NS == 2 && hit[0] == 0 ? 1 : 0;
+      plane = __builtin_amdgcn_readfirstlane((int)__builtin_ctzll(pslot ? hit[NS - 1] : hit[0]));
+      nz = bcast(pslot ? x[NS - 1][0] : x[0][0], plane) != T(0);
+      rpv = nz ? bcast(pslot ? rp[NS - 1] : rp[0], plane) : T(0);  // no elimination after a zero pivot
+      bk = __builtin_amdgcn_readlane(pslot ? pos[NS - 1] : pos[0], plane);
+    }
+    T g[NS];
+    bool me[NS];
+#pragma unroll
+    for (int sl = 0; sl < NS; ++sl) {
+      me[sl] = lane == plane && sl == pslot;
+      g[sl] = me[sl] ? T(0) : x[sl][0] * rpv;
+      if (open[sl] && pos[sl] == j) pos[sl] = bk;  // the row displaced by the interchange
+      open[sl] = open[sl] && !me[sl];
+      here[sl] = here[sl] || me[sl];
+      pos[sl] = me[sl] ? j : pos[sl];
+      from[sl] = me[sl] ? bk : from[sl];
+      myrp[sl] = me[sl] && nz ? rpv : myrp[sl];
+      zero[sl] = zero[sl] || (me[sl] && !nz);
+    }
+#pragma unroll
+    for (int c = 0; c < 15; ++c) {
+      const T pc = bcast(pslot ? x[NS - 1][c + 1] : x[0][c + 1], plane);
+#pragma unroll
+      for (int sl = 0; sl < NS; ++sl) x[sl][c] = x[sl][c + 1] - g[sl] * pc;  // g = 0 in the pivot row
+    }
+#pragma unroll
+    for (int sl = 0; sl < NS; ++sl) x[sl][15] = me[sl] ? T(1) : -g[sl];
+  }
+#pragma unroll
+  for (int sl = 0; sl < NS; ++sl) {
+    const int row = 64 * sl + lane;
+    if (row < kp) {
+#pragma unroll
+      for (int c = 0; c < 16; ++c) K[row + (16 * jb + c) * ldk] = x[sl][c] * myrp[sl];
+      s_pos[row] = pos[sl];
+      if (here[sl]) {
+        s_pan[row] = jb;
+        s_prow[pos[sl]] = row;
+        spiv[pos[sl]] = p0 + from[sl];
+        sud[pos[sl]] = zero[sl] ? T(INFINITY) : myrp[sl];
+        if (zero[sl])
+          atomicMin(pi.info, pi.base | (unsigned long long)(pos[sl] - (pos[sl] >= pi.cut ? pi.skip : 0) + pi.c0));
+      }
     }
   }
 }
 
-// Coupling factor for 64 < 2r <= 128 (2r % 16 == 0): K^{-1} by block_gj2 with
-// eight waves, stored (2r x 2r, col-major), and W = K^{-1} rhs on MFMA
-// (transposed, as couple_factor_inv_kernel): wave w forms rows 16w .. 16w+15.
-constexpr int kCf2Threads = 512;
+// The row (of 16) that lane li feeds as MFMA A operand so that register t of
+// lane group lq of the result holds row 4 lq + t.
 template <typename T>
-__global__ __launch_bounds__(kCf2Threads) void couple_factor_inv2_kernel(int r, int Rp, const T* __restrict__ segs,
-                                                                         const int32_t* __restrict__ seg_start,
-                                                                         T* __restrict__ Kinv,
-                                                                         int32_t* __restrict__ Kpiv,
-                                                                         T* __restrict__ Kud, T* __restrict__ W,
-                                                                         unsigned long long* info, int level, int L) {
+__device__ __forceinline__ int row4_of_lane(int li) {
+  return sizeof(T) == 8 ? 4 * (li & 3) + (li >> 2) : li;
+}
+
+// Four consecutive rows i0 .. of a column of a child's product (r rows,
+// zero past them).  vec: r % 4 = 0, one access.
+template <typename T>
+__device__ __forceinline__ void load_col4(const T* col, int r, int i0, bool vec, T (&v)[4]) {
+  if (vec) {
+    typedef T V4 __attribute__((ext_vector_type(4), aligned(sizeof(T))));
+    const V4 x = *reinterpret_cast<const V4*>(col + min(i0, r - 4));
+#pragma unroll
+    for (int s = 0; s < 4; ++s) v[s] = i0 < r ? x[s] : T(0);
+  } else {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const T x = col[min(i0 + s, r - 1)];
+      v[s] = i0 + s < r ? x : T(0);
+    }
+  }
+}
+// Four consecutive rows i0 .. (below r) of a column of a child's W.
+template <typename T, typename V>
+__device__ __forceinline__ void store_col4(T* col, int r, int i0, bool vec, const V& acc) {
+  if (vec) {
+    typedef T V4 __attribute__((ext_vector_type(4), aligned(sizeof(T))));
+    if (i0 < r) {
+      V4 x;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) x[t] = acc[t];
+      *reinterpret_cast<V4*>(col + i0) = x;
+    }
+  } else {
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      if (i0 + t < r) col[i0 + t] = acc[t];
+  }
+}
+
+// 16 x 16 tile of a product of two LDS matrices (ld ldk): sum over 16 nt of A(li, k) B(k, li)
+template <typename T>
+__device__ __forceinline__ typename Mfma<T>::V tile_mm(const T* A, const T* B, int ldk, int nt, int li, int lq) {
+  typename Mfma<T>::V acc = vzero<typename Mfma<T>::V>();
+  for (int q = 0; q < nt; ++q) {
+    T av[4], bv[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int k = 16 * q + 4 * s + lq;
+      av[s] = A[li + k * ldk];
+      bv[s] = B[k + li * ldk];
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s) acc = Mfma<T>::mma(av[s], bv[s], acc);
+  }
+  return acc;
+}
+
+// In-place Gauss-Jordan inversion of the n x n matrix at K (n % 16 = 0, LDS),
+// 16-column panels: one wave runs a panel in registers, then every other wave
+// applies the panel's exchanges to its own 16 columns as one product,
+// K(i, c) = [i not a pivot row] K(i, c) + sum_j P(i, j) K(p_j, c), on MFMA.
+// The wave of the next panel goes straight on to it: one barrier per panel.
+// Entry (p_j, c) ends as K^{-1}(j, p_c); permuted() puts it in place.
+template <typename T, int NW, int NS, int NB>
+__device__ __forceinline__ void gj_invert(T* K, int ldk, int n, int nid, int tid, int w, int* s_pos, int* s_pan,
+                                          int* s_prow, int32_t* spiv, int p0, T* sud, PanelInfo pi) {
   using M = Mfma<T>;
   using V = typename M::V;
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  T* K = reinterpret_cast<T*>(smem_raw);  // n2 x n2 col-major, then the rhs chunk [c][k] (ld n2 + 1)
-  const int g = blockIdx.x;
-  const int a = 2 * g, b = 2 * g + 1;
-  const int n2 = 2 * r;
-  const int ncin = Rp + r;
-  const int64_t elems = (int64_t)r * ncin;
-  const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lq = lane >> 4;
-  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const T* Pa = segs + (int64_t)seg_start[a] * elems;
-  const T* Pb = segs + (int64_t)seg_start[b] * elems;
-  __shared__ int s_piv[128];
-  __shared__ T s_pv[128];
-  form_k_batched<T, kCf2Threads, 32, 8>(K, Pa, Pb, r, Rp, tid);
-  __syncthreads();
-  block_gj2(K, n2, lane, wid, s_piv, s_pv, info, ((unsigned long long)(L - level) << 44) | ((unsigned long long)g << 16));
-  __syncthreads();
-  T* Kg = Kinv + (int64_t)g * n2 * n2;
-  for (int e = tid; e < n2 * n2; e += kCf2Threads) Kg[e] = K[e];
-  if (tid < n2) {
-    Kpiv[(int64_t)g * n2 + tid] = s_piv[tid];
-    Kud[(int64_t)g * n2 + tid] = T(1) / s_pv[tid];
-  }
-  // B operand: K^{-1}(16 wid + li, 4 ks + lq)
-  const bool act = 16 * wid < n2;  // uniform
-  T bk[32];
-#pragma unroll
-  for (int ks = 0; ks < 32; ++ks) bk[ks] = (act && 4 * ks < n2) ? K[(16 * wid + li) + (4 * ks + lq) * n2] : T(0);
-  __syncthreads();  // K's LDS is reused for the right-hand sides
-  T* Rs = K;
-  const int ldr = n2 + 1;
-  T* Wg = W + (int64_t)g * n2 * Rp;
-  for (int c0 = 0; c0 < Rp; c0 += 64) {
-    {
-      RhsChunk<T, kCf2Threads, 16> rhs;
-      rhs.load(Pa, Pb, r, Rp, c0, tid);
-      rhs.store(Rs, r, tid);
-    }
+  constexpr int NT = 64 * NW;
+  const int lane = tid & 63, li = lane & 15, lq = lane >> 4, nb = n >> 4;
+  for (int jb = 0; jb < nb; ++jb) {
+    if (w == jb) gj_panel<T, NS>(K, ldk, n, nid, jb, lane, s_pos, s_pan, s_prow, spiv, p0, sud, pi);
     __syncthreads();
-    if (act) {
-      V acc[4];
+    if (w != jb && w < nb) {
+      T* Kc = K + (16 * w + li) * ldk;
+      T bv[4];
 #pragma unroll
-      for (int mb = 0; mb < 4; ++mb) acc[mb] = vzero<V>();
+      for (int ks = 0; ks < 4; ++ks) bv[ks] = Kc[s_prow[16 * jb + 4 * ks + lq]];
 #pragma unroll
-      for (int ks = 0; ks < 32; ++ks) {
-        if (4 * ks < n2) {  // uniform
-#pragma unroll
-          for (int mb = 0; mb < 4; ++mb) acc[mb] = M::mma(Rs[(16 * mb + li) * ldr + 4 * ks + lq], bk[ks], acc[mb]);
-        }
-      }
-      const int i = 16 * wid + li;
-#pragma unroll
-      for (int mb = 0; mb < 4; ++mb)
+      for (int rb = 0; rb < NB; ++rb) {
+        if (rb >= nb) continue;
+        V acc;
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-          const int c = c0 + 16 * mb + M::crow(lq, t);
-          if (c < Rp) Wg[i + (int64_t)c * n2] = acc[mb][t];
+          const int row = 16 * rb + M::crow(lq, t);
+          const T x = Kc[row];
+          acc[t] = s_pan[row] == jb ? T(0) : x;
         }
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) acc = M::mma(K[16 * rb + li + (16 * jb + 4 * ks + lq) * ldk], bv[ks], acc);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) Kc[16 * rb + M::crow(lq, t)] = acc[t];
+      }
+    }
+  }
+  __syncthreads();
+  constexpr int NPT = 16 * NB * 16 * NB / NT;
+  T v[NPT];
+  BlockWalk it(tid, NT, n);
+#pragma unroll
+  for (int u = 0; u < NPT; ++u) {
+    v[u] = it.c < n ? K[it.k + it.c * ldk] : T(0);
+    it.next();
+  }
+  __syncthreads();
+  BlockWalk st(tid, NT, n);
+#pragma unroll
+  for (int u = 0; u < NPT; ++u) {
+    if (st.c < n) K[s_pos[st.k] + s_prow[st.c] * ldk] = v[u];
+    st.next();
+  }
+  __syncthreads();
+}
+
+// Coupling factor (any r <= 64), K in LDS with both halves padded to
+// h = r rounded up to 16: [[T_a, I], [I, T_b]] of size 2h, the padding of T_a
+// and T_b zero.  The elimination is a chain of dependent steps, 0.5 us each in
+// FP64 whatever the number of parents, so the number of steps decides.  When
+// every |T| < 1, partial pivoting on K takes the identity's ones for its first
+// h pivots (row h + j in column j, no other candidate reaches 1), which leaves
+// S = I - T_a T_b for the other h; so S is formed on MFMA, inverted with h
+// steps, and with M = S^{-1}
+//   K^{-1} = [[-T_b M, I + T_b M T_a], [M, -M T_a]].
+// Otherwise all 2h steps run on K.  Pivots, interchanges and a singular K are
+// those of LU with partial pivoting on K in both cases.  Rank 32, FP64, one
+// parent: 41 us with 64 steps (one barrier per step on four waves: 53 us);
+// a factorization's 12 levels at N = 2^20: 0.78 ms (1.37 ms), 9 levels of rank
+// 64 at N = 2^17: 0.95 ms (1.93 ms).  NW = 4 waves up to
+// 2h = 64, 8 up to 128.  W = K^{-1} rhs then streams 16 columns per wave from
+// and to memory, K^{-1} read from LDS.
+// (Ranks that correct their products, couple_corrects, leave W to
+// couple_apply_kernel and keep T_a and T_b in Kt for it: W is null.)
+template <typename T, int NW>
+__global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 1) void couple_factor_kernel(
+    int r, int kp, int Rp, const T* __restrict__ segs, const int32_t* __restrict__ seg_start, T* __restrict__ Kinv,
+    int32_t* __restrict__ Kpiv, T* __restrict__ Kud, T* __restrict__ Kt, T* __restrict__ W, unsigned long long* info,
+    int level, int L) {
+  using M = Mfma<T>;
+  using V = typename M::V;
+  constexpr int NT = 64 * NW, NB = NW, TPW = NW / 4;  // threads, 16-row blocks of K, tiles of S per wave
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  T* K = reinterpret_cast<T*>(smem_raw);
+  __shared__ int s_pos[16 * NB], s_pan[16 * NB], s_prow[16 * NB];
+  const int g = blockIdx.x;
+  const int h = (r + 15) & ~15, n = 2 * h, n2 = 2 * r;
+  const int ldk = n + 1;  // rows and columns of a block on different banks
+  const int64_t elems = (int64_t)r * (Rp + r);
+  const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lq = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const T* Pa = segs + (int64_t)seg_start[2 * g] * elems;
+  const T* Pb = segs + (int64_t)seg_start[2 * g + 1] * elems;
+  int32_t* pvg = Kpiv + (int64_t)g * n;
+  T* udg = Kud + (int64_t)g * n;
+  bool small = true;
+  {
+    // K from the products' last r columns, loads in batches
+    constexpr int B = 8;
+    BlockWalk it(tid, NT, n);
+    while (it.c < n) {
+      T v[B];
+      BlockWalk st = it;
+#pragma unroll
+      for (int u = 0; u < B; ++u) {
+        const int i = it.k, j = it.c;
+        T x = i - j == h || j - i == h ? T(1) : T(0);
+        if (i < r && j < r) x = Pa[i + (int64_t)(Rp + j) * r];
+        else if (i >= h && j >= h && i < h + r && j < h + r) x = Pb[(i - h) + (int64_t)(Rp + j - h) * r];
+        v[u] = x;
+        it.next();
+      }
+#pragma unroll
+      for (int u = 0; u < B; ++u) {
+        if (st.c < n) {
+          K[st.k + st.c * ldk] = v[u];
+          if ((st.k < h) == (st.c < h)) small = small && fabs(v[u]) < T(1);
+        }
+        st.next();
+      }
+    }
+    for (int i = tid; i < n; i += NT) {
+      s_pos[i] = i;
+      s_pan[i] = -1;
+    }
+  }
+  small = __syncthreads_and(small);
+  const unsigned long long base = ((unsigned long long)(L - level) << 44) | ((unsigned long long)g << 16);
+  const int nt = h >> 4;
+  if (small) {
+    T* S = K + h * ldk;         // rows 0 .., columns h ..
+    T* X = K + h;               // rows h .., columns 0 ..
+    T* Tb = K + h + h * ldk;
+    int ti[TPW], tj[TPW];
+    bool have[TPW];
+#pragma unroll
+    for (int u = 0; u < TPW; ++u) {
+      const int id = w + NW * u;
+      have[u] = id < nt * nt;
+      ti[u] = 16 * (have[u] ? id % nt : 0);
+      tj[u] = 16 * (have[u] ? id / nt : 0);
+    }
+#pragma unroll
+    for (int u = 0; u < TPW; ++u)
+      if (have[u]) {
+        const V c = tile_mm(K + ti[u], Tb + tj[u] * ldk, ldk, nt, li, lq);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const int i = ti[u] + M::crow(lq, t), j = tj[u] + li;
+          S[i + j * ldk] = (i == j ? T(1) : T(0)) - c[t];
+        }
+      }
+    for (int j = tid; j < h; j += NT) {
+      pvg[j] = h + j;
+      udg[j] = T(1);
     }
     __syncthreads();
+    gj_invert<T, NW, 1, NW / 2>(S, ldk, h, r, tid, w, s_pos, s_pan, s_prow, pvg + h, h, udg + h,
+                                PanelInfo{info, base, h, 0, r});
+#pragma unroll
+    for (int u = 0; u < TPW; ++u)
+      if (have[u]) {
+        const V c = tile_mm(S + ti[u], K + tj[u] * ldk, ldk, nt, li, lq);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) X[ti[u] + M::crow(lq, t) + (tj[u] + li) * ldk] = c[t];  // M T_a
+      }
+    __syncthreads();
+    V x2[TPW], x3[TPW], m[TPW], x1[TPW];
+#pragma unroll
+    for (int u = 0; u < TPW; ++u)
+      if (have[u]) {
+        x2[u] = tile_mm(Tb + ti[u], S + tj[u] * ldk, ldk, nt, li, lq);
+        x3[u] = tile_mm(Tb + ti[u], X + tj[u] * ldk, ldk, nt, li, lq);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const int e = ti[u] + M::crow(lq, t) + (tj[u] + li) * ldk;
+          m[u][t] = S[e];
+          x1[u][t] = X[e];
+        }
+      }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < TPW; ++u)
+      if (have[u]) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const int i = ti[u] + M::crow(lq, t), j = tj[u] + li, e = i + j * ldk;
+          K[e] = -x2[u][t];
+          S[e] = (i == j ? T(1) : T(0)) + x3[u][t];
+          X[e] = m[u][t];
+          Tb[e] = -x1[u][t];
+        }
+      }
+    __syncthreads();
+  } else {
+    gj_invert<T, NW, NW / 4, NB>(K, ldk, n, n, tid, w, s_pos, s_pan, s_prow, pvg, 0, udg,
+                                 PanelInfo{info, base, h, h - r, 0});
   }
+  // K^{-1} without the padding of the halves
+  T* Kg = Kinv + (int64_t)g * kp * kp;
+  for (BlockWalk e(tid, NT, kp); e.c < kp; e.next()) {
+    const int i = e.k < r ? e.k : e.k + h - r, j = e.c < r ? e.c : e.c + h - r;
+    Kg[e.k + e.c * kp] = e.k < n2 && e.c < n2 ? K[i + j * ldk] : T(0);
+  }
+  if (!W) {
+    T* Tg = Kt + (int64_t)g * 2 * r * r;
+    for (int e = tid; e < r * r; e += NT) {
+      Tg[e] = Pa[(int64_t)Rp * r + e];
+      Tg[r * r + e] = Pb[(int64_t)Rp * r + e];
+    }
+    return;
+  }
+  // W = K^{-1} rhs: wave w takes the column blocks w, w + NW, ..; row blocks
+  // 0 .. nt - 1 are the first child's, nt .. 2 nt - 1 the second's
+  const bool vec = r % 4 == 0;
+  T* Wg = W + (int64_t)g * n2 * Rp;
+  for (int c0 = 16 * w; c0 < Rp; c0 += 16 * NW) {
+    const int64_t c = min(c0 + li, Rp - 1);
+    T bv[NB][4];
+#pragma unroll
+    for (int q = 0; q < NB; ++q)
+      if (q < 2 * nt) load_col4((q < nt ? Pa : Pb) + c * r, r, 16 * (q < nt ? q : q - nt) + 4 * lq, vec, bv[q]);
+#pragma unroll 2
+    for (int rb = 0; rb < 2 * nt; ++rb) {
+      V acc = vzero<V>();
+#pragma unroll
+      for (int q = 0; q < NB; ++q)
+        if (q < 2 * nt) {
+#pragma unroll
+          for (int s = 0; s < 4; ++s)
+            acc = M::mma(K[16 * rb + row4_of_lane<T>(li) + (16 * q + 4 * lq + s) * ldk], bv[q][s], acc);
+        }
+      if (c0 + li < Rp)
+        store_col4(Wg + c * n2 + (rb < nt ? 0 : r), r, 16 * (rb < nt ? rb : rb - nt) + 4 * lq, vec, acc);
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// couple_solve
+// ---------------------------------------------------------------------------
+// Four waves per parent, wave w on the 16-row blocks w, w + 4 of the result
+// (blocks of either child's rows); K^{-1} (or its transpose) comes from memory
+// as MFMA A operand, all of a block's loads in flight together, and serves
+// every 16-column block of the right-hand sides.  Bound by that one latency:
+// 11 levels of 32-column adjoint solves at N = 2^18, rank 32 take 125 us (one
+// wave per parent with four columns at a time: 320 us), and one column gains
+// too (rank 64, 9 levels: 116 against 312 us).
+// REF: w -> w + K^{-1} (rhs - K w) once, the waves exchanging w and the
+// residual through LDS.  A product with K^{-1} leaves an error of cond(K)^2
+// roundings where substitution with an LU leaves cond(K); the correction
+// brings it back.  With it W and the factors of an uneven tree (N = 102846,
+// ranks 37 .. 31) take 1.01 ms and a 3-column solve's levels 0.15 ms (LU and
+// substitution: 1.84 and 0.32 ms).
+template <typename T, int TRANS, int NB, bool REF>
+__global__ __launch_bounds__(256) void couple_apply_kernel(int r, int kp, int nrhs, int64_t elems,
+                                                           const T* __restrict__ segs, const int32_t* __restrict__ seg_start,
+                                                           const T* __restrict__ Kinv, const T* __restrict__ Kt,
+                                                           T* __restrict__ w_) {
+  using M = Mfma<T>;
+  using V = typename M::V;
+  constexpr int NR = NB / 4;  // row blocks of a wave
+  __shared__ T xs[REF ? 2 : 1][REF ? NB * 256 : 1];  // [w, residual]: block, lane, 4 rows
+  const int g = blockIdx.x;
+  const int n2 = 2 * r, nt = (r + 15) >> 4;
+  const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lq = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const T* Pa = segs + (int64_t)seg_start[2 * g] * elems;
+  const T* Pb = segs + (int64_t)seg_start[2 * g + 1] * elems;
+  const T* Kg = Kinv + (int64_t)g * kp * kp;
+  T* wg = w_ + (int64_t)g * n2 * nrhs;
+  const bool vec = r % 4 == 0;
+  T av[NR][NB][4];
+#pragma unroll
+  for (int u = 0; u < NR; ++u) {
+    const int rb = w + 4 * u;
+    if (rb >= 2 * nt) continue;
+    const int half = rb >= nt, row = half * r + min(16 * (half ? rb - nt : rb) + row4_of_lane<T>(li), r - 1);
+#pragma unroll
+    for (int q = 0; q < NB; ++q)
+      if (q < 2 * nt) {
+        const int kh = q >= nt, k0 = 16 * (kh ? q - nt : q) + 4 * lq;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const int k = kh * r + min(k0 + s, r - 1);
+          av[u][q][s] = TRANS ? Kg[k + row * kp] : Kg[row + k * kp];
+        }
+      }
+  }
+  for (int c0 = 16 * blockIdx.y; c0 < nrhs; c0 += 16 * gridDim.y) {
+    const int64_t c = min(c0 + li, nrhs - 1);
+    T bv[NB][4];
+#pragma unroll
+    for (int q = 0; q < NB; ++q)
+      if (q < 2 * nt) load_col4((q < nt ? Pa : Pb) + c * r, r, 16 * (q < nt ? q : q - nt) + 4 * lq, vec, bv[q]);
+    V x[NR];
+#pragma unroll
+    for (int u = 0; u < NR; ++u) {
+      x[u] = vzero<V>();
+      if (w + 4 * u < 2 * nt) {
+#pragma unroll
+        for (int q = 0; q < NB; ++q)
+          if (q < 2 * nt) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) x[u] = M::mma(av[u][q][s], bv[q][s], x[u]);
+          }
+      }
+    }
+    if constexpr (REF) {
+#pragma unroll
+      for (int u = 0; u < NR; ++u)
+        if (w + 4 * u < 2 * nt) {
+#pragma unroll
+          for (int s = 0; s < 4; ++s) {
+            const int rb = w + 4 * u, i = 16 * (rb >= nt ? rb - nt : rb) + 4 * lq + s;
+            xs[0][(rb * 64 + lane) * 4 + s] = i < r ? x[u][s] : T(0);
+          }
+        }
+      __syncthreads();
+      // rhs - K x (K^T x): T x of the own child, x of the other
+#pragma unroll
+      for (int u = 0; u < NR; ++u) {
+        const int rb = w + 4 * u;
+        if (rb >= 2 * nt) continue;
+        const int half = rb >= nt, i0 = 16 * (half ? rb - nt : rb), other = half ? rb - nt : rb + nt;
+        const T* Tg = Kt + (int64_t)g * 2 * r * r + half * r * r;
+        const int i = min(i0 + row4_of_lane<T>(li), r - 1);
+        V acc = vzero<V>();
+        for (int q = 0; q < nt; ++q) {
+          T xv[4], tv[4];
+#pragma unroll
+          for (int s = 0; s < 4; ++s) {
+            const int k = min(16 * q + 4 * lq + s, r - 1);
+            tv[s] = TRANS ? Tg[k + i * r] : Tg[i + k * r];
+            xv[s] = xs[0][((q + half * nt) * 64 + lane) * 4 + s];
+          }
+#pragma unroll
+          for (int s = 0; s < 4; ++s) acc = M::mma(tv[s], xv[s], acc);
+        }
+        T rhs[4];
+        load_col4((half ? Pb : Pa) + c * r, r, i0 + 4 * lq, vec, rhs);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const T res = rhs[s] - xs[0][(other * 64 + lane) * 4 + s] - acc[s];
+          xs[1][(rb * 64 + lane) * 4 + s] = i0 + 4 * lq + s < r ? res : T(0);
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < NR; ++u)
+        if (w + 4 * u < 2 * nt) {
+#pragma unroll
+          for (int q = 0; q < NB; ++q)
+            if (q < 2 * nt) {
+#pragma unroll
+              for (int s = 0; s < 4; ++s) bv[q][s] = xs[1][(q * 64 + lane) * 4 + s];
+            }
+          V d = vzero<V>();
+#pragma unroll
+          for (int q = 0; q < NB; ++q)
+            if (q < 2 * nt) {
+#pragma unroll
+              for (int s = 0; s < 4; ++s) d = M::mma(av[u][q][s], bv[q][s], d);
+            }
+          x[u] += d;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < NR; ++u) {
+      const int rb = w + 4 * u, half = rb >= nt;
+      if (rb < 2 * nt && c0 + li < nrhs)
+        store_col4(wg + c * n2 + half * r, r, 16 * (half ? rb - nt : rb) + 4 * lq, vec, x[u]);
+    }
+  }
+}
+
+template <typename T>
+static hipError_t launch_apply(hipStream_t s, int trans, int nparents, int r, int kp, int ncols, int64_t elems,
+                               const T* segs, const int32_t* d_seg_start, const T* Kinv, const T* Kt, T* w) {
+  if (nparents == 0 || r == 0 || ncols == 0) return hipSuccess;
+  if (r > kCfMaxRows / 2 || kp < 2 * r) return hipErrorInvalidValue;
+  // few parents: column blocks over workgroups too
+  const int blocks = (ncols + 15) / 16;
+  const dim3 grid(nparents, std::min(blocks, std::max(1, 1024 / nparents)));
+#define HODLR_CA(TR, NB, REF)                                                                                     \
+  hipLaunchKernelGGL((couple_apply_kernel<T, TR, NB, REF>), grid, dim3(256), 0, s, r, kp, ncols, elems, segs,      \
+                     d_seg_start, Kinv, Kt, w)
+#define HODLR_CAT(NB, REF)          \
+  if (trans) HODLR_CA(1, NB, REF);  \
+  else HODLR_CA(0, NB, REF)
+  if (couple_corrects(r)) {
+    if (r > 32) {
+      HODLR_CAT(8, true);
+    } else {
+      HODLR_CAT(4, true);
+    }
+  } else if (r > 32) {
+    HODLR_CAT(8, false);
+  } else {
+    HODLR_CAT(4, false);
+  }
+#undef HODLR_CAT
+#undef HODLR_CA
+  return hipGetLastError();
 }
 
 template <typename T>
 hipError_t launch_couple_factor(hipStream_t s, int nparents, int r, int kp, int Rp, const T* segs,
-                                const int32_t* d_seg_start, T* Klu, int32_t* Kpiv, int32_t* Kperm, T* Kud, T* Kinv,
-                                T* W, unsigned long long* info, int level, int L) {
+                                const int32_t* d_seg_start, T* Kinv, int32_t* Kpiv, T* Kud, T* Kt, T* W,
+                                unsigned long long* info, int level, int L) {
   if (nparents == 0 || r == 0) return hipSuccess;
-  if (kp > 128) return hipErrorInvalidValue;
-  if (couple_uses_inverse(r) && 2 * r > 64) {
-    const size_t smem_inv = sizeof(T) * std::max<size_t>((size_t)4 * r * r, (size_t)64 * (2 * r + 1));
-    auto ki = couple_factor_inv2_kernel<T>;
-    hipError_t e = hipFuncSetAttribute((const void*)ki, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_inv);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(ki, dim3(nparents), dim3(kCf2Threads), smem_inv, s, r, Rp, segs, d_seg_start, Klu, Kpiv, Kud, W,
-                       info, level, L);
-    return hipGetLastError();
+  const int n = 2 * ((r + 15) & ~15);
+  if (n > kCfMaxRows || kp < 2 * r || kp > n) return hipErrorInvalidValue;
+  const size_t smem = sizeof(T) * (size_t)n * (n + 1);
+  T* const Wf = couple_corrects(r) ? nullptr : W;
+#define HODLR_CF(NW)                                                                                              \
+  {                                                                                                               \
+    auto k = couple_factor_kernel<T, NW>;                                                                         \
+    hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);      \
+    if (e != hipSuccess) return e;                                                                                \
+    hipLaunchKernelGGL(k, dim3(nparents), dim3(64 * NW), smem, s, r, kp, Rp, segs, d_seg_start, Kinv, Kpiv, Kud, Kt, \
+                       Wf, info, level, L);                                                                       \
   }
-  if (couple_uses_inverse(r)) {
-    const size_t smem_inv = sizeof(T) * std::max<size_t>((size_t)4 * r * r, (size_t)64 * (2 * r + 1));
-    auto ki = couple_factor_inv_kernel<T>;
-    hipError_t e = hipFuncSetAttribute((const void*)ki, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_inv);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(ki, dim3(nparents), dim3(kCfThreads), smem_inv, s, r, Rp, segs, d_seg_start, Klu, Kpiv, Kud, W,
-                       info, level, L);
-    return hipGetLastError();
-  }
-  const size_t smem = sizeof(T) * (size_t)4 * r * r;
-  auto k = couple_factor_kernel<T>;
-  hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k, dim3(nparents), dim3(kCfThreads), smem, s, r, kp, Rp, segs, d_seg_start, Klu, Kpiv, Kperm,
-                     Kud, W, info, level, L);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(couple_dinv_kernel<T>, dim3(nparents), dim3(kCfThreads), 0, s, 2 * r, kp, (const T*)Klu, Kinv);
-  return hipGetLastError();
+  if (n <= 64) HODLR_CF(4) else HODLR_CF(8)
+#undef HODLR_CF
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || !couple_corrects(r)) return e;
+  return launch_apply<T>(s, 0, nparents, r, kp, Rp, (int64_t)r * (Rp + r), segs, d_seg_start, Kinv, Kt, W);
 }
 template hipError_t launch_couple_factor<double>(hipStream_t, int, int, int, int, const double*, const int32_t*,
-                                                 double*, int32_t*, int32_t*, double*, double*, double*,
-                                                 unsigned long long*, int, int);
-template hipError_t launch_couple_factor<float>(hipStream_t, int, int, int, int, const float*, const int32_t*,
-                                                float*, int32_t*, int32_t*, float*, float*, float*,
-                                                unsigned long long*, int, int);
-
-// ---------------------------------------------------------------------------
-// couple_solve: one wave per parent, columns in groups of kCsCols
-// ---------------------------------------------------------------------------
-constexpr int kCsCols = 4;
-
-template <typename T, int TRANS>
-__global__ __launch_bounds__(64) void couple_solve_kernel(int r, int kp, int nrhs, const T* __restrict__ segs,
-                                                          const int32_t* __restrict__ seg_start,
-                                                          const T* __restrict__ Klu, const int32_t* __restrict__ Kperm,
-                                                          const T* __restrict__ Kud, T* __restrict__ w) {
-  const int g = blockIdx.x;
-  const int a = 2 * g, b = 2 * g + 1;
-  const int n2 = 2 * r;
-  const int lane = threadIdx.x;
-  const int64_t elems = (int64_t)r * nrhs;
-  const T* Kf = Klu + (int64_t)g * kp * kp;
-  const int32_t* pm = Kperm + (int64_t)g * kp;
-  const T* kud = Kud + (int64_t)g * kp;
-  T* wg = w + (int64_t)g * n2 * nrhs;
-  for (int cbase = 0; cbase < nrhs; cbase += kCsCols) {
-    T x[2][kCsCols];
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const int row = s * 64 + lane;
-#pragma unroll
-      for (int c = 0; c < kCsCols; ++c) {
-        T v = T(0);
-        if (row < n2 && cbase + c < nrhs) {
-          const int src = TRANS ? row : pm[row];
-          const int node = src < r ? a : b;
-          v = seg_sum(segs, seg_start, node, elems, (src % r) + (int64_t)(cbase + c) * r);
-        }
-        x[s][c] = v;
-      }
-    }
-    wave_lu_solve<T, kCsCols, TRANS>(x, Kf, kud, n2, kp, lane);
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const int row = s * 64 + lane;
-#pragma unroll
-      for (int c = 0; c < kCsCols; ++c)
-        if (row < n2 && cbase + c < nrhs) {
-          const int dst = TRANS ? pm[row] : row;
-          wg[dst + (int64_t)(cbase + c) * n2] = x[s][c];
-        }
-    }
-  }
-}
-
-// Same solve for 2r <= 64 with the factor staged in LDS, lane i owning row i
-// of the right-hand sides: each substitution step reads one LDS entry per lane
-// (prefetched a step ahead) and broadcasts x_j with readlane.  The loops are
-// not unrolled: the code runs once per wave and would otherwise be bound by
-// instruction fetch.
-template <typename T, int TRANS>
-__global__ __launch_bounds__(64) void couple_solve_reg_kernel(int r, int kp, int nrhs, const T* __restrict__ segs,
-                                                              const int32_t* __restrict__ seg_start,
-                                                              const T* __restrict__ Klu,
-                                                              const int32_t* __restrict__ Kperm,
-                                                              const T* __restrict__ Kud, T* __restrict__ w) {
-  __shared__ T Ks[64 * 64];  // Ks[j * 64 + i] = K(i, j) (TRANS: K(j, i))
-  const int g = blockIdx.x;
-  const int a = 2 * g, b = 2 * g + 1;
-  const int n2 = 2 * r;
-  const int lane = threadIdx.x;
-  const int64_t elems = (int64_t)r * nrhs;
-  const T* Kf = Klu + (int64_t)g * kp * kp;
-  const int32_t* pm = Kperm + (int64_t)g * kp;
-  T* wg = w + (int64_t)g * n2 * nrhs;
-  const bool valid = lane < n2;
-  const int ln = valid ? lane : 0;
-  for (int j = 0; j < n2; ++j) Ks[j * 64 + lane] = TRANS ? Kf[j + (int64_t)ln * kp] : Kf[ln + (int64_t)j * kp];
-  const T dinv = valid ? Kud[(int64_t)g * kp + lane] : T(1);
-  const int src = TRANS ? ln : pm[ln];
-  const int64_t sbase = (int64_t)seg_start[src < r ? a : b] * elems + (src % r);
-  const int dst = TRANS ? pm[ln] : ln;
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  for (int c0 = 0; c0 < nrhs; c0 += kCsCols) {
-    T x[kCsCols];
-#pragma unroll
-    for (int c = 0; c < kCsCols; ++c) {
-      const T v = segs[sbase + (int64_t)min(c0 + c, nrhs - 1) * r];
-      x[c] = (valid && c0 + c < nrhs) ? v : T(0);
-    }
-    // forward: L (unit lower) or U^T (lower); backward: U or L^T (unit upper)
-    T f = Ks[lane];
-    for (int j = 0; j < n2; ++j) {
-      const T fj = f;
-      f = Ks[min(j + 1, 63) * 64 + lane];
-      const T dj = TRANS ? bcast(dinv, j) : T(1);
-#pragma unroll
-      for (int c = 0; c < kCsCols; ++c) {
-        const T xj = bcast(x[c], j) * dj;
-        if (TRANS && lane == j) x[c] = xj;
-        else if (lane > j) x[c] -= fj * xj;
-      }
-    }
-    f = Ks[(n2 - 1) * 64 + lane];
-    for (int j = n2 - 1; j >= 0; --j) {
-      const T fj = f;
-      f = Ks[max(j - 1, 0) * 64 + lane];
-      const T dj = TRANS ? T(1) : bcast(dinv, j);
-#pragma unroll
-      for (int c = 0; c < kCsCols; ++c) {
-        const T xj = bcast(x[c], j) * dj;
-        if (!TRANS && lane == j) x[c] = xj;
-        else if (lane < j) x[c] -= fj * xj;
-      }
-    }
-    if (valid) {
-#pragma unroll
-      for (int c = 0; c < kCsCols; ++c)
-        if (c0 + c < nrhs) wg[dst + (int64_t)(c0 + c) * n2] = x[c];
-    }
-  }
-}
-
-// Solves with an explicit K^{-1} (factors from couple_factor_inv_kernel or
-// couple_factor_inv2_kernel): one wave per parent, lane i forms rows
-// i + 64 s (s < NS) of w = K^{-1} rhs (TRANS: K^{-T} rhs), the
-// right-hand-side columns broadcast from LDS.
-template <typename T, int TRANS, int NS>
-__global__ __launch_bounds__(64) void couple_apply_kernel(int r, int nrhs, const T* __restrict__ segs,
-                                                          const int32_t* __restrict__ seg_start,
-                                                          const T* __restrict__ Kinv, T* __restrict__ w) {
-  __shared__ T xs[kCsCols * 64 * NS];
-  const int g = blockIdx.x;
-  const int a = 2 * g, b = 2 * g + 1;
-  const int n2 = 2 * r;
-  const int lane = threadIdx.x;
-  const int64_t elems = (int64_t)r * nrhs;
-  const T* Kg = Kinv + (int64_t)g * n2 * n2;
-  T* wg = w + (int64_t)g * n2 * nrhs;
-  bool valid[NS];
-  int ln[NS];
-  int64_t sbase[NS];
-#pragma unroll
-  for (int sl = 0; sl < NS; ++sl) {
-    const int row = 64 * sl + lane;
-    valid[sl] = row < n2;
-    ln[sl] = valid[sl] ? row : 0;
-    sbase[sl] = (int64_t)seg_start[ln[sl] < r ? a : b] * elems + (ln[sl] % r);
-  }
-  for (int c0 = 0; c0 < nrhs; c0 += kCsCols) {
-#pragma unroll
-    for (int sl = 0; sl < NS; ++sl)
-#pragma unroll
-      for (int c = 0; c < kCsCols; ++c) {
-        const T v = segs[sbase[sl] + (int64_t)min(c0 + c, nrhs - 1) * r];
-        xs[c * 64 * NS + 64 * sl + lane] = (valid[sl] && c0 + c < nrhs) ? v : T(0);
-      }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    T acc[NS][kCsCols];
-#pragma unroll
-    for (int sl = 0; sl < NS; ++sl)
-#pragma unroll
-      for (int c = 0; c < kCsCols; ++c) acc[sl][c] = T(0);
-#pragma unroll 8
-    for (int k = 0; k < n2; ++k) {
-#pragma unroll
-      for (int sl = 0; sl < NS; ++sl) {
-        const T kv = TRANS ? Kg[k + (int64_t)ln[sl] * n2] : Kg[ln[sl] + (int64_t)k * n2];
-#pragma unroll
-        for (int c = 0; c < kCsCols; ++c) acc[sl][c] += kv * xs[c * 64 * NS + k];
-      }
-    }
-#pragma unroll
-    for (int sl = 0; sl < NS; ++sl)
-      if (valid[sl]) {
-#pragma unroll
-        for (int c = 0; c < kCsCols; ++c)
-          if (c0 + c < nrhs) wg[64 * sl + lane + (int64_t)(c0 + c) * n2] = acc[sl][c];
-      }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  }
-}
+                                                 double*, int32_t*, double*, double*, double*, unsigned long long*, int,
+                                                 int);
+template hipError_t launch_couple_factor<float>(hipStream_t, int, int, int, int, const float*, const int32_t*, float*,
+                                                int32_t*, float*, float*, float*, unsigned long long*, int, int);
 
 template <typename T>
 hipError_t launch_couple_solve(hipStream_t s, int trans, int nparents, int r, int kp, int nrhs, const T* segs,
-                               const int32_t* d_seg_start, const T* Klu, const int32_t* Kperm, const T* Kud, T* w) {
-  if (nparents == 0 || r == 0 || nrhs == 0) return hipSuccess;
-  if (couple_uses_inverse(r)) {
-#define HODLR_CA(TR, NS)                                                                                            \
-  hipLaunchKernelGGL((couple_apply_kernel<T, TR, NS>), dim3(nparents), dim3(64), 0, s, r, nrhs, segs, d_seg_start, \
-                     Klu, w)
-    if (2 * r > 64) {
-      if (trans) HODLR_CA(1, 2);
-      else HODLR_CA(0, 2);
-    } else {
-      if (trans) HODLR_CA(1, 1);
-      else HODLR_CA(0, 1);
-    }
-#undef HODLR_CA
-    return hipGetLastError();
-  }
-  if (2 * r <= 64) {
-    if (trans)
-      hipLaunchKernelGGL((couple_solve_reg_kernel<T, 1>), dim3(nparents), dim3(64), 0, s, r, kp, nrhs, segs,
-                         d_seg_start, Klu, Kperm, Kud, w);
-    else
-      hipLaunchKernelGGL((couple_solve_reg_kernel<T, 0>), dim3(nparents), dim3(64), 0, s, r, kp, nrhs, segs,
-                         d_seg_start, Klu, Kperm, Kud, w);
-    return hipGetLastError();
-  }
-  if (trans)
-    hipLaunchKernelGGL((couple_solve_kernel<T, 1>), dim3(nparents), dim3(64), 0, s, r, kp, nrhs, segs, d_seg_start,
-                       Klu, Kperm, Kud, w);
-  else
-    hipLaunchKernelGGL((couple_solve_kernel<T, 0>), dim3(nparents), dim3(64), 0, s, r, kp, nrhs, segs, d_seg_start,
-                       Klu, Kperm, Kud, w);
-  return hipGetLastError();
+                               const int32_t* d_seg_start, const T* Kinv, const T* Kt, T* w) {
+  return launch_apply<T>(s, trans, nparents, r, kp, nrhs, (int64_t)r * nrhs, segs, d_seg_start, Kinv, Kt, w);
 }
 template hipError_t launch_couple_solve<double>(hipStream_t, int, int, int, int, int, const double*, const int32_t*,
-                                                const double*, const int32_t*, const double*, double*);
+                                                const double*, const double*, double*);
 template hipError_t launch_couple_solve<float>(hipStream_t, int, int, int, int, int, const float*, const int32_t*,
-                                               const float*, const int32_t*, const float*, float*);
+                                               const float*, const float*, float*);
 
 }  // namespace hodlr

@@ -348,12 +348,11 @@ struct hodlr_factors {
   void* udinv = nullptr;
   void* invl = nullptr;  // leaf LU scratch: inverted diagonal blocks of L
   void* Y = nullptr;
-  std::vector<int64_t> koff, kvoff, kioff;  // per parent level p: offsets of K blocks / K vectors / K inverses
-  void* Klu = nullptr;
+  std::vector<int64_t> koff, kvoff, ktoff;  // per parent level p: offsets of K^{-1} blocks / K vectors / T blocks
+  void* Kinv = nullptr;
+  void* Kt = nullptr;
   int32_t* Kpiv = nullptr;
-  int32_t* Kperm = nullptr;
   void* Kud = nullptr;
-  void* Kinv = nullptr;  // inverted 16 x 16 diagonal blocks of the K factors
   // factor workspace
   void* W = nullptr;
   void* P = nullptr;
@@ -517,8 +516,10 @@ void plan(hodlr_factors* F, int q0) {
 
 size_t tsz(hodlr_dtype c) { return c == HODLR_F64 ? 8 : 4; }
 
-// leading dimension of a stored K factor: 2r rounded up to 16
+// leading dimension of a stored K^{-1}: 2r rounded up to 16; pivots kept per
+// parent: two halves of r rounded up to 16
 int kpad(int r) { return (2 * r + 15) & ~15; }
+int kvecs(int r) { return 2 * ((r + 15) & ~15); }
 
 hodlr_status allocate_factors(hodlr_factors* F, hipStream_t st) {
   DevMem& M = F->mem;
@@ -561,23 +562,22 @@ hodlr_status allocate_factors(hodlr_factors* F, hipStream_t st) {
   }
   F->koff.assign(L + 1, 0);
   F->kvoff.assign(L + 1, 0);
-  F->kioff.assign(L + 1, 0);
-  int64_t kk = 0, kv = 0, ki = 0;
+  F->ktoff.assign(L + 1, 0);
+  int64_t kk = 0, kv = 0, kt = 0;
   size_t wmax = 0, pmax = 0, segmax = 0;
   for (int p = 0; p < L; ++p) {
     const int r = F->ranks[p];  // r_{p+1}
     const int kp = kpad(r);
     F->koff[p] = kk;
     F->kvoff[p] = kv;
-    F->kioff[p] = ki;
+    F->ktoff[p] = kt;
+    if (couple_corrects(r)) kt += (int64_t(1) << p) * 2 * r * r;
     kk += (int64_t(1) << p) * kp * kp;
-    kv += (int64_t(1) << p) * kp;
-    ki += (int64_t(1) << p) * 2 * (kp / 16) * 256;
+    kv += (int64_t(1) << p) * kvecs(r);
     wmax = std::max(wmax, (size_t)(int64_t(1) << p) * 2 * r * F->Rp[p]);
   }
   F->koff[L] = kk;
   F->kvoff[L] = kv;
-  F->kioff[L] = ki;
   for (int p = 1; p <= L; ++p) {
     const int q = fwd_prod_tiles(F, p);
     const size_t elems = (size_t)F->ranks[p - 1] * F->Rp[p];
@@ -585,11 +585,10 @@ hodlr_status allocate_factors(hodlr_factors* F, hipStream_t st) {
     const ProdPlan& pp = F->prods[{q, p}];
     segmax = std::max(segmax, (pp.buf_items[0] + pp.buf_items[1]) * elems);
   }
-  reserve(&F->Klu, (size_t)kk * ts);
+  reserve(&F->Kinv, (size_t)kk * ts);
+  reserve(&F->Kt, (size_t)kt * ts);
   M.reserve(&F->Kpiv, (size_t)kv);
-  M.reserve(&F->Kperm, (size_t)kv);
   reserve(&F->Kud, (size_t)kv * ts);
-  reserve(&F->Kinv, (size_t)ki * ts);
   reserve(&F->W, wmax * ts);
   reserve(&F->P, pmax * ts);
   reserve(&F->segbuf, segmax * ts);
@@ -657,13 +656,9 @@ hodlr_status run_factor(hodlr_factors* F, hipStream_t st, int bf) {
       if (s) return s;
       const int kp = kpad(r);
       HL("couple_factor", (launch_couple_factor<T>(st, 1 << p, r, kp, Rp, segs, seg_start,
-                                                   tp<T>(F->Klu) + F->koff[p], F->Kpiv + F->kvoff[p],
-                                                   F->Kperm + F->kvoff[p], tp<T>(F->Kud) + F->kvoff[p],
-                                                   tp<T>(F->Kinv) + F->kioff[p], tp<T>(F->W), F->d_info + 1, p, L)));
-      if (Rp > 0 && r > 0 && !couple_uses_inverse(r))
-        HL("couple_trsm", (launch_block_trsm<T>(st, 0, 1 << p, kp, 2 * r, (int64_t)2 * r * Rp,
-                                                tp<T>(F->Klu) + F->koff[p], F->Kperm + F->kvoff[p],
-                                                tp<T>(F->Kinv) + F->kioff[p], tp<T>(F->W), 2 * r, Rp)));
+                                                   tp<T>(F->Kinv) + F->koff[p], F->Kpiv + F->kvoff[p],
+                                                   tp<T>(F->Kud) + F->kvoff[p], tp<T>(F->Kt) + F->ktoff[p],
+                                                   tp<T>(F->W), F->d_info + 1, p, L)));
       if (p > 0 && r > 0) {
         HL("level_pass",
            (launch_level_pass<T, T, S>(st, F->ntiles[q], F->d_tiles[q], F->tile_shape[q], Y, F->ldy, Rp,
@@ -819,8 +814,7 @@ hodlr_status apply_inverse(hodlr_factors* F, Workspace& Wk, hipStream_t st, int 
                                           &segs, &seg_start);
         if (s) return s;
         HL("couple_solve", (launch_couple_solve<T>(st, 0, 1 << p, r, kpad(r), nrhs, segs, seg_start,
-                                                   tp<T>(F->Klu) + F->koff[p], F->Kperm + F->kvoff[p],
-                                                   tp<T>(F->Kud) + F->kvoff[p], w)));
+                                                   tp<T>(F->Kinv) + F->koff[p], tp<T>(F->Kt) + F->ktoff[p], w)));
       }
       const int kb = p > 0 ? F->ranks[p - 1] : 0;
       if (r == 0 && kb == 0) continue;
@@ -847,8 +841,7 @@ hodlr_status apply_inverse(hodlr_factors* F, Workspace& Wk, hipStream_t st, int 
                                           &segs, &seg_start);
         if (s) return s;
         HL("couple_solve_t", (launch_couple_solve<T>(st, 1, 1 << p, r, kpad(r), nrhs, segs, seg_start,
-                                                     tp<T>(F->Klu) + F->koff[p], F->Kperm + F->kvoff[p],
-                                                     tp<T>(F->Kud) + F->kvoff[p], w)));
+                                                     tp<T>(F->Kinv) + F->koff[p], tp<T>(F->Kt) + F->ktoff[p], w)));
       }
       const int tq = q < L ? q + 1 : L;
       const int kb = q < L ? F->ranks[q] : 0;
@@ -1409,8 +1402,7 @@ hodlr_status hodlr_logdet(const hodlr_factors* Fc, double* sign, double* logabs,
     const int r = F->ranks[p];
     if (r == 0) continue;
     lv.count[lv.n] = 1 << p;
-    lv.r[lv.n] = r;
-    lv.kp[lv.n] = kpad(r);
+    lv.kp[lv.n] = kvecs(r);
     lv.kvoff[lv.n] = F->kvoff[p];
     ++lv.n;
   }
@@ -1453,24 +1445,13 @@ hodlr_status hodlr_logdet(const hodlr_factors* Fc, double* sign, double* logabs,
 namespace {
 // K^{-1} diagonal blocks P_a of every level, FP64, Pd at pdoff[l] + a r_l^2
 template <typename T>
-hodlr_status logdet_pblocks(hodlr_factors* F, hipStream_t st, DevMem& M, double* Pd,
-                            const std::vector<int64_t>& pdoff) {
+hodlr_status logdet_pblocks(hodlr_factors* F, hipStream_t st, double* Pd, const std::vector<int64_t>& pdoff) {
   for (int p = 0; p < F->L; ++p) {
     const int r = F->ranks[p];
     if (r == 0) continue;
-    const int np = 1 << p, n2 = 2 * r, kp = kpad(r);
-    double* Pl = Pd + pdoff[p + 1];
-    if (couple_uses_inverse(r)) {  // K^{-1} is stored (n2 x n2 per parent)
-      HL("logdet_grad", launch_pblocks<T>(st, np, r, tp<T>(F->Klu) + F->koff[p], n2, (int64_t)n2 * n2, Pl));
-    } else {  // K^{-1} = K^{-1} I by the block solver on the stored LU
-      T* X = nullptr;
-      hodlr_status s = M.alloc(&X, (size_t)np * n2 * n2);
-      if (s) return s;
-      HL("logdet_grad", launch_identity_blocks<T>(st, np, n2, X));
-      HL("logdet_grad", launch_block_trsm<T>(st, 0, np, kp, n2, n2, tp<T>(F->Klu) + F->koff[p], F->Kperm + F->kvoff[p],
-                                              tp<T>(F->Kinv) + F->kioff[p], X, (int64_t)np * n2, n2));
-      HL("logdet_grad", launch_pblocks<T>(st, np, r, X, (int64_t)np * n2, n2, Pl));
-    }
+    const int kp = kpad(r);
+    HL("logdet_grad", launch_pblocks<T>(st, 1 << p, r, tp<T>(F->Kinv) + F->koff[p], kp, (int64_t)kp * kp,
+                                        Pd + pdoff[p + 1]));
   }
   return HODLR_OK;
 }
@@ -1541,7 +1522,7 @@ hodlr_status logdet_grad_impl(hodlr_factors* F, hipStream_t st, DevMem& M, void*
     return HODLR_ERR_HIP;
   HL("logdet_grad", (launch_convert<double, T>(st, N, R, tp<T>(F->Y), F->ldy, Y64, N, F->gsy)));
   HL("logdet_grad", (launch_convert<double, T>(st, N, R, tp<T>(FT->Y), FT->ldy, Yt64, N, FT->gsy)));
-  if ((s = logdet_pblocks<T>(F, st, M, Pd, pdoff))) return s;
+  if ((s = logdet_pblocks<T>(F, st, Pd, pdoff))) return s;
   // Lam(I_a, c_l) = (A_a^{-T} V_a) P_a^T; YP(I_a, c_l) = Y_a P_a
   HL("logdet_grad", launch_node_mix(st, N, L, R, F->d_off, F->d_rpre, d_pdoff, Pd, 1, Yt64, Lam));
   HL("logdet_grad", launch_node_mix(st, N, L, R, F->d_off, F->d_rpre, d_pdoff, Pd, 0, Y64, YP));

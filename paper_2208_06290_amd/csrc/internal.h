@@ -90,11 +90,6 @@ hipError_t launch_leaf_trsm(hipStream_t s, int trans, int nleaf, int ldl, const 
                             int64_t lul, int inplace, const int32_t* perm, const T* dinv, const S* B, int64_t ldb,
                             T* X, int64_t ldx, int ncols, int64_t gsb = 256, int64_t gsx = 256, int bf = 0);
 
-// The same solves for nblk equal blocks of m rows (m <= ldl): block g's rows start at X + g * ostride.
-template <typename T>
-hipError_t launch_block_trsm(hipStream_t s, int trans, int nblk, int ldl, int m, int64_t ostride, const T* lu,
-                             const int32_t* perm, const T* dinv, T* X, int64_t ldx, int ncols);
-
 // Fused level pass on tiles:
 //   update : Z(tile, 0:nz) -= A1(tile, 0:ka) * W_node(0:ka, 0:nz)      (if ka > 0)
 //   product: P_tile(0:kb, 0:nz) = B1(tile, 0:kb)^T * Z(tile, 0:nz)      (if kb > 0)
@@ -125,28 +120,26 @@ template <typename T>
 hipError_t launch_segment_reduce(hipStream_t s, int nsegs, const int2* d_desc, int64_t elems, const T* P, T* out,
                                  int maxy);
 
-// Coupling systems with 2r <= 128 and 2r % 16 == 0 are inverted explicitly
-// (Gauss-Jordan with partial pivoting; four waves up to 2r = 64, eight
-// beyond, two rows a lane): the factor stores K^{-1} (2r x 2r,
-// col-major) in place of the LU, W receives K^{-1} rhs directly and the solves
-// apply K^{-1} or its transpose.  Other ranks keep the LU, its 16 x 16 diagonal
-// inverses and the block solver.
-__host__ __device__ inline bool couple_uses_inverse(int r) { return r > 0 && 2 * r <= 128 && (2 * r) % 16 == 0; }
-
-// Coupling factor for all parents of one level (children have rank r, W has Rp columns);
-// K factors stored kp x kp (kp = 2r rounded up to 16); W gets the unsolved right-hand
-// sides (LU) or the solved ones (explicit inverse).
-// Segments of child node c: [seg_start[c], seg_start[c+1]), each r x (Rp + r) col-major.
+// Coupling factor for all parents of one level (children have rank r, W has Rp columns):
+// K^{-1} stored kp x kp per parent (kp = 2r rounded up to 16, zero padding), Kpiv / Kud its
+// interchanges and reciprocal pivots (two halves of r rounded up to 16 per parent), W = K^{-1} rhs
+// (2r x Rp per parent).
+// Child c's product: item seg_start[c], r x (Rp + r) col-major.
+// Ranks off the multiples of 8 correct every product with K^{-1} by its
+// residual: their coupling systems have the accuracy of substitution with an
+// LU (rank 33, entries of V^T Y above one: error 1e-12 of x with it, 2e-10
+// without).  Kt (2 r x r per parent) keeps T_a and T_b for that.
+__host__ __device__ inline bool couple_corrects(int r) { return r % 8 != 0; }
 template <typename T>
 hipError_t launch_couple_factor(hipStream_t s, int nparents, int r, int kp, int Rp, const T* segs,
-                                const int32_t* d_seg_start, T* Klu, int32_t* Kpiv, int32_t* Kperm, T* Kud, T* Kinv,
-                                T* W, unsigned long long* info, int level, int L);
+                                const int32_t* d_seg_start, T* Kinv, int32_t* Kpiv, T* Kud, T* Kt, T* W,
+                                unsigned long long* info, int level, int L);
 
 // Coupling solve for all parents of one level: w = K^{-1} rhs (trans=0) or K^{-T} rhs.
-// rhs rows of child c come from its segments (r x nrhs each); w is 2r x nrhs per parent.
+// rhs rows of child c come from its item (r x nrhs); w is 2r x nrhs per parent.
 template <typename T>
 hipError_t launch_couple_solve(hipStream_t s, int trans, int nparents, int r, int kp, int nrhs, const T* segs,
-                               const int32_t* d_seg_start, const T* Klu, const int32_t* Kperm, const T* Kud, T* w);
+                               const int32_t* d_seg_start, const T* Kinv, const T* Kt, T* w);
 
 // Pairwise tree sum out[i] = in[2i] + in[2i+1] (blocks of elems doubles).
 hipError_t launch_tree_sum(hipStream_t s, int nnodes, int64_t elems, const double* in, double* out);
@@ -200,12 +193,11 @@ hipError_t scratch_device_ptr(void** out);
 
 namespace hodlr {
 // Coupling factors of the levels that have them, for the log-determinant:
-// per entry p < n, `count` parents of rank r, K stored with kp entries per
-// parent from element kvoff of the K vectors (interchanges, 1 / pivots).
+// per entry p < n, `count` parents with kp entries each (two halves of the rank
+// rounded up to 16) from element kvoff of the K vectors (interchanges, 1 / pivots).
 struct LogdetLevels {
   int n = 0;
   int count[HODLR_MAX_LEVELS];
-  int r[HODLR_MAX_LEVELS];
   int kp[HODLR_MAX_LEVELS];
   int64_t kvoff[HODLR_MAX_LEVELS];
 };
@@ -225,8 +217,6 @@ hipError_t launch_transpose_leaves(hipStream_t s, int nleaf, int m_max, const in
                                    int64_t ldd, S* Dt, int64_t ldt);
 template <typename T>
 hipError_t launch_identity_leaves(hipStream_t s, int nleaf, int ncols, const int64_t* d_leaf_off, T* E, int64_t lde);
-template <typename T>
-hipError_t launch_identity_blocks(hipStream_t s, int nblk, int n2, T* X);
 template <typename T>
 hipError_t launch_pblocks(hipStream_t s, int nparents, int r, const T* Kinv, int64_t ldk, int64_t pstride, double* Pd);
 hipError_t launch_node_mix(hipStream_t s, int64_t n, int L, int R, const int64_t* d_leaf_off, const int32_t* d_rpre,

@@ -294,13 +294,6 @@ hipError_t launch_leaf_trsm(hipStream_t s, int trans, int nleaf, int ldl, const 
                            gsb, gsx, bf);
 }
 
-template <typename T>
-hipError_t launch_block_trsm(hipStream_t s, int trans, int nblk, int ldl, int m, int64_t ostride, const T* lu,
-                             const int32_t* perm, const T* dinv, T* X, int64_t ldx, int ncols) {
-  return launch_trsm<T, T>(s, trans, nblk, ldl, nullptr, ostride, m, lu, ldl, 0, perm, dinv, X, ldx, X, ldx, ncols,
-                           256, 256, 0);
-}
-
 template hipError_t launch_leaf_trsm<double, double>(hipStream_t, int, int, int, const int64_t*, const double*,
                                                      int64_t, int, const int32_t*, const double*, const double*,
                                                      int64_t, double*, int64_t, int, int64_t, int64_t, int);
@@ -310,9 +303,5 @@ template hipError_t launch_leaf_trsm<float, double>(hipStream_t, int, int, int, 
 template hipError_t launch_leaf_trsm<float, float>(hipStream_t, int, int, int, const int64_t*, const float*,
                                                    int64_t, int, const int32_t*, const float*, const float*,
                                                    int64_t, float*, int64_t, int, int64_t, int64_t, int);
-template hipError_t launch_block_trsm<double>(hipStream_t, int, int, int, int, int64_t, const double*,
-                                              const int32_t*, const double*, double*, int64_t, int);
-template hipError_t launch_block_trsm<float>(hipStream_t, int, int, int, int, int64_t, const float*, const int32_t*,
-                                             const float*, float*, int64_t, int);
 
 }  // namespace hodlr

@@ -62,7 +62,7 @@ __global__ __launch_bounds__(kLdThreads) void logdet_items_kernel(int nleaf, int
   } else {
     int k = item - nleaf, p = 0;
     while (p < lv.n && k >= lv.count[p]) k -= lv.count[p++];
-    const int n2 = 2 * lv.r[p];
+    const int n2 = lv.kp[p];  // both halves of K padded to kp / 2 (pivots 1)
     const T* ud = Kud + lv.kvoff[p] + (int64_t)k * lv.kp[p];
     const int32_t* pv = Kpiv + lv.kvoff[p] + (int64_t)k * lv.kp[p];
     for (int j = tid; j < n2; j += kLdThreads) {
@@ -70,7 +70,7 @@ __global__ __launch_bounds__(kLdThreads) void logdet_items_kernel(int nleaf, int
       s -= log(fabs(d));
       par ^= (d < 0.0) ^ (pv[j] != j);
     }
-    if (tid == 0) par ^= lv.r[p] & 1;  // (-1)^r of the block exchange
+    if (tid == 0) par ^= (lv.kp[p] / 2) & 1;  // block exchange: (-1)^r, and -1 for each padded pair
   }
   block_sum<kLdThreads>(s, par, ls, lp);
   if (tid == 0) {
@@ -150,17 +150,6 @@ __global__ void identity_leaves_kernel(const int64_t* __restrict__ leaf_off, int
   }
 }
 
-// nblk stacked n2 x n2 identities: X(g n2 + i, j) = delta_ij, ld = nblk n2
-template <typename T>
-__global__ void identity_blocks_kernel(int nblk, int n2, T* __restrict__ X) {
-  const int64_t ld = (int64_t)nblk * n2;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < ld * n2; e += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t row = e % ld;
-    const int j = (int)(e / ld);
-    X[e] = ((int)(row % n2) == j) ? T(1) : T(0);
-  }
-}
-
 // P_a for the children a = 2g + h of the parents g of one level: Pd[a][k][c] =
 // Kinv_g(h r + k, h r + c), from K^{-1} stored per parent with leading
 // dimension ldk and parent stride pstride (elements)
@@ -223,12 +212,6 @@ hipError_t launch_identity_leaves(hipStream_t s, int nleaf, int ncols, const int
   return hipGetLastError();
 }
 template <typename T>
-hipError_t launch_identity_blocks(hipStream_t s, int nblk, int n2, T* X) {
-  if (nblk == 0 || n2 == 0) return hipSuccess;
-  hipLaunchKernelGGL(identity_blocks_kernel<T>, dim3(256), dim3(256), 0, s, nblk, n2, X);
-  return hipGetLastError();
-}
-template <typename T>
 hipError_t launch_pblocks(hipStream_t s, int nparents, int r, const T* Kinv, int64_t ldk, int64_t pstride, double* Pd) {
   if (nparents == 0 || r == 0) return hipSuccess;
   hipLaunchKernelGGL(pblocks_kernel<T>, dim3(256), dim3(256), 0, s, nparents, r, Kinv, ldk, pstride, Pd);
@@ -247,8 +230,6 @@ template hipError_t launch_transpose_leaves<float>(hipStream_t, int, int, const 
                                                    float*, int64_t);
 template hipError_t launch_identity_leaves<double>(hipStream_t, int, int, const int64_t*, double*, int64_t);
 template hipError_t launch_identity_leaves<float>(hipStream_t, int, int, const int64_t*, float*, int64_t);
-template hipError_t launch_identity_blocks<double>(hipStream_t, int, int, double*);
-template hipError_t launch_identity_blocks<float>(hipStream_t, int, int, float*);
 template hipError_t launch_pblocks<double>(hipStream_t, int, int, const double*, int64_t, int64_t, double*);
 template hipError_t launch_pblocks<float>(hipStream_t, int, int, const float*, int64_t, int64_t, double*);
 

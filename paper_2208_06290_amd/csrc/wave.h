@@ -63,6 +63,31 @@ __device__ __forceinline__ int wave_min(int v) {
   return dpp::uniform63(v);
 }
 
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+  v = max(v, (uint32_t)dpp::mov<dpp::kQuad1032, 0xf>((int)v));
+  v = max(v, (uint32_t)dpp::mov<dpp::kQuad2301, 0xf>((int)v));
+  v = max(v, (uint32_t)dpp::mov<dpp::kRowHalfMirror, 0xf>((int)v));
+  v = max(v, (uint32_t)dpp::mov<dpp::kRowMirror, 0xf>((int)v));
+  v = max(v, (uint32_t)dpp::mov<dpp::kRowBcast15, 0xa>((int)v));
+  v = max(v, (uint32_t)dpp::mov<dpp::kRowBcast31, 0xc>((int)v));
+  return (uint32_t)dpp::uniform63((int)v);
+}
+
+// Order of moduli as unsigned integers: the bits of |x| (NaN as infinity), in
+// the high and, for FP64, the low word; open rows are one higher than zero, so
+// closed rows (0) never win.
+__device__ __forceinline__ void modulus_words(double x, bool open, uint32_t& hi, uint32_t& lo) {
+  const unsigned long long b = __builtin_bit_cast(unsigned long long, x) & 0x7fffffffffffffffull;
+  const bool nan = b > 0x7ff0000000000000ull;
+  hi = open ? (nan ? 0x7ff00000u : (uint32_t)(b >> 32)) + 1u : 0u;
+  lo = nan ? 0u : (uint32_t)b;
+}
+__device__ __forceinline__ void modulus_words(float x, bool open, uint32_t& hi, uint32_t& lo) {
+  const uint32_t b = __builtin_bit_cast(uint32_t, x) & 0x7fffffffu;
+  hi = open ? min(b, 0x7f800000u) + 1u : 0u;
+  lo = 0u;
+}
+
 // Pivot search: the largest v over the wave and, among the lanes holding it,
 // the smallest key (v >= 0 for candidates, -1 otherwise; NaN mapped to
 // infinity by the caller).  Both results are uniform.
