@@ -283,7 +283,8 @@ struct ProdPlan {
   int maxcount = 0;
   std::vector<ProdStage> stages;  // empty: the coupling kernels read tile partials directly
   size_t buf_items[2] = {0, 0};   // ping-pong regions of the segment buffer, in items
-  int32_t* d_seg_start = nullptr;
+  int32_t* d_tile_start = nullptr;  // first tile of each node
+  int32_t* d_seg_start = nullptr;   // first item after the last stage
 };
 
 // Solve-side workspace of one stream: tile partials, segment sums, W, the
@@ -297,6 +298,7 @@ struct Workspace {
   DevMem mem;
   int nrhs = -1;
   void* sP = nullptr;
+  void* sP2 = nullptr;  // second tile-partial buffer of narrow solves (null: their passes read W)
   void* sseg = nullptr;
   void* sw = nullptr;
   void* sx = nullptr;      // compute-type copy of the right-hand sides
@@ -452,6 +454,10 @@ void make_prod(hodlr_factors* F, int q, int p) {
   std::vector<int> start(pp.nnodes + 1);
   for (int i = 0; i <= pp.nnodes; ++i) start[i] = ts[i * stride];
   for (int i = 0; i < pp.nnodes; ++i) pp.maxcount = std::max(pp.maxcount, start[i + 1] - start[i]);
+  {
+    const std::vector<int32_t> st32(start.begin(), start.end());
+    F->up.add(&pp.d_tile_start, st32.data(), st32.size());
+  }
   int stage = 0;
   std::vector<std::vector<int2>> descs;
   while (true) {
@@ -727,6 +733,18 @@ Workspace* get_ws(hodlr_factors* F, hipStream_t st) {
   return p;
 }
 
+// Most columns of a solve whose passes form W themselves; most item columns a
+// workgroup sums for that (a node's tiles times right-hand sides, read by every
+// workgroup of the level): beyond, the reduction comes first.  Most tiles of
+// such a pass: every workgroup reads K^{-1} of its parent, a quarter of its own
+// bytes, which costs what the launches saved once the chip is full (FP64, rank
+// 32, one column, with and without: N = 16384 98 and 118 us, 65536 154 and 186,
+// 262144 503 and 551, 524288 953 and 980, 1048576 the same or slower; FP32
+// adjoint, 524288: 906 and 893).
+constexpr int kNarrow = 16;
+constexpr int kCplLoads = 32;
+constexpr int kCplTiles = 1024;
+
 // Sizes of the solve-side buffers for nrhs columns (elements).
 struct WsSizes {
   size_t pmax = 0, segmax = 0, wmax = 0, n = 0, treeN = 0, nrm = 0, ld = 0;
@@ -774,6 +792,7 @@ hodlr_status ensure_ws(hodlr_factors* F, Workspace& W, int nrhs) {
   DevMem& M = W.mem;
   auto reserve = [&](void** p, size_t bytes) { M.reserve(reinterpret_cast<unsigned char**>(p), bytes); };
   reserve(&W.sP, z.pmax * ts);
+  reserve(&W.sP2, z.pmax / nrhs * std::min(nrhs, kNarrow) * ts);
   reserve(&W.sseg, z.segmax * ts);
   reserve(&W.sw, z.wmax * ts);
   reserve(&W.sx, z.n * ts);
@@ -788,6 +807,49 @@ hodlr_status ensure_ws(hodlr_factors* F, Workspace& W, int nrhs) {
   return HODLR_OK;
 }
 
+// One level of a solve after its products: the coupling solves of parent level
+// p (children of level q = p + 1, rank r) on the products P over tile level pq,
+// then Z -= A1 w and the next products (B1, kb columns) on tile level tq.
+// Narrow solves form w in the pass, which writes its products to Pn; others
+// keep to P.  Returns the buffer of the new products in *Pout.
+template <typename T, typename SA, typename SB>
+hodlr_status solve_level(hodlr_factors* F, Workspace& Wk, hipStream_t st, int trans, int p, int pq, int tq, int nrhs,
+                         T* X, int64_t ldx, const SA* A1, int64_t lda, const SB* B1, int64_t ldb, int kb,
+                         GroupStrides gs, T* P, T* Pn, T** Pout) {
+  const int q = p + 1, r = F->ranks[p];
+  const char* pass = trans ? "adjoint_pass" : "solve_pass";
+  T* w = tp<T>(Wk.sw);
+  *Pout = P;
+  // products with K^{-1} that are not corrected by their residual
+  if (r > 0 && nrhs <= kNarrow && F->ntiles[tq] <= kCplTiles && Pn && !couple_corrects(r)) {
+    const ProdPlan& pp = F->prods.at({pq, q});
+    const T* items = P;
+    const int32_t* start = pp.d_tile_start;
+    if ((int64_t)pp.maxcount * nrhs > kCplLoads || pp.maxcount > kSegTiles) {
+      hodlr_status s = prod_segments<T>(F, st, pq, q, (int64_t)r * nrhs, P, tp<T>(Wk.sseg), &items, &start);
+      if (s) return s;
+    }
+    HL(pass, (launch_coupled_pass<T, SA, SB>(st, trans, F->ntiles[tq], F->d_tiles[tq], F->tile_shape[tq], X, ldx, nrhs,
+                                             A1, lda, r, tp<T>(F->Kinv) + F->koff[p], kpad(r), items, start, tq - q, B1,
+                                             ldb, kb, Pn, gs)));
+    *Pout = Pn;
+    return HODLR_OK;
+  }
+  if (r > 0) {
+    const T* segs;
+    const int32_t* seg_start;
+    hodlr_status s = prod_segments<T>(F, st, pq, q, (int64_t)r * nrhs, P, tp<T>(Wk.sseg), &segs, &seg_start);
+    if (s) return s;
+    HL(trans ? "couple_solve_t" : "couple_solve",
+       (launch_couple_solve<T>(st, trans, 1 << p, r, kpad(r), nrhs, segs, seg_start, tp<T>(F->Kinv) + F->koff[p],
+                               tp<T>(F->Kt) + F->ktoff[p], w)));
+  }
+  if (r == 0 && kb == 0) return HODLR_OK;
+  HL(pass, (launch_level_pass<T, SA, SB>(st, F->ntiles[tq], F->d_tiles[tq], F->tile_shape[tq], X, ldx, nrhs, A1, lda, r,
+                                         w, 2 * r, (int64_t)2 * r * nrhs, tq - q, B1, ldb, kb, P, gs)));
+  return HODLR_OK;
+}
+
 // x <- A^{-1} x (trans = 0) or A^{-T} x (trans = 1) in the compute precision, x: N x nrhs, ld N
 template <typename T, typename S>
 hodlr_status apply_inverse(hodlr_factors* F, Workspace& Wk, hipStream_t st, int trans, int nrhs, T* X, int64_t ldx) {
@@ -796,7 +858,10 @@ hodlr_status apply_inverse(hodlr_factors* F, Workspace& Wk, hipStream_t st, int 
   const T* Y = tp<T>(F->Y);
   const S* V = static_cast<const S*>(F->V);
   T* P = tp<T>(Wk.sP);
-  T* w = tp<T>(Wk.sw);
+  T* Pn = tp<T>(Wk.sP2);
+  auto turn = [&](T* out) {  // the buffer with the new products first
+    if (out != P) std::swap(P, Pn);
+  };
   if (!trans) {
     HL("leaf_solve", (launch_leaf_trsm<T, T>(st, 0, F->nleaf, F->ldl, F->d_off, tp<T>(F->lu), F->lul, F->inplace,
                                              F->perm, tp<T>(F->invl), X, ldx, X, ldx, nrhs)));
@@ -806,23 +871,13 @@ hodlr_status apply_inverse(hodlr_factors* F, Workspace& Wk, hipStream_t st, int 
                                                  F->ldv, F->ranks[L - 1], P)));
     for (int p = L - 1; p >= 0; --p) {
       const int q = p + 1;
-      const int r = F->ranks[q - 1];
-      if (r > 0) {
-        const T* segs;
-        const int32_t* seg_start;
-        hodlr_status s = prod_segments<T>(F, st, fwd_prod_tiles(F, q), q, (int64_t)r * nrhs, P, tp<T>(Wk.sseg),
-                                          &segs, &seg_start);
-        if (s) return s;
-        HL("couple_solve", (launch_couple_solve<T>(st, 0, 1 << p, r, kpad(r), nrhs, segs, seg_start,
-                                                   tp<T>(F->Kinv) + F->koff[p], tp<T>(F->Kt) + F->ktoff[p], w)));
-      }
-      const int kb = p > 0 ? F->ranks[p - 1] : 0;
-      if (r == 0 && kb == 0) continue;
-      HL("solve_pass", (launch_level_pass<T, T, S>(st, F->ntiles[q], F->d_tiles[q], F->tile_shape[q], X, ldx, nrhs,
-                                                   Y + (int64_t)F->Rp[p] * F->ldy, F->ldy, r, w, 2 * r,
-                                                   (int64_t)2 * r * nrhs, 0,
-                                                   p > 0 ? V + (int64_t)F->Rp[p - 1] * F->ldv : nullptr, F->ldv, kb,
-                                                   P, GroupStrides{256, F->gsy, 256})));
+      T* out;
+      hodlr_status s = solve_level<T, T, S>(F, Wk, st, 0, p, fwd_prod_tiles(F, q), q, nrhs, X, ldx,
+                                            Y + (int64_t)F->Rp[p] * F->ldy, F->ldy,
+                                            p > 0 ? V + (int64_t)F->Rp[p - 1] * F->ldv : nullptr, F->ldv,
+                                            p > 0 ? F->ranks[p - 1] : 0, GroupStrides{256, F->gsy, 256}, P, Pn, &out);
+      if (s) return s;
+      turn(out);
     }
     return HODLR_OK;
   }
@@ -833,24 +888,13 @@ hodlr_status apply_inverse(hodlr_factors* F, Workspace& Wk, hipStream_t st, int 
                                                    GroupStrides{256, 256, F->gsy})));
     for (int p = 0; p < L; ++p) {
       const int q = p + 1;
-      const int r = F->ranks[q - 1];
-      if (r > 0) {
-        const T* segs;
-        const int32_t* seg_start;
-        hodlr_status s = prod_segments<T>(F, st, adj_prod_tiles(F, q), q, (int64_t)r * nrhs, P, tp<T>(Wk.sseg),
-                                          &segs, &seg_start);
-        if (s) return s;
-        HL("couple_solve_t", (launch_couple_solve<T>(st, 1, 1 << p, r, kpad(r), nrhs, segs, seg_start,
-                                                     tp<T>(F->Kinv) + F->koff[p], tp<T>(F->Kt) + F->ktoff[p], w)));
-      }
-      const int tq = q < L ? q + 1 : L;
-      const int kb = q < L ? F->ranks[q] : 0;
-      if (r == 0 && kb == 0) continue;
-      HL("adjoint_pass", (launch_level_pass<T, S, T>(st, F->ntiles[tq], F->d_tiles[tq], F->tile_shape[tq], X, ldx, nrhs,
-                                                     V + (int64_t)F->Rp[p] * F->ldv, F->ldv, r, w, 2 * r,
-                                                     (int64_t)2 * r * nrhs, tq - q,
-                                                     q < L ? Y + (int64_t)F->Rp[q] * F->ldy : nullptr, F->ldy, kb, P,
-                                                     GroupStrides{256, 256, F->gsy})));
+      T* out;
+      hodlr_status s = solve_level<T, S, T>(F, Wk, st, 1, p, adj_prod_tiles(F, q), q < L ? q + 1 : L, nrhs, X, ldx,
+                                            V + (int64_t)F->Rp[p] * F->ldv, F->ldv,
+                                            q < L ? Y + (int64_t)F->Rp[q] * F->ldy : nullptr, F->ldy,
+                                            q < L ? F->ranks[q] : 0, GroupStrides{256, 256, F->gsy}, P, Pn, &out);
+      if (s) return s;
+      turn(out);
     }
   }
   HL("leaf_solve_t", (launch_leaf_trsm<T, T>(st, 1, F->nleaf, F->ldl, F->d_off, tp<T>(F->lu), F->lul, F->inplace,
@@ -1252,6 +1296,8 @@ hodlr_status hodlr_solve_noalloc(const hodlr_factors* Fc, int32_t trans, int64_t
   W.sseg = take(z.segmax * ts);
   W.sw = take(z.wmax * ts);
   W.sx = ts == 8 ? nullptr : take(z.n * ts);
+  // what is left may hold the second tile-partial buffer of a narrow solve
+  if (nrhs <= kNarrow && need + z.pmax * ts + 256 <= scratch_capacity()) W.sP2 = take(z.pmax * ts);
   hipStream_t st = static_cast<hipStream_t>(stream);
   std::lock_guard<std::mutex> g(F->na_mu);
   if (hipStreamWaitEvent(st, F->ready, 0) != hipSuccess) return HODLR_ERR_HIP;

@@ -114,6 +114,15 @@ hipError_t launch_level_pass(hipStream_t s, int ntiles, const Tile* tiles, TileS
                              int64_t w_pstride, int node_shift, const SB* B1, int64_t ldb, int kb, TZ* P,
                              GroupStrides gs = GroupStrides(), int bf = 0);
 
+// Narrow pass (nz <= 16) whose update takes W = K^{-1} rhs (trans: K^{-T} rhs) of the level's
+// coupling systems, formed in the pass: Kinv and kp as launch_couple_solve, child c's items
+// (r x nz each) d_start[c] .. d_start[c + 1] - 1, summed in order.  P must not overlap items.
+template <typename TZ, typename SA, typename SB>
+hipError_t launch_coupled_pass(hipStream_t s, int trans, int ntiles, const Tile* tiles, TileShape sh, TZ* Z,
+                               int64_t ldz, int nz, const SA* A1, int64_t lda, int r, const TZ* Kinv, int kp,
+                               const TZ* items, const int32_t* d_start, int node_shift, const SB* B1, int64_t ldb,
+                               int kb, TZ* P, GroupStrides gs = GroupStrides());
+
 // Segment sums of tile partials: out[s] = sum of tiles [desc[s].x, desc[s].x + desc[s].y),
 // maxy = max over s of desc[s].y (<= kSegTiles).
 template <typename T>

@@ -77,11 +77,31 @@ constexpr int lp_occupancy() {
 // the end, zeroes them in B1 and never stores them.  K is padded with zero rows of
 // W (A1 re-reads its last column).  Columns past nz and B1 columns past kb
 // re-read the last one; their results are not stored.
-template <typename TZ, typename SA, typename SB, int WC, int NCB, bool FULL, bool BF>
+//
+// CPL (one chunk of up to 16 columns): W is not read but formed here, from the
+// parent's K^{-1} (CPL = 2: its transpose) and the children's products: every
+// workgroup sums its parent's items (a node's tile partials, in order), and wave
+// w forms the 16-row block w of its own child's rows, in the layout and order
+// of couple_apply_kernel.  That repeats a few thousand multiply-adds per tile
+// and saves the launches that would form W and, up to kCplLoads item columns,
+// the reduction before them: a launch is 4 us, as long as a narrow pass over a
+// small system (N = 4096, one vector: 19 launches and 83 us without, 8 and
+// 51 us with).
+template <typename T>
+struct CoupleArgs {
+  const T* Kinv = nullptr;  // of the level's first parent, kp x kp each
+  int kp = 0;
+  const T* items = nullptr;  // r x nz each, child c's: start[c] .. start[c + 1]
+  const int32_t* start = nullptr;
+};
+
+template <typename TZ, typename SA, typename SB, int WC, int NCB, bool FULL, bool BF, int CPL = 0>
 __global__ __launch_bounds__(kLpThreads, (lp_occupancy<TZ, NCB, FULL>())) void level_pass_rows_kernel(
     const Tile* __restrict__ tiles, int zchunks, int c_base, int bchunks, int kbc, TZ* Z, int64_t ldz, int nz,
     const SA* A1, int64_t lda, int ka, const TZ* __restrict__ W, int64_t w_ld, int64_t w_pstride, int node_shift,
-    const SB* __restrict__ B1, int64_t ldb, int kb_total, TZ* __restrict__ P, GroupStrides gs, int red_off) {
+    const SB* __restrict__ B1, int64_t ldb, int kb_total, TZ* __restrict__ P, GroupStrides gs, int red_off,
+    CoupleArgs<TZ> cpl) {
+  static_assert(CPL == 0 || (WC == 1 && NCB == 1 && !BF), "the fused coupling solve is for one narrow chunk");
   using M = Mfma<TZ>;
   using V = typename M::V;
   constexpr int WR = 4 / WC;
@@ -110,7 +130,66 @@ __global__ __launch_bounds__(kLpThreads, (lp_occupancy<TZ, NCB, FULL>())) void l
 
   // W chunk to LDS, negated: element (k, c) of the chunk, k = 16 g + 4 q + s, in slot s of
   // lane 16 q + c % 16 of fragment (g, c / 16)
-  if (ka > 0) {
+  if constexpr (CPL > 0) {
+    const int nd = tl.node >> node_shift, half = nd & 1, nt = ng, r = ka;
+    const bool vec = r % 4 == 0;
+    // K^{-1} rows of this wave's block (half r + 16 w + row), all columns
+    const TZ* Kg = cpl.Kinv + (int64_t)(nd >> 1) * cpl.kp * cpl.kp;
+    const int row = half * r + min(16 * w + (sizeof(TZ) == 8 ? 4 * (li & 3) + (li >> 2) : li), r - 1);
+    TZ kv[8][4];
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      if (w < nt && q < 2 * nt) {
+        const int kh = q >= nt, i0 = 16 * (kh ? q - nt : q) + 4 * lq;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const int k = kh * r + min(i0 + t, r - 1);
+          kv[q][t] = CPL == 2 ? Kg[k + row * cpl.kp] : Kg[row + k * cpl.kp];
+        }
+      }
+    // the children's product sums as B fragments: group q, lane, 4 rows
+    TZ* Ts = reinterpret_cast<TZ*>(smem_raw) + (red_off / sizeof(TZ)) * 2;
+    for (int e = tid; e < 2 * nt * 64; e += kLpThreads) {
+      const int q = e >> 6, h = q >= nt, c = e & 15, i0 = 16 * (h ? q - nt : q) + 4 * ((e >> 4) & 3);
+      TZ sum[4] = {TZ(0), TZ(0), TZ(0), TZ(0)};
+      if (c < nz && i0 < r) {
+        const int child = (nd & ~1) + h, i1 = cpl.start[child + 1];
+        for (int it = cpl.start[child], first = it; it < i1; it += 4) {
+          TZ v[4][4];  // four items' loads in flight
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const TZ* col = cpl.items + ((int64_t)min(it + u, i1 - 1) * nz + c) * r;
+            if (vec) {
+              load_run(col + i0, v[u]);
+            } else {
+#pragma unroll
+              for (int t = 0; t < 4; ++t) v[u][t] = i0 + t < r ? col[min(i0 + t, r - 1)] : TZ(0);
+            }
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            if (it + u < i1) {
+#pragma unroll
+              for (int t = 0; t < 4; ++t) sum[t] = it + u == first ? v[u][t] : sum[t] + v[u][t];
+            }
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < 4; ++t) Ts[e * 4 + t] = sum[t];
+    }
+    __syncthreads();
+    if (w < nt) {
+      V acc = vzero<V>();
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+        if (q < 2 * nt) {
+#pragma unroll
+          for (int t = 0; t < 4; ++t) acc = M::mma(kv[q][t], Ts[(q * 64 + lane) * 4 + t], acc);
+        }
+#pragma unroll
+      for (int t = 0; t < 4; ++t) Ws[(w * 64 + lane) * 4 + t] = 16 * w + 4 * lq + t < r ? -acc[t] : TZ(0);
+    }
+  } else if (ka > 0) {
     const int nd = tl.node >> node_shift;
     const TZ* Wn = W + (int64_t)(nd >> 1) * w_pstride + (int64_t)(nd & 1) * ka;
     for (int e = tid; e < ng * 4 * kCw; e += kLpThreads) {
@@ -589,7 +668,7 @@ static hipError_t launch_rows_part(hipStream_t s, int ntiles, int zchunks, int c
   hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(wsz + red));
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(kLpThreads), wsz + red, s, tiles, zchunks, c_base, bchunks, kbc, Z,
-                     ldz, nz, A1, lda, ka, W, w_ld, w_pstride, node_shift, B1, ldb, kb, P, gs, (int)wsz);
+                     ldz, nz, A1, lda, ka, W, w_ld, w_pstride, node_shift, B1, ldb, kb, P, gs, (int)wsz, CoupleArgs<TZ>());
   return hipGetLastError();
 }
 
@@ -780,6 +859,36 @@ hipError_t launch_level_pass(hipStream_t s, int ntiles, const Tile* tiles, TileS
                                         node_shift, B1, ldb, kb, P, gs);
 }
 
+// A narrow pass that forms W itself (see CPL of the row kernel).
+template <typename TZ, typename SA, typename SB>
+hipError_t launch_coupled_pass(hipStream_t s, int trans, int ntiles, const Tile* tiles, TileShape sh, TZ* Z,
+                               int64_t ldz, int nz, const SA* A1, int64_t lda, int r, const TZ* Kinv, int kp,
+                               const TZ* items, const int32_t* d_start, int node_shift, const SB* B1, int64_t ldb,
+                               int kb, TZ* P, GroupStrides gs) {
+  if (ntiles == 0 || nz == 0) return hipSuccess;
+  if (r < 1 || r > 64 || kp < 2 * r || nz > 16 || sh.rows < 1 || sh.rows > kTileRows) return hipErrorInvalidValue;
+  constexpr int kCw = 16;
+  const int nt = (r + 15) / 16;
+  const size_t part = std::max(sizeof(TZ) * 4 * 16 * kCw, sizeof(TZ) * kCw * 16 * nt);  // W, or a reduction buffer
+  const size_t smem = 2 * part + sizeof(TZ) * 2 * nt * 256;
+  const CoupleArgs<TZ> cpl{Kinv, kp, items, d_start};
+#define HODLR_LC(FULL, TR)                                                                                           \
+  {                                                                                                                  \
+    auto k = level_pass_rows_kernel<TZ, SA, SB, 1, 1, FULL, false, TR>;                                              \
+    hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);        \
+    if (e != hipSuccess) return e;                                                                                   \
+    hipLaunchKernelGGL(k, dim3(ntiles), dim3(kLpThreads), smem, s, tiles, 1, 0, 1, std::max(kb, 1), Z, ldz, nz, A1,   \
+                       lda, r, (const TZ*)nullptr, 0, 0, node_shift, B1, ldb, kb, P, gs, (int)part, cpl);            \
+  }
+  if (sh.mult(64)) {
+    if (trans) HODLR_LC(true, 2) else HODLR_LC(true, 1)
+  } else {
+    if (trans) HODLR_LC(false, 2) else HODLR_LC(false, 1)
+  }
+#undef HODLR_LC
+  return hipGetLastError();
+}
+
 #define HODLR_LP_INST(TZ, SA, SB)                                                                                  \
   template hipError_t launch_level_pass<TZ, SA, SB>(hipStream_t, int, const Tile*, TileShape, TZ*, int64_t, int,     \
                                                     const SA*, int64_t, int, const TZ*, int64_t, int64_t, int,      \
@@ -790,5 +899,14 @@ HODLR_LP_INST(float, double, float)
 HODLR_LP_INST(float, float, float)
 HODLR_LP_INST(double, double, float)
 #undef HODLR_LP_INST
+#define HODLR_LC_INST(TZ, SA, SB)                                                                                    \
+  template hipError_t launch_coupled_pass<TZ, SA, SB>(hipStream_t, int, int, const Tile*, TileShape, TZ*, int64_t, int, \
+                                                      const SA*, int64_t, int, const TZ*, int, const TZ*,             \
+                                                      const int32_t*, int, const SB*, int64_t, int, TZ*, GroupStrides);
+HODLR_LC_INST(double, double, double)
+HODLR_LC_INST(float, float, double)
+HODLR_LC_INST(float, double, float)
+HODLR_LC_INST(float, float, float)
+#undef HODLR_LC_INST
 
 }  // namespace hodlr

@@ -60,3 +60,20 @@ def test_y_big(name, prec, unit):
     hodlr, H, A = _case(name)
     Y = hodlr.factor(A, prec).y_big().cpu().numpy().T
     assert _rel(Y, O.y_big(O.factor(H))) < 100 * unit
+
+
+@pytest.mark.parametrize("ranks", [[8, 16, 24, 8, 40, 8], [64, 32, 48, 64, 56, 16], [24, 0, 16, 0, 8, 8]])
+@pytest.mark.parametrize("nrhs", [1, 2, 3, 16])
+def test_narrow_levels_of_several_tiles(ranks, nrhs):
+    """Up to 16 columns each pass solves its coupling systems itself: nodes of 1
+    to 32 tiles (products summed in the pass or before it), whole and ragged."""
+    from paper_2208_06290_amd import hodlr
+    for leaves in ([256] * 64, [256] * 56 + [255, 17, 130, 200, 193, 256, 64, 100]):
+        off = np.concatenate([[0], np.cumsum(leaves)]).astype(np.int64)
+        inp = W.synthetic(int(off[-1]), 0, ranks, seed=nrhs, leaf_offsets=off)
+        H = O.from_inputs(inp)
+        B = np.random.default_rng(nrhs).standard_normal((H.N, nrhs))
+        b = torch.as_tensor(np.ascontiguousarray(B.T), device=DEV)
+        F = hodlr.factor(hodlr.HODLRMatrix.from_inputs(inp.to(DEV)), "fp64")
+        assert _rel(F.solve(b).cpu().numpy().T, O.solve(O.factor(H), B)) < 1e-12
+        assert _rel(F.solve_adjoint(b).cpu().numpy().T, O.solve_adjoint(H, B)) < 1e-12
