@@ -12,15 +12,20 @@
 //   3. the panel (rows below, 32 columns) is factored with one thread per row,
 //      the row held in registers: pivot = largest magnitude, lowest current
 //      position on ties (LAPACK idamax), rows are not moved - each thread
-//      tracks its position; each wave publishes its best candidate's row in
-//      LDS and every thread selects the winner, one barrier per column.
+//      tracks its position; each wave with rows publishes its best candidate's
+//      row in LDS and every thread selects the winner, one barrier per column.
+//      The wave's search compares moduli as words (DPP maxima of the high words,
+//      low words and positions only on ties).
 // Entries are stored by original row while factoring (later interchanges move
 // no data); a final pass writes them in pivoted order.  Four workgroups per CU
-// in FP64, five with 4-byte elements (the panel steps are latency-bound): at
-// most 128 registers per lane and 40 KB of LDS, so the panel rows reach the
-// registers 8 columns at a time
-// and the diagonal-block inverses are formed with rolled loops, their
-// columns in LDS.
+// in FP64, five with 4-byte elements: at most 128 registers per lane and 40 KB
+// of LDS, so the panel rows reach the registers 8 columns at a time.
+//
+// Bound by instruction issue and latency of the panels (46 % of the time; the
+// sweeps 19 %, the loads 16 % at the rate of memory, the moves to rows 11 %, the
+// diagonal inverses 4 %).  4096 leaves of 256: FP64 3.00 ms, FP32 from FP64
+// 2.11, bfloat16 updates (2048 leaves) 0.97; with all waves in every panel, the search on
+// values and the inverses on half a wave in LDS 3.95, 2.79 and 1.35 ms.
 //
 // Output per leaf a (block of ldl x ldl, column-major, ld = ldl; ldl = m_max
 // rounded up to 16; or, in place, the leaf's own rows of D with ld = ldd,
@@ -195,52 +200,74 @@ __global__ __launch_bounds__(kLuThreads, sizeof(T) == 4 ? 5 : 4) void leaf_lu_ke
       for (int cc = 0; cc < 8; ++cc) r[8 * h + cc] = own ? stage[tid * 8 + cc] : T(0);
       __syncthreads();
     }
+    // waves without rows of this panel only keep the barriers
+    const int nact = (pr + 63) >> 6;
+    if (w >= nact) {
+      for (int j = 0; j < cw; ++j) __syncthreads();
+    } else {
 #pragma unroll
-    for (int j = 0; j < CW; ++j) {
-      if (j < cw) {
-        // one barrier per column: each wave publishes its best candidate (value,
-        // position, whole row); every thread then picks the winner of the four
-        const int sb = j & 1;
-        const bool cand = own && !done;
-        T v = cand ? fabs(r[j]) : T(-1);
-        if (cand && !(v == v)) v = T(INFINITY);  // a NaN can still be chosen
-        T vmax;
-        int key;
-        wave_argmax(v, cand ? mypos : 0x7fffffff, vmax, key);
-        v = vmax;
-        if (cand && mypos == key) {
-#pragma unroll
-          for (int cc = 0; cc < CW; ++cc) crow_[sb][w][cc] = r[cc];
-        }
-        if (lane == 0) {
-          cval[sb][w] = v;
-          ckey[sb][w] = key;
-        }
-        __syncthreads();
-        T bv = cval[sb][0];
-        int bk = ckey[sb][0], bw = 0;
-#pragma unroll
-        for (int x = 1; x < 4; ++x)
-          if (cval[sb][x] > bv || (cval[sb][x] == bv && ckey[sb][x] < bk)) {
-            bv = cval[sb][x];
-            bk = ckey[sb][x];
-            bw = x;
+      for (int j = 0; j < CW; ++j) {
+        if (j < cw) {
+          // one barrier per column: each wave publishes its best candidate (value,
+          // position, row from column j on); every thread then picks the winner
+          const int sb = j & 1;
+          const bool cand = own && !done;
+          uint32_t hi, lo;
+          modulus_words(r[j], cand, hi, lo);  // a NaN can still be chosen
+          const uint32_t mh = wave_max(hi);
+          bool best = hi == mh;
+          if constexpr (sizeof(T) == 8) {
+            if (__builtin_popcountll(__ballot(best)) > 1) {
+              const uint32_t ml = wave_max(best ? lo : 0u);  // (lane moves: every lane takes part)
+              best = best && lo == ml;
+            }
           }
-        const T* prow = crow_[sb][bw];
-        if (cand) {
-          if (mypos == bk) {  // this row is the pivot of column j
-            done = true;
-            pv[c0 + j] = c0 + bk;
-            if (r[j] == T(0)) atomicMin(info, ((unsigned long long)a << 20) | (unsigned long long)(c0 + j));
-            mypos = j;
-          } else {
-            if (mypos == j) mypos = bk;  // the row displaced by the interchange
-            const T pivot = prow[j];
-            if (pivot != T(0)) {
-              const T l = r[j] * (T(1) / pivot);
-              r[j] = l;
+          if (__builtin_popcountll(__ballot(best)) > 1) {
+            const int first = wave_min(best && cand ? mypos : 0x7fffffff);
+            best = best && mypos == first;
+          }
+          if (mh == 0) {  // no candidates in this wave
+            if (lane == 0) {
+              cval[sb][w] = T(-1);
+              ckey[sb][w] = 0x7fffffff;
+            }
+          } else if (best) {
+            const T v = fabs(r[j]);
+            cval[sb][w] = v == v ? v : T(INFINITY);
+            ckey[sb][w] = mypos;
 #pragma unroll
-              for (int cc = j + 1; cc < CW; ++cc) r[cc] -= l * prow[cc];
+            for (int cc = j; cc < CW; ++cc) crow_[sb][w][cc] = r[cc];
+          }
+          __syncthreads();
+          T bv = cval[sb][0];
+          int bk = ckey[sb][0], bw = 0;
+#pragma unroll
+          for (int x = 1; x < 4; ++x)
+            if (x < nact) {
+              const T xv = cval[sb][x];
+              const int xk = ckey[sb][x];
+              if (xv > bv || (xv == bv && xk < bk)) {
+                bv = xv;
+                bk = xk;
+                bw = x;
+              }
+            }
+          const T* prow = crow_[sb][bw];
+          if (cand) {
+            if (mypos == bk) {  // this row is the pivot of column j
+              done = true;
+              pv[c0 + j] = c0 + bk;
+              if (r[j] == T(0)) atomicMin(info, ((unsigned long long)a << 20) | (unsigned long long)(c0 + j));
+              mypos = j;
+            } else {
+              if (mypos == j) mypos = bk;  // the row displaced by the interchange
+              const T pivot = prow[j];
+              if (pivot != T(0)) {
+                const T l = r[j] * (T(1) / pivot);
+                r[j] = l;
+#pragma unroll
+                for (int cc = j + 1; cc < CW; ++cc) r[cc] -= l * prow[cc];
+              }
             }
           }
         }
@@ -256,53 +283,44 @@ __global__ __launch_bounds__(kLuThreads, sizeof(T) == 4 ? 5 : 4) void leaf_lu_ke
         if (cc < cw) F[orig + (int64_t)(c0 + cc) * lul] = r[cc];
       if (mypos < CW) {
 #pragma unroll
-        for (int cc = 0; cc < CW; ++cc) dblk[mypos * CW + cc] = r[cc];
+        for (int cc = 0; cc < CW; ++cc) dblk[mypos * CW + cc] = cc < cw ? r[cc] : T(0);
       }
     }
+    // rows beyond m act as identity
+    for (int e = cw * CW + tid; e < CW * CW; e += kLuThreads) dblk[e] = e / CW == e % CW ? T(1) : T(0);
     __syncthreads();
     if (own) pm[c0 + mypos] = orig;
-    // inverses of the new 16 x 16 diagonal blocks: threads 0..31 invert the
-    // unit-lower L blocks, 32..63 the upper U blocks (one column each); rows
-    // beyond m act as identity
-    if (tid < 64) {
-      const int half = (tid >> 4) & 1;
-      int cc = tid & 15;
+    // inverses of the new 16 x 16 diagonal blocks, a column per thread in
+    // registers: wave 0 the unit-lower L blocks, wave 1 the upper U blocks
+    if (lane < 32 && w < 2) {
+      const int half = lane >> 4, kb = (CW / 16) * c + half;
+      int cc = li;
       asm volatile("" : "+v"(cc));  // keeps the identity columns from being hoisted out of the chunk loop
-      const int kb = (CW / 16) * c + half;
-      const int g0 = 16 * kb;
       const T* Bk = dblk + (16 * half) * CW + 16 * half;  // element (i, j) at Bk[i * CW + j]
-      T* xs = stage + CW * CW + tid * 16;                  // this thread's column, in LDS (rolled loops: few registers)
-      if (half < CW / 16 && kb < nbk) {
-        if (tid < 32) {
-#pragma unroll 1
+      if (kb < nbk) {
+        T x[16];
+        if (w == 0) {
+#pragma unroll
           for (int i = 0; i < 16; ++i) {
             T sacc = (i == cc) ? T(1) : T(0);
-            for (int jj = 0; jj < i; ++jj) {
-              const T bv = Bk[i * CW + jj];
-              sacc -= ((g0 + i < m) ? bv : T(0)) * xs[jj];
-            }
-            xs[i] = (i >= cc) ? sacc : T(0);
-          }
 #pragma unroll
-          for (int i = 0; i < 16; ++i) IL[kb * 256 + i * 16 + cc] = xs[i];
+            for (int jj = 0; jj < i; ++jj) sacc -= Bk[i * CW + jj] * x[jj];
+            x[i] = (i >= cc) ? sacc : T(0);
+            IL[kb * 256 + i * 16 + cc] = x[i];
+          }
         } else {
-#pragma unroll 1
+#pragma unroll
           for (int i = 15; i >= 0; --i) {
             T sacc = (i == cc) ? T(1) : T(0);
-            for (int jj = i + 1; jj < 16; ++jj) {
-              const T bv = Bk[i * CW + jj];
-              sacc -= ((g0 + i < m && g0 + jj < m) ? bv : T(0)) * xs[jj];
-            }
-            const T dv = Bk[i * CW + i];
-            const T d = (g0 + i < m) ? dv : T(1);
-            xs[i] = (i <= cc) ? sacc / d : T(0);
-          }
 #pragma unroll
-          for (int i = 0; i < 16; ++i) IL[(ldl / 16 + kb) * 256 + i * 16 + cc] = xs[i];
+            for (int jj = i + 1; jj < 16; ++jj) sacc -= Bk[i * CW + jj] * x[jj];
+            x[i] = (i <= cc) ? sacc / Bk[i * CW + i] : T(0);
+            IL[(ldl / 16 + kb) * 256 + i * 16 + cc] = x[i];
+          }
         }
       }
-    } else if (tid < 64 + CW && c0 + tid - 64 < ldl) {
-      const int j = tid - 64;
+    } else if (w == 2 && lane < CW && c0 + lane < ldl) {
+      const int j = lane;
       udinv[(int64_t)a * ldl + c0 + j] = (j < cw) ? T(1) / dblk[j * CW + j] : T(1);
     }
     __syncthreads();
