@@ -11,15 +11,18 @@
 // exhausted step (v(j_k) = 0) giving u_k = v_k = 0.  U_a = [u_k] goes to rows
 // I_a, V_b = [v_k] to rows I_b of the level's columns of U_big / V_big.
 //
-// All blocks of all levels advance together: step k is one launch for the
+// Blocks of up to kCbRows rows and columns and ranks up to kCbRank take all their
+// steps in one workgroup (aca_block_kernel).  The others
+// advance together: step k is one launch for the
 // residual rows (a workgroup per 1024-column tile of a block, writing v
 // unnormalized and the tile's largest modulus) and one for the residual
 // columns (each workgroup first reduces its block's row partials to j_k and
 // the pivot value, normalizes its tile of v, then forms its tile of u and the
 // tile's largest modulus over unused rows); the next row launch reduces those
 // to i_{k+1}.  Partials are reduced in a fixed order (deterministic).
-#include "internal.h"
+#include "wave.h"
 
+#include <algorithm>
 #include <climits>
 
 namespace hodlr {
@@ -31,14 +34,10 @@ constexpr int kCsEpt = 4;
 constexpr int kCsTile = kCsThreads * kCsEpt;  // elements of a block row / column per workgroup
 constexpr double kPi = 3.141592653589793238462643383279502884;
 
-__device__ __forceinline__ double kernel_offdiag(const ConstructKernel& k, int64_t p, int64_t q) {
-  double d2 = 0.0, dx0 = 0.0, dx1 = 0.0;
-  for (int d = 0; d < k.dim; ++d) {
-    const double t = k.pts[p + d * k.ldp] - k.pts[q + d * k.ldp];
-    d2 += t * t;
-    if (d == 0) dx0 = t;
-    if (d == 1) dx1 = t;
-  }
+// the entry of points p and q from |x_p - x_q|^2, the first two differences and
+// the normal and weight of q
+__device__ __forceinline__ double kernel_value(const ConstructKernel& k, double d2, double dx0, double dx1, double n0,
+                                               double n1, double wq) {
   switch (k.kind) {
     case HODLR_KERNEL_GAUSS:
       return exp(-d2 / (2.0 * (k.ell * k.ell)));
@@ -47,10 +46,22 @@ __device__ __forceinline__ double kernel_offdiag(const ConstructKernel& k, int64
       return (1.0 + s) * exp(-s);
     }
     default: {  // Laplace double layer: w_q n_q . (x_p - x_q) / (2 pi |x_p - x_q|^2)
-      const double num = k.nrm[q] * dx0 + k.nrm[q + k.ldp] * dx1;
-      return num / (2.0 * kPi * d2) * k.w[q];
+      const double num = n0 * dx0 + n1 * dx1;
+      return num / (2.0 * kPi * d2) * wq;
     }
   }
+}
+
+__device__ __forceinline__ double kernel_offdiag(const ConstructKernel& k, int64_t p, int64_t q) {
+  double d2 = 0.0, dx0 = 0.0, dx1 = 0.0;
+  for (int d = 0; d < k.dim; ++d) {
+    const double t = k.pts[p + d * k.ldp] - k.pts[q + d * k.ldp];
+    d2 += t * t;
+    if (d == 0) dx0 = t;
+    if (d == 1) dx1 = t;
+  }
+  if (k.kind != HODLR_KERNEL_LAPLACE_DL) return kernel_value(k, d2, dx0, dx1, 0.0, 0.0, 0.0);
+  return kernel_value(k, d2, dx0, dx1, k.nrm[q], k.nrm[q + k.ldp], k.w[q]);
 }
 
 __device__ __forceinline__ double kernel_entry(const ConstructKernel& k, int64_t p, int64_t q) {
@@ -276,6 +287,136 @@ __global__ __launch_bounds__(kCsThreads) void aca_col_kernel(ConstructKernel kd,
   }
 }
 
+// All steps of one block, one row and one column of it per thread: the generators
+// stay in registers (2 x 32 doubles a thread), the points in LDS, and memory sees
+// only the finished columns.  (The tiled steps read every earlier column again:
+// 496 of them per generator at rank 32, and run at 4.2 TB/s.)  Each wave publishes
+// its best candidate with its generator row, so a half step is one barrier;
+// bound by that chain (entry, subtractions in order of l, search).  Entries,
+// order of subtractions and choice of pivots are those of the tiled steps, and so
+// are the results, to the bit.  N = 262144, leaf 128, rank 32: 0.22 ms a level
+// (tiled 0.53); the whole construction 4.78 ms (tiled 5.85).  The limits: two
+// generators of rank 32 take half of the registers at 512 threads.
+constexpr int kCbRank = 32;
+constexpr int kCbRows = 512;
+
+template <int NT>
+__global__ __launch_bounds__(NT, 2) void aca_block_kernel(ConstructKernel kd, const AcaBlock* __restrict__ blocks,
+                                                          double* __restrict__ U, int64_t ldu,
+                                                          double* __restrict__ V, int64_t ldv) {
+  constexpr int NW = NT / 64;
+  const AcaBlock b = blocks[blockIdx.x];
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  __shared__ double rpt[3][NT], cpt[6][NT];                   // row points; column points, normals, weights
+  __shared__ __align__(16) double hist[2][NW][kCbRank];       // per wave: its candidate's generator row
+  __shared__ unsigned long long ckey[2][NW];                  // order of moduli (see below)
+  __shared__ int cidx[2][NW];
+  __shared__ double cval[2][NW];
+  const bool isrow = tid < b.m, iscol = tid < b.n, dl = kd.kind == HODLR_KERNEL_LAPLACE_DL;
+  for (int d = 0; d < kd.dim; ++d) {
+    if (isrow) rpt[d][tid] = kd.pts[b.r0 + tid + d * kd.ldp];
+    if (iscol) cpt[d][tid] = kd.pts[b.c0 + tid + d * kd.ldp];
+  }
+  if (dl && iscol) {
+    cpt[3][tid] = kd.nrm[b.c0 + tid];
+    cpt[4][tid] = kd.nrm[b.c0 + tid + kd.ldp];
+    cpt[5][tid] = kd.w[b.c0 + tid];
+  }
+  __syncthreads();
+
+  auto entry = [&](int i, int j) {
+    double d2 = 0.0, dx0 = 0.0, dx1 = 0.0;
+    for (int d = 0; d < kd.dim; ++d) {
+      const double t = rpt[d][i] - cpt[d][j];
+      d2 += t * t;
+      if (d == 0) dx0 = t;
+      if (d == 1) dx1 = t;
+    }
+    if (!dl) return kernel_value(kd, d2, dx0, dx1, 0.0, 0.0, 0.0);
+    return kernel_value(kd, d2, dx0, dx1, cpt[3][j], cpt[4][j], cpt[5][j]);
+  };
+  // x - sum_{l<k} c_l g_l in order of l (both are zero from l = k on)
+  auto residual = [&](double x, const double* c, const double (&g)[kCbRank], int k) {
+#pragma unroll
+    for (int l0 = 0; l0 < kCbRank; l0 += 8)
+      if (l0 < k) {
+#pragma unroll
+        for (int l = l0; l < l0 + 8; ++l) x -= c[l] * g[l];
+      }
+    return x;
+  };
+  // The largest modulus, lowest index on ties, of candidates x (absent: NaN or
+  // out of the block; last: before these): published per wave with its row g
+  // (whole groups of 8 below k), then chosen from the waves.  Moduli are compared as integers.
+  auto pick = [&](int sb, double x, bool in, bool last, const double (&g)[kCbRank], int k, int& wave) {
+    const unsigned long long bits = __builtin_bit_cast(unsigned long long, x) & 0x7fffffffffffffffull;
+    const bool open = in && (last || x == x);
+    const uint32_t hi = !open ? 0u : last ? 1u : (uint32_t)(bits >> 32) + 2u;
+    const uint32_t lo = open && !last ? (uint32_t)bits : 0u;
+    const uint32_t mh = wave_max(hi);
+    bool best = hi == mh;
+    const uint32_t ml = wave_max(best ? lo : 0u);  // (lane moves: every lane takes part)
+    best = best && lo == ml;
+    const unsigned long long hit = __ballot(best);  // indices ascend with the lane
+    if (lane == (int)__builtin_ctzll(hit)) {
+      ckey[sb][w] = ((unsigned long long)mh << 32) | ml;
+      cidx[sb][w] = tid;
+      cval[sb][w] = x;
+#pragma unroll
+      for (int l0 = 0; l0 < kCbRank; l0 += 8)
+        if (l0 < k) {
+#pragma unroll
+          for (int l = l0; l < l0 + 8; ++l) hist[sb][w][l] = g[l];
+        }
+    }
+    __syncthreads();
+    unsigned long long key = ckey[sb][0];
+    wave = 0;
+#pragma unroll
+    for (int o = 1; o < NW; ++o) {
+      const unsigned long long ko = ckey[sb][o];
+      if (ko > key) {
+        key = ko;
+        wave = o;
+      }
+    }
+    wave = __builtin_amdgcn_readfirstlane(wave);
+  };
+
+  double u[kCbRank], v[kCbRank];
+#pragma unroll
+  for (int l = 0; l < kCbRank; ++l) u[l] = v[l] = 0.0;
+  int i = 0, wi = 0;
+  bool used = false;
+#pragma unroll 1
+  for (int k = 0; k < b.rank; ++k) {
+    used = used || tid == i;
+    double x = 0.0;
+    if (iscol) x = residual(entry(i, tid), hist[1][wi], v, k);
+    int wj;
+    pick(0, x, iscol, false, v, k, wj);
+    const int j = cidx[0][wj];
+    const double delta = cval[0][wj];
+    const bool exhausted = delta == 0.0;
+    const double vk = exhausted ? 0.0 : x / delta;
+    if (iscol) V[(b.c0 + tid) + (int64_t)(b.col + k) * ldv] = vk;
+    double y = 0.0;
+    if (isrow && !exhausted) y = residual(entry(tid, j), hist[0][wj], u, k);
+    if (isrow) U[(b.r0 + tid) + (int64_t)(b.col + k) * ldu] = y;
+#pragma unroll
+    for (int l0 = 0; l0 < kCbRank; l0 += 8)
+      if (l0 == (k & ~7)) {
+#pragma unroll
+        for (int l = l0; l < l0 + 8; ++l) {
+          v[l] = l == k ? (iscol ? vk : 0.0) : v[l];
+          u[l] = l == k ? y : u[l];
+        }
+      }
+    pick(1, y, isrow, used, u, k + 1, wi);
+    i = cidx[1][wi];
+  }
+}
+
 // FP64 n x c (ld lds) to the storage type (ld ldd)
 template <typename TS>
 __global__ __launch_bounds__(kCsThreads) void store_cols_kernel(int64_t n, const double* __restrict__ src, int64_t lds,
@@ -299,6 +440,26 @@ template hipError_t launch_construct_leaves<float>(hipStream_t, const ConstructK
                                                    float*, int64_t);
 
 int aca_tile_elems() { return kCsTile; }
+
+int aca_block_class(int m, int n, int rank) {
+  const int rows = std::max(m, n);
+  if (rank > kCbRank || rows > kCbRows) return -1;
+  return rows <= 128 ? 0 : rows <= 256 ? 1 : 2;
+}
+
+hipError_t launch_aca_blocks(hipStream_t s, const ConstructKernel& k, int cls, int nblocks, const AcaBlock* blocks,
+                             double* U, int64_t ldu, double* V, int64_t ldv) {
+  if (nblocks == 0) return hipSuccess;
+  if (cls == 0)
+    hipLaunchKernelGGL(aca_block_kernel<128>, dim3(nblocks), dim3(128), 0, s, k, blocks, U, ldu, V, ldv);
+  else if (cls == 1)
+    hipLaunchKernelGGL(aca_block_kernel<256>, dim3(nblocks), dim3(256), 0, s, k, blocks, U, ldu, V, ldv);
+  else if (cls == 2)
+    hipLaunchKernelGGL(aca_block_kernel<kCbRows>, dim3(nblocks), dim3(kCbRows), 0, s, k, blocks, U, ldu, V, ldv);
+  else
+    return hipErrorInvalidValue;
+  return hipGetLastError();
+}
 
 hipError_t launch_aca_step(hipStream_t s, const ConstructKernel& k, int ntiles, const AcaBlock* blocks,
                            const AcaTile* tiles, int step, int kmax, double* U, int64_t ldu, double* V, int64_t ldv,

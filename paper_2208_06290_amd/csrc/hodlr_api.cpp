@@ -1711,14 +1711,13 @@ hodlr_status hodlr_construct(const hodlr_kernel* k, int64_t n, int32_t levels, c
   if (s) return s;
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int L = levels;
-  int R = 0, kmax = 0;
-  for (int r : rk) {
-    R += r;
-    kmax = std::max(kmax, r);
-  }
+  int R = 0;
+  for (int r : rk) R += r;
   hodlr::ConstructKernel kd{(int)k->kind, k->dim, k->points, k->ldp, k->normals, k->weights, k->curvature, k->ell,
                             k->shift};
   DevMem M;
+  std::vector<hodlr::AcaBlock> all;
+  std::vector<hodlr::AcaTile> tiles;
   auto run = [&]() -> hodlr_status {
     hodlr_status e;
     int64_t* d_off = nullptr;
@@ -1733,43 +1732,51 @@ hodlr_status hodlr_construct(const hodlr_kernel* k, int64_t n, int32_t levels, c
       HL("construct_leaves",
          hodlr::launch_construct_leaves<float>(st, kd, nleaf, d_off, m_max, static_cast<float*>(D), ldd));
     if (R == 0) return HODLR_OK;
-    // the sibling blocks of every level and their tiles
+    // the sibling blocks of every level: those of one workgroup by class, then
+    // the tiled ones and their tiles
     const int te = hodlr::aca_tile_elems();
-    std::vector<hodlr::AcaBlock> blocks;
-    std::vector<hodlr::AcaTile> tiles;
-    int col = 0;
+    std::vector<hodlr::AcaBlock> blocks[4];
+    int col = 0, kmax = 0;
     for (int l = 1; l <= L; ++l) {
       const int r = rk[l - 1];
       if (r > 0) {
         const int per = 1 << (L - l);
         for (int a = 0; a < (1 << l); ++a) {
           const int b = a ^ 1;
-          hodlr::AcaBlock B;
+          hodlr::AcaBlock B{};
           B.r0 = off[(size_t)a * per];
           B.m = (int32_t)(off[(size_t)(a + 1) * per] - B.r0);
           B.c0 = off[(size_t)b * per];
           B.n = (int32_t)(off[(size_t)(b + 1) * per] - B.c0);
           B.col = col;
           B.rank = r;
+          const int cls = hodlr::aca_block_class(B.m, B.n, r);
+          if (cls >= 0) {
+            blocks[cls].push_back(B);
+            continue;
+          }
           B.tile0 = (int32_t)tiles.size();
           B.ntile = (std::max(B.m, B.n) + te - 1) / te;
-          for (int t = 0; t < B.ntile; ++t) tiles.push_back({(int32_t)blocks.size(), t, (int32_t)tiles.size()});
-          blocks.push_back(B);
+          for (int t = 0; t < B.ntile; ++t) tiles.push_back({(int32_t)blocks[3].size(), t, (int32_t)tiles.size()});
+          blocks[3].push_back(B);
+          kmax = std::max(kmax, r);
         }
       }
       col += r;
     }
+    for (auto& v : blocks) all.insert(all.end(), v.begin(), v.end());
     const size_t nt = tiles.size();
     hodlr::AcaBlock* d_blocks = nullptr;
     hodlr::AcaTile* d_tiles = nullptr;
     hodlr::AcaPartials P{};
-    if ((e = M.alloc(&d_blocks, blocks.size())) || (e = M.alloc(&d_tiles, nt)) || (e = M.alloc(&P.rp_abs, nt)) ||
+    if ((e = M.alloc(&d_blocks, all.size())) || (e = M.alloc(&d_tiles, nt)) || (e = M.alloc(&P.rp_abs, nt)) ||
         (e = M.alloc(&P.rp_val, nt)) || (e = M.alloc(&P.rp_idx, nt)) || (e = M.alloc(&P.cp_abs, nt)) ||
-        (e = M.alloc(&P.cp_idx, nt)) || (e = M.alloc(&P.piv, blocks.size() * kmax)))
+        (e = M.alloc(&P.cp_idx, nt)) || (e = M.alloc(&P.piv, blocks[3].size() * kmax)))
       return e;
-    if (hipMemcpyAsync(d_blocks, blocks.data(), blocks.size() * sizeof(hodlr::AcaBlock), hipMemcpyHostToDevice, st) !=
+    if (hipMemcpyAsync(d_blocks, all.data(), all.size() * sizeof(hodlr::AcaBlock), hipMemcpyHostToDevice, st) !=
             hipSuccess ||
-        hipMemcpyAsync(d_tiles, tiles.data(), nt * sizeof(hodlr::AcaTile), hipMemcpyHostToDevice, st) != hipSuccess)
+        (nt && hipMemcpyAsync(d_tiles, tiles.data(), nt * sizeof(hodlr::AcaTile), hipMemcpyHostToDevice, st) !=
+                   hipSuccess))
       return HODLR_ERR_HIP;
     double* U64 = static_cast<double*>(U);
     double* V64 = static_cast<double*>(V);
@@ -1778,8 +1785,13 @@ hodlr_status hodlr_construct(const hodlr_kernel* k, int64_t n, int32_t levels, c
       if ((e = M.alloc(&U64, (size_t)n * R)) || (e = M.alloc(&V64, (size_t)n * R))) return e;
       ldu64 = ldv64 = n;
     }
+    const hodlr::AcaBlock* d_cls = d_blocks;
+    for (int c = 0; c < 3; ++c) {
+      HL("aca_block", hodlr::launch_aca_blocks(st, kd, c, (int)blocks[c].size(), d_cls, U64, ldu64, V64, ldv64));
+      d_cls += blocks[c].size();
+    }
     for (int step = 0; step < kmax; ++step)
-      HL("aca_step", hodlr::launch_aca_step(st, kd, (int)nt, d_blocks, d_tiles, step, kmax, U64, ldu64, V64, ldv64, P));
+      HL("aca_step", hodlr::launch_aca_step(st, kd, (int)nt, d_cls, d_tiles, step, kmax, U64, ldu64, V64, ldv64, P));
     if (dtype == HODLR_F32) {
       HL("construct_store", hodlr::launch_store_cols<float>(st, n, R, U64, ldu64, static_cast<float*>(U), ldu));
       HL("construct_store", hodlr::launch_store_cols<float>(st, n, R, V64, ldv64, static_cast<float*>(V), ldv));

@@ -269,7 +269,13 @@ int aca_tile_elems();
 template <typename TS>
 hipError_t launch_construct_leaves(hipStream_t s, const ConstructKernel& k, int nleaf, const int64_t* d_off, int m_max,
                                    TS* D, int64_t ldd);
-// step `step` of every block (rank > step): the residual-row launch and the residual-column launch
+// Blocks that one workgroup takes through all steps: the class of a block's
+// kernel (0 .. 2), or -1 for the tiled steps; the launch for nblocks of a class
+// (their tile0 and ntile are not used).
+int aca_block_class(int m, int n, int rank);
+hipError_t launch_aca_blocks(hipStream_t s, const ConstructKernel& k, int cls, int nblocks, const AcaBlock* blocks,
+                             double* U, int64_t ldu, double* V, int64_t ldv);
+// step `step` of every tiled block (rank > step): the residual-row launch and the residual-column launch
 hipError_t launch_aca_step(hipStream_t s, const ConstructKernel& k, int ntiles, const AcaBlock* blocks,
                            const AcaTile* tiles, int step, int kmax, double* U, int64_t ldu, double* V, int64_t ldv,
                            AcaPartials p);

@@ -1,0 +1,34 @@
+"""Cross approximation of single blocks at the edges of the one-workgroup
+kernels (128, 256 and 512 rows or columns, more rows than columns and the other
+way round, ranks 1 to 33, which take the tiled steps), against the construction
+oracle: the same pivots exactly (residuals far above rounding), approximants to
+1e-12 of the block."""
+import numpy as np
+import pytest
+
+import oracle as O
+from test_gpu_construct import _gpu_build, _spec
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("kind,dim,rank", [("gauss", 2, 8), ("matern32", 3, 32), ("matern32", 3, 33), ("laplace_dl", 2, 6),
+                                           ("gauss", 1, 1)])
+@pytest.mark.parametrize("m,n", [(40, 64), (128, 127), (129, 60), (200, 256), (256, 257), (512, 300), (511, 512), (513, 100)])
+def test_blocks(kind, dim, rank, m, n):
+    off = np.array([0, m, m + n], dtype=np.int64)
+    if max(m, n) > 256:  # leaves hold up to 256 rows: halve them
+        off = np.array([0, m // 2, m, m + n // 2, m + n], dtype=np.int64)
+        if max(np.diff(off)) > 256:
+            off = np.array(sorted({0, m // 4, m // 2, 3 * m // 4, m, m + n // 4, m + n // 2, m + 3 * n // 4, m + n}))
+    L = int(np.log2(len(off) - 1))
+    ranks = [rank] + [0] * (L - 1)
+    spec = _spec(kind, m + n, dim, 3, 0.1)
+    A = _gpu_build(spec, ranks, off)
+    U, V = A.U.cpu().numpy().T, A.V.cpu().numpy().T
+    for (s0, e0), (t0, f0) in (((0, m), (m, m + n)), ((m, m + n), (0, m))):
+        M = O.kernel_entries(spec, np.arange(s0, e0), np.arange(t0, f0))
+        Uo, Vo, I, J = O.aca(lambda ri, cj: M[np.ix_(ri, cj)], e0 - s0, f0 - t0, rank)
+        for k, j in enumerate(J):
+            assert j >= 0 and V[t0 + j, k] == 1.0, k
+        assert np.linalg.norm(U[s0:e0] @ V[t0:f0].T - Uo @ Vo.T) <= 1e-12 * np.linalg.norm(M)
