@@ -919,16 +919,9 @@ hodlr_status matvec_impl(hodlr_factors* F, hipStream_t st, int trans, int nrhs, 
       HL("mv_tree", launch_tree_sum(st, 1 << l, (int64_t)F->R * nrhs, tree + tree_slot(l + 1, 0) * F->R * nrhs,
                                     tree + tree_slot(l, 0) * F->R * nrhs));
   }
-  // every leaf exactly 256 rows (one row per lane of the 4 waves) and every level width a multiple of 4:
-  // the kernel needs no masks
-  bool full = true;
-  for (int a = 0; a < F->nleaf && full; ++a)
-    if (F->off[a + 1] - F->off[a] != 256) full = false;
-  for (int l = 0; l < L && full; ++l)
-    if (F->ranks[l] % 4) full = false;
   HL("mv_apply", (launch_matvec_apply<S>(st, trans, F->nleaf, L, F->d_off, F->d_rpre, F->R,
                                          static_cast<const S*>(F->D), F->ldd, Ua, lda, X, ldx, tree, Yo, ldy, nrhs,
-                                         full)));
+                                         F->tile_shape[L])));
   return HODLR_OK;
 }
 
@@ -1384,18 +1377,18 @@ hodlr_status grad_impl(hodlr_factors* F, Workspace& Wk, hipStream_t st, int64_t 
     HL("grad_leaf", (launch_grad_leaf<double>(st, F->nleaf, F->m_max, F->d_off, n, X, ldx, Lam, ldl,
                                               static_cast<double*>(dD), F->ldd)));
     if (F->R > 0 && L > 0) {
-      HL("grad_gen", (launch_grad_gen<double>(st, F->nleaf, L, F->d_off, F->d_rpre, F->R, n, Lam, ldl, Wk.tree,
+      HL("grad_gen", (launch_grad_gen<double>(st, F->nleaf, F->m_max, L, F->d_off, F->d_rpre, F->R, n, Lam, ldl, Wk.tree,
                                               static_cast<double*>(dU), F->ldu)));
-      HL("grad_gen", (launch_grad_gen<double>(st, F->nleaf, L, F->d_off, F->d_rpre, F->R, n, X, ldx, Wk.tree2,
+      HL("grad_gen", (launch_grad_gen<double>(st, F->nleaf, F->m_max, L, F->d_off, F->d_rpre, F->R, n, X, ldx, Wk.tree2,
                                               static_cast<double*>(dV), F->ldv)));
     }
   } else {
     HL("grad_leaf", (launch_grad_leaf<float>(st, F->nleaf, F->m_max, F->d_off, n, X, ldx, Lam, ldl,
                                              static_cast<float*>(dD), F->ldd)));
     if (F->R > 0 && L > 0) {
-      HL("grad_gen", (launch_grad_gen<float>(st, F->nleaf, L, F->d_off, F->d_rpre, F->R, n, Lam, ldl, Wk.tree,
+      HL("grad_gen", (launch_grad_gen<float>(st, F->nleaf, F->m_max, L, F->d_off, F->d_rpre, F->R, n, Lam, ldl, Wk.tree,
                                              static_cast<float*>(dU), F->ldu)));
-      HL("grad_gen", (launch_grad_gen<float>(st, F->nleaf, L, F->d_off, F->d_rpre, F->R, n, X, ldx, Wk.tree2,
+      HL("grad_gen", (launch_grad_gen<float>(st, F->nleaf, F->m_max, L, F->d_off, F->d_rpre, F->R, n, X, ldx, Wk.tree2,
                                              static_cast<float*>(dV), F->ldv)));
     }
   }
@@ -1570,8 +1563,8 @@ hodlr_status logdet_grad_impl(hodlr_factors* F, hipStream_t st, DevMem& M, void*
   HL("logdet_grad", (launch_convert<double, T>(st, N, R, tp<T>(FT->Y), FT->ldy, Yt64, N, FT->gsy)));
   if ((s = logdet_pblocks<T>(F, st, Pd, pdoff))) return s;
   // Lam(I_a, c_l) = (A_a^{-T} V_a) P_a^T; YP(I_a, c_l) = Y_a P_a
-  HL("logdet_grad", launch_node_mix(st, N, L, R, F->d_off, F->d_rpre, d_pdoff, Pd, 1, Yt64, Lam));
-  HL("logdet_grad", launch_node_mix(st, N, L, R, F->d_off, F->d_rpre, d_pdoff, Pd, 0, Y64, YP));
+  HL("logdet_grad", launch_node_mix(st, N, F->nleaf, F->m_max, L, R, F->d_off, F->d_rpre, d_pdoff, Pd, 1, Yt64, Lam));
+  HL("logdet_grad", launch_node_mix(st, N, F->nleaf, F->m_max, L, R, F->d_off, F->d_rpre, d_pdoff, Pd, 0, Y64, YP));
   // dD = D^{-T} - Lam Y^T on the leaf blocks
   HL("logdet_grad", launch_grad_leaf<S>(st, F->nleaf, F->m_max, F->d_off, R, Y64, N, Lam, N, dD, F->ldd, E64, N));
   // projection trees V^T Y and U^T Lam (per node, all columns)
@@ -1588,8 +1581,8 @@ hodlr_status logdet_grad_impl(hodlr_factors* F, hipStream_t st, DevMem& M, void*
   };
   if ((s = project(F->V, F->ldv, Y64, tV))) return s;
   if ((s = project(F->U, F->ldu, Lam, tU))) return s;
-  HL("logdet_grad", launch_grad_gen<S>(st, F->nleaf, L, F->d_off, F->d_rpre, R, R, Lam, N, tV, dU, F->ldu, Lam, N, 1));
-  HL("logdet_grad", launch_grad_gen<S>(st, F->nleaf, L, F->d_off, F->d_rpre, R, R, Y64, N, tU, dV, F->ldv, YP, N, 1));
+  HL("logdet_grad", launch_grad_gen<S>(st, F->nleaf, F->m_max, L, F->d_off, F->d_rpre, R, R, Lam, N, tV, dU, F->ldu, Lam, N, 1));
+  HL("logdet_grad", launch_grad_gen<S>(st, F->nleaf, F->m_max, L, F->d_off, F->d_rpre, R, R, Y64, N, tU, dV, F->ldv, YP, N, 1));
   return HODLR_OK;
 }
 }  // namespace

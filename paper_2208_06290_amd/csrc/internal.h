@@ -161,7 +161,8 @@ __host__ __device__ inline int64_t tree_slot(int l, int node) { return ((int64_t
 template <typename S>
 hipError_t launch_matvec_apply(hipStream_t s, int trans, int nleaf, int L, const int64_t* d_leaf_off,
                                const int32_t* d_rpre, int R, const S* D, int64_t ldd, const S* Ua, int64_t lda,
-                               const double* X, int64_t ldx, const double* tree, double* Y, int64_t ldy, int nrhs, int full);
+                               const double* X, int64_t ldx, const double* tree, double* Y, int64_t ldy, int nrhs,
+                               TileShape sh);  // sh: of the leaves
 
 // Gradient pieces.  grad_leaf: dD_a = add_a - Lam_a X_a^T on the leaf blocks (add may be null).
 // grad_gen: out(I_a, c) = add(I_a, c) - Left(I_a, :) S(c, :)^T with S the projection-tree entry of
@@ -172,8 +173,8 @@ hipError_t launch_grad_leaf(hipStream_t s, int nleaf, int m_max, const int64_t* 
                             const double* X, int64_t ldx, const double* Lam, int64_t ldl, S* dD, int64_t ldd,
                             const double* add = nullptr, int64_t ldadd = 0);
 template <typename S>
-hipError_t launch_grad_gen(hipStream_t s, int nleaf, int L, const int64_t* d_leaf_off, const int32_t* d_rpre, int R,
-                           int nrhs, const double* Left, int64_t ldl, const double* tree, S* out, int64_t ldo,
+hipError_t launch_grad_gen(hipStream_t s, int nleaf, int m_max, int L, const int64_t* d_leaf_off,
+                           const int32_t* d_rpre, int R, int nrhs, const double* Left, int64_t ldl, const double* tree, S* out, int64_t ldo,
                            const double* add = nullptr, int64_t ldadd = 0, int tri = 0);
 
 // Refinement helpers (FP64).
@@ -228,8 +229,11 @@ template <typename T>
 hipError_t launch_identity_leaves(hipStream_t s, int nleaf, int ncols, const int64_t* d_leaf_off, T* E, int64_t lde);
 template <typename T>
 hipError_t launch_pblocks(hipStream_t s, int nparents, int r, const T* Kinv, int64_t ldk, int64_t pstride, double* Pd);
-hipError_t launch_node_mix(hipStream_t s, int64_t n, int L, int R, const int64_t* d_leaf_off, const int32_t* d_rpre,
-                           const int64_t* d_pdoff, const double* Pd, int trans, const double* in, double* out);
+// out(i, c) = sum_k in(i, R_{l-1} + k) M_a(k, c - R_{l-1}) for every column c (level l) and row i
+// (node a of level l), M_a = P_a (trans: P_a^T) from Pd at element pdoff[l] + a r_l^2; FP64, N x R, ld N
+hipError_t launch_node_mix(hipStream_t s, int64_t n, int nleaf, int m_max, int L, int R, const int64_t* d_leaf_off,
+                           const int32_t* d_rpre, const int64_t* d_pdoff, const double* Pd, int trans,
+                           const double* in, double* out);
 }  // namespace hodlr
 
 namespace hodlr {

@@ -21,18 +21,6 @@ namespace hodlr {
 
 constexpr int kLpThreads = 256;
 
-// N consecutive elements at any element alignment.
-template <typename S, int N>
-struct Vec {
-  typedef S type __attribute__((ext_vector_type(N), aligned(sizeof(S))));
-};
-template <typename S, typename T, int N>
-__device__ __forceinline__ void load_run(const S* p, T (&d)[N]) {
-  const typename Vec<S, N>::type v = *reinterpret_cast<const typename Vec<S, N>::type*>(p);
-#pragma unroll
-  for (int t = 0; t < N; ++t) d[t] = (T)v[t];
-}
-
 // Rows of the accumulators.  A group of 16 RP rows (RP elements are 16 bytes)
 // is RP MFMA blocks; register t of lane group lq in block h is row
 // RP (4 t + lq) + h, so for each t a lane holds 16 contiguous bytes of its

@@ -166,36 +166,6 @@ __global__ void pblocks_kernel(int nparents, int r, const T* __restrict__ Kinv, 
   }
 }
 
-// out(i, c) = sum_k in(i, R_{l-1} + k) M_a(k, c - R_{l-1}) for every column c
-// (level l) and row i (node a of level l), M_a = P_a (trans = 0) or P_a^T
-// (trans = 1) from Pd at element pdoff[l] + a r_l^2; FP64, N x R, ld N
-__global__ void node_mix_kernel(int64_t n, int L, int R, const int64_t* __restrict__ leaf_off,
-                                const int32_t* __restrict__ rpre, const int64_t* __restrict__ pdoff,
-                                const double* __restrict__ Pd, int trans, const double* __restrict__ in,
-                                double* __restrict__ out) {
-  const int64_t total = n * R;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t i = e % n;
-    const int c = (int)(e / n);
-    int l = 1;
-    while (l < L && c >= rpre[l]) ++l;
-    const int c0 = rpre[l - 1], r = rpre[l] - c0, cc = c - c0;
-    // leaf of row i (last leaf offset <= i), then its level-l ancestor
-    int lo = 0, hi = 1 << L;
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (leaf_off[mid] <= i) lo = mid;
-      else hi = mid;
-    }
-    const int64_t a = lo >> (L - l);
-    const double* M = Pd + pdoff[l] + a * r * r;
-    double acc = 0.0;
-    for (int k = 0; k < r; ++k)
-      acc += in[i + (int64_t)(c0 + k) * n] * (trans ? M[cc * r + k] : M[k * r + cc]);
-    out[e] = acc;
-  }
-}
-
 template <typename S>
 hipError_t launch_transpose_leaves(hipStream_t s, int nleaf, int m_max, const int64_t* d_leaf_off, const S* D,
                                    int64_t ldd, S* Dt, int64_t ldt) {
@@ -215,13 +185,6 @@ template <typename T>
 hipError_t launch_pblocks(hipStream_t s, int nparents, int r, const T* Kinv, int64_t ldk, int64_t pstride, double* Pd) {
   if (nparents == 0 || r == 0) return hipSuccess;
   hipLaunchKernelGGL(pblocks_kernel<T>, dim3(256), dim3(256), 0, s, nparents, r, Kinv, ldk, pstride, Pd);
-  return hipGetLastError();
-}
-hipError_t launch_node_mix(hipStream_t s, int64_t n, int L, int R, const int64_t* d_leaf_off, const int32_t* d_rpre,
-                           const int64_t* d_pdoff, const double* Pd, int trans, const double* in, double* out) {
-  if (n == 0 || R == 0) return hipSuccess;
-  hipLaunchKernelGGL(node_mix_kernel, dim3(2048), dim3(256), 0, s, n, L, R, d_leaf_off, d_rpre, d_pdoff, Pd, trans, in,
-                     out);
   return hipGetLastError();
 }
 template hipError_t launch_transpose_leaves<double>(hipStream_t, int, int, const int64_t*, const double*, int64_t,

@@ -10,7 +10,9 @@
 // Gradients (dL/dA = -Lambda X^T restricted to D, U, V):
 //   dD_a = -Lambda_a X_a^T,  dU(I_a, level l) = -Lambda_a (V_b^T X_b)^T,
 //   dV(I_b, level l) = -X_b (U_a^T Lambda_a)^T.
-#include "internal.h"
+#include "mfma.h"
+
+#include <algorithm>
 
 namespace hodlr {
 
@@ -19,7 +21,9 @@ constexpr int kMvThreads = 256;
 __device__ __forceinline__ d4 mma64(double a, double b, d4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
-__device__ __forceinline__ int crow64(int lq, int t) { return 4 * t + lq; }
+// A operand row of lane li such that register t of the product holds row 4 lq + t:
+// four consecutive rows of a lane's column
+__device__ __forceinline__ int row4(int li) { return 4 * (li & 3) + (li >> 2); }
 
 // pairwise tree sum: out[i] = in[2i] + in[2i+1], blocks of `elems`
 __global__ void tree_sum_kernel(int nnodes, int64_t elems, const double* __restrict__ in, double* __restrict__ out) {
@@ -37,72 +41,128 @@ hipError_t launch_tree_sum(hipStream_t s, int nnodes, int64_t elems, const doubl
 }
 
 // y(leaf rows, chunk) = op(D_a) x_a + U(I_a, :) G_a     (op = identity or transpose)
-template <typename S, int TRANS, int NCB, bool FULL>
+// Bound by the latency of streaming D and U for few right-hand sides.  Waves
+// stand WR x WK = 4 over 64-row blocks and groups of 16 K columns (WK = 1, 2, 4 for
+// leaves above 128, up to 128 and up to 64 rows, so that every wave has rows);
+// partial sums meet in LDS in a fixed order.  A lane holds K columns
+// 4 lq + s of a group, contiguous in x, G and a transposed D.  Loads in flight come
+// from the workgroups of a CU (4 to 6): with the next group's operands prefetched
+// they were fewer and it was slower.  FULL: whole 64-row blocks; otherwise rows
+// past the leaf re-read its last one (their results are not stored).
+// N = 131072, leaf 128, R = 240, FP32 storage, one vector: 67 us, transposed 83
+// (four row blocks for every leaf, element loads of a transposed D: 137 and
+// 230); N = 2^20, leaf 256, FP64: 0.93 ms, 5.7 TB/s, as before.
+template <typename S, int TRANS, int NCB, int WK, bool FULL>
 __global__ __launch_bounds__(kMvThreads) void matvec_apply_kernel(
     const int64_t* __restrict__ leaf_off, int L, const int32_t* __restrict__ rpre, int R, const S* __restrict__ D,
     int64_t ldd, const S* __restrict__ Ua, int64_t lda, const double* __restrict__ X, int64_t ldx,
     const double* __restrict__ tree, double* __restrict__ Y, int64_t ldy, int nrhs, int zchunks) {
+  constexpr int WR = 4 / WK;
   const int leaf = blockIdx.x / zchunks;
   const int zc = blockIdx.x % zchunks;
   const int64_t o = leaf_off[leaf];
   const int m = (int)(leaf_off[leaf + 1] - o);
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, li = lane & 15, lq = lane >> 4;
+  const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lq = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6), kp = w / WR, wr0 = 64 * (w % WR);
   const int c0 = zc * 64;
-  const int wr0 = 64 * w;
   d4 acc[4][NCB];
 #pragma unroll
   for (int rb = 0; rb < 4; ++rb)
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) acc[rb][cb] = d4{0, 0, 0, 0};
-  // One K-step of 4 columns: A operand rows of the leaf (clamped into range
-  // and masked unless FULL), B operand from x or the level's projections.
-  // Four steps' loads are issued before their MFMAs so several are in flight.
-  auto kstep = [&](bool tr, const S* Am, int64_t ldA, int kcol, int kend, const double* Bm, int64_t ldB, int kofs,
-                   double (&av)[4], double (&bv)[NCB]) {
-    const int kk = kcol + lq, kc = FULL ? kk : min(kk, kend - 1);
+
+  // the K columns: the leaf block (l = 0, rows of x), then every level (the
+  // sibling's projections V^T x), in groups of 16
+  int l = 0, k0 = 0, kend = m;
+  const S* Ap = D + o;
+  int64_t ldA = ldd, ldB = ldx;
+  const double* Bp = X + o;
+  auto advance = [&](int steps) {
+    for (; steps > 0 && l <= L; --steps) {
+      k0 += 16;
+      while (l <= L && k0 >= kend) {
+        if (++l > L) break;
+        const int cl0 = rpre[l - 1];
+        k0 = 0;
+        kend = rpre[l] - cl0;
+        Ap = Ua + o + (int64_t)cl0 * lda;
+        ldA = lda;
+        Bp = tree + tree_slot(l, (leaf >> (L - l)) ^ 1) * R * nrhs + cl0;
+        ldB = R;
+      }
+    }
+  };
+  auto load = [&](double (&av)[4][4], double (&bv)[NCB][4]) {
+    const bool tr = TRANS && l == 0, whole = k0 + 16 <= kend;  // uniform
+    const int kq = k0 + 4 * lq;
 #pragma unroll
     for (int rb = 0; rb < 4; ++rb) {
-      const int row = wr0 + 16 * rb + li, rc = FULL ? row : min(row, m - 1);
-      const double v = tr ? (double)Am[o + kc + (int64_t)rc * ldA] : (double)Am[o + rc + (int64_t)kc * ldA];
-      av[rb] = (FULL || (row < m && kk < kend)) ? v : 0.0;
+      const int row = wr0 + 16 * rb + row4(li), rc = FULL ? row : min(row, m - 1);
+      if (whole && tr) {
+        load_run(Ap + kq + (int64_t)rc * ldA, av[rb]);
+      } else {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const int kc = whole ? kq + s : min(kq + s, kend - 1);
+          const double v = tr ? (double)Ap[kc + (int64_t)rc * ldA] : (double)Ap[rc + (int64_t)kc * ldA];
+          av[rb][s] = whole || kq + s < kend ? v : 0.0;
+        }
+      }
     }
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) {
-      const int col = c0 + 16 * cb + li;
-      const double v = Bm[kofs + kc + (int64_t)min(col, nrhs - 1) * ldB];
-      bv[cb] = ((FULL || kk < kend) && col < nrhs) ? v : 0.0;
+      const double* col = Bp + (int64_t)min(c0 + 16 * cb + li, nrhs - 1) * ldB;
+      if (whole) {
+        load_run(col + kq, bv[cb]);
+      } else {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const double v = col[min(kq + s, kend - 1)];
+          bv[cb][s] = kq + s < kend ? v : 0.0;
+        }
+      }
     }
   };
-  auto run = [&](bool tr, const S* Am, int64_t ldA, int kbeg, int kend, const double* Bm, int64_t ldB, int kofs) {
-    int k0 = kbeg;
-    for (; k0 + 16 <= kend; k0 += 16) {
-      double av[4][4], bv[4][NCB];
+  auto use = [&](const double (&av)[4][4], const double (&bv)[NCB][4]) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) kstep(tr, Am, ldA, k0 + 4 * u, kend, Bm, ldB, kofs, av[u], bv[u]);
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int rb = 0; rb < 4; ++rb)
-#pragma unroll
-          for (int cb = 0; cb < NCB; ++cb) acc[rb][cb] = mma64(av[u][rb], bv[u][cb], acc[rb][cb]);
-    }
-    for (; k0 < kend; k0 += 4) {
-      double av[4], bv[NCB];
-      kstep(tr, Am, ldA, k0, kend, Bm, ldB, kofs, av, bv);
+    for (int s = 0; s < 4; ++s)
 #pragma unroll
       for (int rb = 0; rb < 4; ++rb)
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) acc[rb][cb] = mma64(av[rb], bv[cb], acc[rb][cb]);
-    }
+        for (int cb = 0; cb < NCB; ++cb) acc[rb][cb] = mma64(av[rb][s], bv[cb][s], acc[rb][cb]);
   };
-  // leaf block: rows of x are the leaf's rows
-  run(TRANS, D, ldd, 0, m, X + o, ldx, 0);
-  // low-rank blocks of every level: the sibling's projections V^T x
-  for (int l = 1; l <= L; ++l) {
-    const int cl0 = rpre[l - 1], cl1 = rpre[l];
-    if (cl1 == cl0) continue;
-    const int node = leaf >> (L - l);
-    run(false, Ua, lda, cl0, cl1, tree + tree_slot(l, node ^ 1) * R * nrhs, R, 0);
+  if (wr0 < m) {
+    advance(kp);
+#pragma unroll 1
+    while (l <= L) {
+      double av[4][4], bv[NCB][4];
+      load(av, bv);
+      use(av, bv);
+      advance(WK);
+    }
+  }
+  if constexpr (WK > 1) {
+    __shared__ double red[4 - WR][NCB][4][64];
+#pragma unroll
+    for (int rb = 0; rb < 4; ++rb) {
+      if (rb > 0) __syncthreads();
+      if (kp > 0) {
+#pragma unroll
+        for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+          for (int t = 0; t < 4; ++t) red[w - WR][cb][t][lane] = acc[rb][cb][t];
+      }
+      __syncthreads();
+      if (kp == 0) {
+#pragma unroll
+        for (int u = 1; u < WK; ++u)
+#pragma unroll
+          for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) acc[rb][cb][t] += red[w + (u - 1) * WR][cb][t][lane];
+      }
+    }
+    if (kp > 0) return;
   }
 #pragma unroll
   for (int rb = 0; rb < 4; ++rb)
@@ -110,7 +170,7 @@ __global__ __launch_bounds__(kMvThreads) void matvec_apply_kernel(
     for (int cb = 0; cb < NCB; ++cb)
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
-        const int row = wr0 + 16 * rb + crow64(lq, t);
+        const int row = wr0 + 16 * rb + 4 * lq + t;
         const int col = c0 + 16 * cb + li;
         if (row < m && col < nrhs) Y[o + row + (int64_t)col * ldy] = acc[rb][cb][t];
       }
@@ -120,181 +180,245 @@ template <typename S>
 hipError_t launch_matvec_apply(hipStream_t s, int trans, int nleaf, int L, const int64_t* d_leaf_off,
                                const int32_t* d_rpre, int R, const S* D, int64_t ldd, const S* Ua, int64_t lda,
                                const double* X, int64_t ldx, const double* tree, double* Y, int64_t ldy, int nrhs,
-                               int full) {
+                               TileShape sh) {
   if (nleaf == 0 || nrhs == 0) return hipSuccess;
+  if (sh.rows > 256) return hipErrorInvalidValue;
   const int zchunks = (nrhs + 63) / 64;
   dim3 grid((unsigned)(nleaf * zchunks));
-#define HODLR_MV(TR, NC)                                                                                        \
-  if (full)                                                                                                       \
-    hipLaunchKernelGGL((matvec_apply_kernel<S, TR, NC, true>), grid, dim3(kMvThreads), 0, s, d_leaf_off, L, d_rpre, \
-                       R, D, ldd, Ua, lda, X, ldx, tree, Y, ldy, nrhs, zchunks);                                   \
-  else                                                                                                            \
-    hipLaunchKernelGGL((matvec_apply_kernel<S, TR, NC, false>), grid, dim3(kMvThreads), 0, s, d_leaf_off, L, d_rpre, \
-                       R, D, ldd, Ua, lda, X, ldx, tree, Y, ldy, nrhs, zchunks)
+#define HODLR_MV(TR, NC, WKV, FULLV)                                                                                \
+  hipLaunchKernelGGL((matvec_apply_kernel<S, TR, NC, WKV, FULLV>), grid, dim3(kMvThreads), 0, s, d_leaf_off, L, d_rpre, \
+                     R, D, ldd, Ua, lda, X, ldx, tree, Y, ldy, nrhs, zchunks)
   // chunks of 64 columns; up to 16 or 32 columns a narrower instance (one chunk, no padded MFMA columns)
-  if (trans) {
-    if (nrhs <= 16) { HODLR_MV(1, 1); } else if (nrhs <= 32) { HODLR_MV(1, 2); } else { HODLR_MV(1, 4); }
-  } else {
-    if (nrhs <= 16) { HODLR_MV(0, 1); } else if (nrhs <= 32) { HODLR_MV(0, 2); } else { HODLR_MV(0, 4); }
+#define HODLR_MVC(TR, WKV, FULLV)                                                                   \
+  if (nrhs <= 16) HODLR_MV(TR, 1, WKV, FULLV); else if (nrhs <= 32) HODLR_MV(TR, 2, WKV, FULLV); else HODLR_MV(TR, 4, WKV, FULLV)
+#define HODLR_MVW(TR)                                                                \
+  if (sh.rows > 128) {                                                               \
+    if (sh.mult(64)) { HODLR_MVC(TR, 1, true); } else { HODLR_MVC(TR, 1, false); }   \
+  } else if (sh.rows > 64) {                                                         \
+    if (sh.mult(64)) { HODLR_MVC(TR, 2, true); } else { HODLR_MVC(TR, 2, false); }   \
+  } else {                                                                           \
+    HODLR_MVC(TR, 4, false);                                                         \
   }
+  if (trans) { HODLR_MVW(1) } else { HODLR_MVW(0) }
+#undef HODLR_MVW
+#undef HODLR_MVC
 #undef HODLR_MV
   return hipGetLastError();
 }
 template hipError_t launch_matvec_apply<double>(hipStream_t, int, int, int, const int64_t*, const int32_t*, int,
                                                 const double*, int64_t, const double*, int64_t, const double*,
-                                                int64_t, const double*, double*, int64_t, int, int);
+                                                int64_t, const double*, double*, int64_t, int, TileShape);
 template hipError_t launch_matvec_apply<float>(hipStream_t, int, int, int, const int64_t*, const int32_t*, int,
                                                const float*, int64_t, const float*, int64_t, const double*, int64_t,
-                                               const double*, double*, int64_t, int, int);
+                                               const double*, double*, int64_t, int, TileShape);
 
 // ---------------------------------------------------------------------------
 // gradients
 // ---------------------------------------------------------------------------
-// dD_a(i, j) = add(o+i, j) - sum_k Lam(o+i, k) X(o+j, k) (add: FP64, ld ldadd, or null = 0);
-// WG = (leaf, 64-column chunk of the block)
-template <typename S>
-__global__ __launch_bounds__(kMvThreads) void grad_leaf_kernel(const int64_t* __restrict__ leaf_off, int nchunks,
-                                                               int nrhs, const double* __restrict__ X, int64_t ldx,
-                                                               const double* __restrict__ Lam, int64_t ldl,
-                                                               S* __restrict__ dD, int64_t ldd,
-                                                               const double* __restrict__ add, int64_t ldadd) {
+// out(I_leaf, c) = [add(I_leaf, c) -] sum_k Left(I_leaf, k) B_c(k) with, per column c,
+//   LEAF  B_c(k) = X(o + c, k), c < m: the outer products on the leaf block
+//   GEN   B_c(k) = S(c, k) of the sibling of the leaf's ancestor at c's level, c < R;
+//         tri = 1: over the columns k of the levels above c's level only
+//   MIX   k over the columns of c's own level, B_c(k) = M(k, c), M the r x r matrix
+//         of the leaf's ancestor there (Pd at pdoff[l] + node r^2; tri = 1: M^T)
+// Bound by memory for few k (the written columns) and by MFMA for many.  Waves
+// stand WR x WC = 4 over 64-row and 64-column blocks of the leaf's rows and a
+// chunk of columns (WC = 1, 2, 4 for leaves above 128, up to 128 and up to 64
+// rows); a wave past the leaf or the columns ends, its k range is that of
+// its columns, and a lane stores 4 consecutive rows.  N = 131072, leaf 128,
+// R = 240, FP32, one vector: GEN 35 us, LEAF 19 (four row blocks for every leaf and
+// stores of single rows: 249 and 111); N = 32768, leaf 128, 192 columns, FP64: the two
+// GEN (tri), LEAF and the two MIX of a gradient of log|det A| together 331 us
+// (before, with an element-wise MIX: 1504).
+enum LeftMode { kLeftLeaf, kLeftGen, kLeftMix };
+struct LeftArgs {
+  int ncols = 0;  // GEN and MIX: R
+  int nk = 0;     // columns of Left
+  int tri = 0;
+  const double* B = nullptr;  // X, the tree or Pd
+  int64_t ldb = 0;            // of X
+  const int64_t* pdoff = nullptr;
+};
+
+template <typename S, int WC, int MODE>
+__global__ __launch_bounds__(kMvThreads, 2) void left_product_kernel(const int64_t* __restrict__ leaf_off, int L,
+                                                                     const int32_t* __restrict__ rpre, int nchunks,
+                                                                     const double* __restrict__ Left, int64_t ldl,
+                                                                     LeftArgs g, S* __restrict__ out, int64_t ldo,
+                                                                     const double* __restrict__ add, int64_t ldadd) {
+  constexpr int WR = 4 / WC;
+  __shared__ int rs[HODLR_MAX_LEVELS + 1];
   const int leaf = blockIdx.x / nchunks, ch = blockIdx.x % nchunks;
   const int64_t o = leaf_off[leaf];
   const int m = (int)(leaf_off[leaf + 1] - o);
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, li = lane & 15, lq = lane >> 4;
-  const int c0 = ch * 64;
-  if (c0 >= m) return;
-  const int wr0 = 64 * w;
+  const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lq = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wr0 = 64 * (w % WR), c0 = 64 * (WC * ch + w / WR);
+  const int ncols = MODE == kLeftLeaf ? m : g.ncols;
+  if constexpr (MODE != kLeftLeaf) {
+    if (tid <= L) rs[tid] = rpre[tid];
+    __syncthreads();
+  }
+  if (wr0 >= m || c0 >= ncols) return;
+  auto level = [&](int c) {  // of column c: 1 .. L
+    int l = 1;
+    for (int i = 1; i < L; ++i) l += c >= rs[i];
+    return l;
+  };
+  // per column block: the lane's column of B, its stride and range of k
+  const double* bp[4];
+  int klo[4], khi[4], ks[4];
+#pragma unroll
+  for (int cb = 0; cb < 4; ++cb) {
+    const int c = min(c0 + 16 * cb + li, ncols - 1);
+    klo[cb] = 0;
+    khi[cb] = g.nk;
+    if constexpr (MODE == kLeftLeaf) {
+      bp[cb] = g.B + o + c;
+    } else {
+      const int l = level(c), node = leaf >> (L - l);
+      if constexpr (MODE == kLeftGen) {
+        bp[cb] = g.B + tree_slot(l, node ^ 1) * ncols * g.nk + c;
+        ks[cb] = ncols;
+        if (g.tri) khi[cb] = min(g.nk, rs[l - 1]);
+      } else {
+        const int r0 = rs[l - 1], r = rs[l] - r0;
+        klo[cb] = r0;
+        khi[cb] = rs[l];
+        ks[cb] = g.tri ? 1 : r;
+        bp[cb] = g.B + g.pdoff[l] + (int64_t)node * r * r + (int64_t)(c - r0) * (g.tri ? r : 1);
+      }
+    }
+  }
+  // the wave's range of k: levels rise with c
+  const int kbeg = MODE == kLeftMix ? rs[level(c0) - 1] & ~3 : 0;
+  int kend = g.nk;
+  if (MODE == kLeftMix) kend = rs[level(min(c0 + 63, ncols - 1))];
+  if (MODE == kLeftGen && g.tri) kend = min(kend, rs[level(min(c0 + 63, ncols - 1)) - 1]);
   d4 acc[4][4];
 #pragma unroll
   for (int rb = 0; rb < 4; ++rb)
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb) acc[rb][cb] = d4{0, 0, 0, 0};
-  for (int k0 = 0; k0 < nrhs; k0 += 4) {
-    const int kk = k0 + lq;
-    double av[4], bv[4];
+  const double* Lw = Left + o + wr0;
+  auto load = [&](int k0, double (&av)[4], double (&bv)[4]) {
+    const int kk = k0 + lq, kc = min(kk, g.nk - 1);
 #pragma unroll
     for (int rb = 0; rb < 4; ++rb) {
-      const int row = wr0 + 16 * rb + li;
-      av[rb] = (row < m && kk < nrhs) ? -Lam[o + row + (int64_t)kk * ldl] : 0.0;
+      const double v = Lw[min(16 * rb + row4(li), m - 1 - wr0) + (int64_t)kc * ldl];
+      av[rb] = kk < g.nk ? v : 0.0;
     }
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb) {
-      const int col = c0 + 16 * cb + li;
-      bv[cb] = (col < m && kk < nrhs) ? X[o + col + (int64_t)kk * ldx] : 0.0;
+      const bool in = kk >= klo[cb] && kk < khi[cb];
+      bv[cb] = in ? bp[cb][(kk - klo[cb]) * (MODE == kLeftLeaf ? g.ldb : (int64_t)ks[cb])] : 0.0;
     }
+  };
+  double av[4], bv[4];
+  if (kbeg < kend) load(kbeg, av, bv);
+#pragma unroll 1
+  for (int k0 = kbeg; k0 < kend; k0 += 4) {
+    double an[4], bn[4];
+    if (k0 + 4 < kend) load(k0 + 4, an, bn);
 #pragma unroll
     for (int rb = 0; rb < 4; ++rb)
 #pragma unroll
       for (int cb = 0; cb < 4; ++cb) acc[rb][cb] = mma64(av[rb], bv[cb], acc[rb][cb]);
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      av[x] = an[x];
+      bv[x] = bn[x];
+    }
   }
 #pragma unroll
-  for (int rb = 0; rb < 4; ++rb)
+  for (int cb = 0; cb < 4; ++cb) {
+    const int c = c0 + 16 * cb + li;
+    if (c >= ncols) continue;
 #pragma unroll
-    for (int cb = 0; cb < 4; ++cb)
+    for (int rb = 0; rb < 4; ++rb) {
+      const int row = wr0 + 16 * rb + 4 * lq;
+      S* po = out + o + row + (int64_t)c * ldo;
+      if (row + 4 <= m) {
+        double base[4] = {0.0, 0.0, 0.0, 0.0};
+        if (add) load_run(add + o + row + (int64_t)c * ldadd, base);
+        typename Vec<S, 4>::type v;
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int row = wr0 + 16 * rb + crow64(lq, t);
-        const int col = c0 + 16 * cb + li;
-        if (row < m && col < m)
-          dD[o + row + (int64_t)col * ldd] = (S)((add ? add[o + row + (int64_t)col * ldadd] : 0.0) + acc[rb][cb][t]);
+        for (int t = 0; t < 4; ++t) v[t] = (S)(MODE == kLeftMix ? acc[rb][cb][t] : base[t] - acc[rb][cb][t]);
+        *reinterpret_cast<typename Vec<S, 4>::type*>(po) = v;
+      } else {
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+          if (row + t < m) {
+            const double base = add ? add[o + row + t + (int64_t)c * ldadd] : 0.0;
+            po[t] = (S)(MODE == kLeftMix ? acc[rb][cb][t] : base - acc[rb][cb][t]);
+          }
       }
+    }
+  }
+}
+
+template <typename S, int MODE>
+static hipError_t launch_left(hipStream_t s, int nleaf, int m_max, int L, const int64_t* d_leaf_off,
+                              const int32_t* d_rpre, const double* Left, int64_t ldl, const LeftArgs& g, int ncols,
+                              S* out, int64_t ldo, const double* add, int64_t ldadd) {
+  if (nleaf == 0 || ncols == 0) return hipSuccess;
+  if (m_max > 256 || L > HODLR_MAX_LEVELS) return hipErrorInvalidValue;
+#define HODLR_LEFT(WCV)                                                                                             \
+  {                                                                                                                 \
+    const int nchunks = (ncols + 64 * WCV - 1) / (64 * WCV);                                                        \
+    hipLaunchKernelGGL((left_product_kernel<S, WCV, MODE>), dim3((unsigned)(nleaf * nchunks)), dim3(kMvThreads), 0, \
+                       s, d_leaf_off, L, d_rpre, nchunks, Left, ldl, g, out, ldo, add, ldadd);                      \
+  }
+  if (m_max > 128) HODLR_LEFT(1)
+  else if (m_max > 64) HODLR_LEFT(2)
+  else HODLR_LEFT(4)
+#undef HODLR_LEFT
+  return hipGetLastError();
 }
 
 template <typename S>
 hipError_t launch_grad_leaf(hipStream_t s, int nleaf, int m_max, const int64_t* d_leaf_off, int nrhs,
                             const double* X, int64_t ldx, const double* Lam, int64_t ldl, S* dD, int64_t ldd,
                             const double* add, int64_t ldadd) {
-  if (nleaf == 0) return hipSuccess;
-  const int nchunks = (m_max + 63) / 64;
-  hipLaunchKernelGGL(grad_leaf_kernel<S>, dim3((unsigned)(nleaf * nchunks)), dim3(kMvThreads), 0, s, d_leaf_off,
-                     nchunks, nrhs, X, ldx, Lam, ldl, dD, ldd, add, ldadd);
-  return hipGetLastError();
+  LeftArgs g;
+  g.nk = nrhs;
+  g.B = X;
+  g.ldb = ldx;
+  return launch_left<S, kLeftLeaf>(s, nleaf, m_max, 0, d_leaf_off, nullptr, Lam, ldl, g, m_max, dD, ldd, add, ldadd);
 }
 template hipError_t launch_grad_leaf<double>(hipStream_t, int, int, const int64_t*, int, const double*, int64_t,
                                              const double*, int64_t, double*, int64_t, const double*, int64_t);
 template hipError_t launch_grad_leaf<float>(hipStream_t, int, int, const int64_t*, int, const double*, int64_t,
                                             const double*, int64_t, float*, int64_t, const double*, int64_t);
 
-// out(I_leaf, c) = add(I_leaf, c) - sum_j Left(I_leaf, j) * S_l(c)[sib](c, j) for every column c of
-// U_big / V_big (add: FP64 N x R with ld ldadd, or null = 0); the sum runs over j < nrhs, or with
-// tri = 1 over the columns of the levels above c's level only (j < R_{l-1})
 template <typename S>
-__global__ __launch_bounds__(kMvThreads) void grad_gen_kernel(const int64_t* __restrict__ leaf_off, int L,
-                                                              const int32_t* __restrict__ rpre, int R, int nchunks,
-                                                              int nrhs, const double* __restrict__ Left, int64_t ldl,
-                                                              const double* __restrict__ tree,
-                                                              S* __restrict__ out, int64_t ldo,
-                                                              const double* __restrict__ add, int64_t ldadd,
-                                                              int tri) {
-  const int leaf = blockIdx.x / nchunks, ch = blockIdx.x % nchunks;
-  const int64_t o = leaf_off[leaf];
-  const int m = (int)(leaf_off[leaf + 1] - o);
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, li = lane & 15, lq = lane >> 4;
-  const int c0 = ch * 64;
-  const int wr0 = 64 * w;
-  // per column block cb: level, sibling block base
-  const double* sb[4];
-  int cvalid[4], klim[4];
-#pragma unroll
-  for (int cb = 0; cb < 4; ++cb) {
-    const int c = c0 + 16 * cb + li;
-    cvalid[cb] = c < R;
-    int l = 1;
-    while (l < L && c >= rpre[l]) ++l;
-    const int node = leaf >> (L - l);
-    sb[cb] = cvalid[cb] ? tree + tree_slot(l, node ^ 1) * R * nrhs + c : tree;
-    klim[cb] = tri ? min(nrhs, (int)rpre[l - 1]) : nrhs;
-  }
-  d4 acc[4][4];
-#pragma unroll
-  for (int rb = 0; rb < 4; ++rb)
-#pragma unroll
-    for (int cb = 0; cb < 4; ++cb) acc[rb][cb] = d4{0, 0, 0, 0};
-  for (int k0 = 0; k0 < nrhs; k0 += 4) {
-    const int kk = k0 + lq;
-    double av[4], bv[4];
-#pragma unroll
-    for (int rb = 0; rb < 4; ++rb) {
-      const int row = wr0 + 16 * rb + li;
-      av[rb] = (row < m && kk < nrhs) ? -Left[o + row + (int64_t)kk * ldl] : 0.0;
-    }
-#pragma unroll
-    for (int cb = 0; cb < 4; ++cb) bv[cb] = (cvalid[cb] && kk < klim[cb]) ? sb[cb][(int64_t)kk * R] : 0.0;
-#pragma unroll
-    for (int rb = 0; rb < 4; ++rb)
-#pragma unroll
-      for (int cb = 0; cb < 4; ++cb) acc[rb][cb] = mma64(av[rb], bv[cb], acc[rb][cb]);
-  }
-#pragma unroll
-  for (int rb = 0; rb < 4; ++rb)
-#pragma unroll
-    for (int cb = 0; cb < 4; ++cb)
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int row = wr0 + 16 * rb + crow64(lq, t);
-        const int col = c0 + 16 * cb + li;
-        if (row < m && col < R)
-          out[o + row + (int64_t)col * ldo] = (S)((add ? add[o + row + (int64_t)col * ldadd] : 0.0) + acc[rb][cb][t]);
-      }
-}
-
-template <typename S>
-hipError_t launch_grad_gen(hipStream_t s, int nleaf, int L, const int64_t* d_leaf_off, const int32_t* d_rpre, int R,
-                           int nrhs, const double* Left, int64_t ldl, const double* tree, S* out, int64_t ldo,
+hipError_t launch_grad_gen(hipStream_t s, int nleaf, int m_max, int L, const int64_t* d_leaf_off, const int32_t* d_rpre,
+                           int R, int nrhs, const double* Left, int64_t ldl, const double* tree, S* out, int64_t ldo,
                            const double* add, int64_t ldadd, int tri) {
-  if (nleaf == 0 || R == 0) return hipSuccess;
-  const int nchunks = (R + 63) / 64;
-  hipLaunchKernelGGL(grad_gen_kernel<S>, dim3((unsigned)(nleaf * nchunks)), dim3(kMvThreads), 0, s, d_leaf_off, L,
-                     d_rpre, R, nchunks, nrhs, Left, ldl, tree, out, ldo, add, ldadd, tri);
-  return hipGetLastError();
+  LeftArgs g;
+  g.ncols = R;
+  g.nk = nrhs;
+  g.tri = tri;
+  g.B = tree;
+  return launch_left<S, kLeftGen>(s, nleaf, m_max, L, d_leaf_off, d_rpre, Left, ldl, g, R, out, ldo, add, ldadd);
 }
-template hipError_t launch_grad_gen<double>(hipStream_t, int, int, const int64_t*, const int32_t*, int, int,
+template hipError_t launch_grad_gen<double>(hipStream_t, int, int, int, const int64_t*, const int32_t*, int, int,
                                             const double*, int64_t, const double*, double*, int64_t, const double*,
                                             int64_t, int);
-template hipError_t launch_grad_gen<float>(hipStream_t, int, int, const int64_t*, const int32_t*, int, int,
+template hipError_t launch_grad_gen<float>(hipStream_t, int, int, int, const int64_t*, const int32_t*, int, int,
                                            const double*, int64_t, const double*, float*, int64_t, const double*,
                                            int64_t, int);
+
+hipError_t launch_node_mix(hipStream_t s, int64_t n, int nleaf, int m_max, int L, int R, const int64_t* d_leaf_off,
+                           const int32_t* d_rpre, const int64_t* d_pdoff, const double* Pd, int trans,
+                           const double* in, double* out) {
+  LeftArgs g;
+  g.ncols = g.nk = R;
+  g.tri = trans;
+  g.B = Pd;
+  g.pdoff = d_pdoff;
+  return launch_left<double, kLeftMix>(s, nleaf, m_max, L, d_leaf_off, d_rpre, in, n, g, R, out, n, nullptr, 0);
+}
 
 // ---------------------------------------------------------------------------
 // refinement helpers (FP64)

@@ -161,4 +161,16 @@ __device__ __forceinline__ V vzero() {
   return v;
 }
 
+// N consecutive elements at any element alignment.
+template <typename S, int N>
+struct Vec {
+  typedef S type __attribute__((ext_vector_type(N), aligned(sizeof(S))));
+};
+template <typename S, typename T, int N>
+__device__ __forceinline__ void load_run(const S* p, T (&d)[N]) {
+  const typename Vec<S, N>::type v = *reinterpret_cast<const typename Vec<S, N>::type*>(p);
+#pragma unroll
+  for (int t = 0; t < N; ++t) d[t] = (T)v[t];
+}
+
 }  // namespace hodlr
