@@ -915,9 +915,7 @@ hodlr_status matvec_impl(hodlr_factors* F, hipStream_t st, int trans, int nrhs, 
     HL("mv_project", (launch_level_pass<double, double, S>(st, F->ntiles[L], F->d_tiles[L], F->tile_shape[L], const_cast<double*>(X),
                                                            ldx, nrhs, (const double*)nullptr, 0, 0,
                                                            (const double*)nullptr, 0, 0, 0, Vb, ldb, F->R, leaves)));
-    for (int l = L - 1; l >= 1; --l)
-      HL("mv_tree", launch_tree_sum(st, 1 << l, (int64_t)F->R * nrhs, tree + tree_slot(l + 1, 0) * F->R * nrhs,
-                                    tree + tree_slot(l, 0) * F->R * nrhs));
+    HL("mv_tree", launch_tree_sums(st, L, (int64_t)F->R * nrhs, tree));
   }
   HL("mv_apply", (launch_matvec_apply<S>(st, trans, F->nleaf, L, F->d_off, F->d_rpre, F->R,
                                          static_cast<const S*>(F->D), F->ldd, Ua, lda, X, ldx, tree, Yo, ldy, nrhs,
@@ -1366,9 +1364,7 @@ hodlr_status grad_impl(hodlr_factors* F, Workspace& Wk, hipStream_t st, int64_t 
       HL("grad_project", (launch_level_pass<double, double, float>(
                              st, F->ntiles[L], F->d_tiles[L], F->tile_shape[L], const_cast<double*>(Xin), ldxin, n, (const double*)nullptr,
                              0, 0, (const double*)nullptr, 0, 0, 0, static_cast<const float*>(Mv), ldm, F->R, leaves)));
-    for (int l = L - 1; l >= 1; --l)
-      HL("grad_tree", launch_tree_sum(st, 1 << l, (int64_t)F->R * n, tree + tree_slot(l + 1, 0) * F->R * n,
-                                      tree + tree_slot(l, 0) * F->R * n));
+    HL("grad_tree", launch_tree_sums(st, L, (int64_t)F->R * n, tree));
     return HODLR_OK;
   };
   if ((s = project(F->V, F->ldv, X, ldx, Wk.tree))) return s;     // V^T X node sums
@@ -1574,9 +1570,7 @@ hodlr_status logdet_grad_impl(hodlr_factors* F, hipStream_t st, DevMem& M, void*
                                                             const_cast<double*>(Xin), N, R, (const double*)nullptr, 0,
                                                             0, (const double*)nullptr, 0, 0, 0,
                                                             static_cast<const S*>(Mv), ldm, R, leaves)));
-    for (int l = L - 1; l >= 1; --l)
-      HL("logdet_grad", launch_tree_sum(st, 1 << l, (int64_t)R * R, tree + tree_slot(l + 1, 0) * (int64_t)R * R,
-                                        tree + tree_slot(l, 0) * (int64_t)R * R));
+    HL("logdet_grad", launch_tree_sums(st, L, (int64_t)R * R, tree));
     return HODLR_OK;
   };
   if ((s = project(F->V, F->ldv, Y64, tV))) return s;

@@ -150,8 +150,8 @@ template <typename T>
 hipError_t launch_couple_solve(hipStream_t s, int trans, int nparents, int r, int kp, int nrhs, const T* segs,
                                const int32_t* d_seg_start, const T* Kinv, const T* Kt, T* w);
 
-// Pairwise tree sum out[i] = in[2i] + in[2i+1] (blocks of elems doubles).
-hipError_t launch_tree_sum(hipStream_t s, int nnodes, int64_t elems, const double* in, double* out);
+// Pairwise sums up the projection tree (below) from level L to level 1 (blocks of elems doubles).
+hipError_t launch_tree_sums(hipStream_t s, int L, int64_t elems, double* tree);
 
 // Projection tree: for l = 1..L, the 2^l node sums (R x nrhs each, col-major ld R) of level l
 // start at node slot (2^l - 2); slot k begins at tree + k * R * nrhs.

@@ -25,18 +25,46 @@ __device__ __forceinline__ d4 mma64(double a, double b, d4 c) {
 // four consecutive rows of a lane's column
 __device__ __forceinline__ int row4(int li) { return 4 * (li & 3) + (li >> 2); }
 
-// pairwise tree sum: out[i] = in[2i] + in[2i+1], blocks of `elems`
-__global__ void tree_sum_kernel(int nnodes, int64_t elems, const double* __restrict__ in, double* __restrict__ out) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int i = blockIdx.y;
-  if (e >= elems || i >= nnodes) return;
-  out[(int64_t)i * elems + e] = in[(int64_t)(2 * i) * elems + e] + in[(int64_t)(2 * i + 1) * elems + e];
+// Sums over the projection tree: node i of level l = nodes 2 i + node 2 i + 1 of
+// level l + 1, blocks of `elems`.  One launch forms up to three levels: a thread
+// takes one element of the 2^DEPTH blocks below one node and keeps the sums in
+// between, so these are not read again and a tree of 10 levels takes 3 launches
+// (one a level: 9; N = 131072, R = 240, one vector: 56 us, now 10; N = 524288, R = 704,
+// 32 vectors: 225, now 132).
+template <int DEPTH>
+__global__ __launch_bounds__(256) void tree_sum_kernel(int l, int nblk, int64_t elems, double* __restrict__ tree) {
+  const int64_t e = (int64_t)(blockIdx.x % nblk) * 256 + threadIdx.x;
+  const int i = blockIdx.x / nblk;  // node of level l - DEPTH, from the blocks of level l
+  if (e >= elems) return;
+  double v[1 << DEPTH];
+#pragma unroll
+  for (int k = 0; k < 1 << DEPTH; ++k) v[k] = tree[(tree_slot(l, (i << DEPTH) + k)) * elems + e];
+#pragma unroll
+  for (int d = DEPTH - 1; d >= 0; --d) {
+#pragma unroll
+    for (int k = 0; k < 1 << d; ++k) {
+      v[k] = v[2 * k] + v[2 * k + 1];
+      tree[tree_slot(l - DEPTH + d, (i << d) + k) * elems + e] = v[k];
+    }
+  }
 }
 
-hipError_t launch_tree_sum(hipStream_t s, int nnodes, int64_t elems, const double* in, double* out) {
-  if (nnodes == 0 || elems == 0) return hipSuccess;
-  dim3 grid((unsigned)((elems + 255) / 256), (unsigned)nnodes);
-  hipLaunchKernelGGL(tree_sum_kernel, grid, dim3(256), 0, s, nnodes, elems, in, out);
+hipError_t launch_tree_sums(hipStream_t s, int L, int64_t elems, double* tree) {
+  if (elems == 0) return hipSuccess;
+  const int64_t nblk = (elems + 255) / 256;
+  for (int l = L; l > 1;) {
+    const int depth = std::min(l - 1, 3);
+    const int64_t wgs = nblk << (l - depth);
+    if (wgs > 0x7fffffff) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)wgs);
+    if (depth == 3)
+      hipLaunchKernelGGL(tree_sum_kernel<3>, grid, dim3(256), 0, s, l, (int)nblk, elems, tree);
+    else if (depth == 2)
+      hipLaunchKernelGGL(tree_sum_kernel<2>, grid, dim3(256), 0, s, l, (int)nblk, elems, tree);
+    else
+      hipLaunchKernelGGL(tree_sum_kernel<1>, grid, dim3(256), 0, s, l, (int)nblk, elems, tree);
+    l -= depth;
+  }
   return hipGetLastError();
 }
 
@@ -450,25 +478,32 @@ __global__ void colnorm_partial_kernel(int64_t n, const double* __restrict__ X, 
     part[((int64_t)j * gridDim.x + blockIdx.x) * 2 + 1] = si[0];
   }
 }
-__global__ void colnorm_final_kernel(int nblk, int nrhs, const double* __restrict__ part, double* __restrict__ out2,
-                                     double* __restrict__ outinf) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= nrhs) return;
+// one wave per column: its lanes load the partials (all in flight), then halve
+// (a thread a column, walking them: a norm of 131072 rows took 33 us, now 11)
+__global__ __launch_bounds__(64) void colnorm_final_kernel(int nblk, const double* __restrict__ part,
+                                                           double* __restrict__ out2, double* __restrict__ outinf) {
+  const int j = blockIdx.x;
   double a2 = 0.0, ai = 0.0;
-  for (int b = 0; b < nblk; ++b) {
+  for (int b = threadIdx.x; b < nblk; b += 64) {
     a2 += part[((int64_t)j * nblk + b) * 2];
     ai = fmax(ai, part[((int64_t)j * nblk + b) * 2 + 1]);
   }
-  out2[j] = sqrt(a2);
-  outinf[j] = ai;
+#pragma unroll
+  for (int h = 32; h > 0; h >>= 1) {
+    a2 += __shfl_down(a2, h);
+    ai = fmax(ai, __shfl_down(ai, h));
+  }
+  if (threadIdx.x == 0) {
+    out2[j] = sqrt(a2);
+    outinf[j] = ai;
+  }
 }
 
 hipError_t launch_colnorms(hipStream_t s, int64_t n, int nrhs, const double* X, int64_t ldx, double* part,
                            double* out2, double* outinf) {
   if (nrhs == 0) return hipSuccess;
   hipLaunchKernelGGL(colnorm_partial_kernel, dim3(kNormBlocks, nrhs), dim3(256), 0, s, n, X, ldx, part);
-  hipLaunchKernelGGL(colnorm_final_kernel, dim3((nrhs + 63) / 64), dim3(64), 0, s, kNormBlocks, nrhs, part, out2,
-                     outinf);
+  hipLaunchKernelGGL(colnorm_final_kernel, dim3(nrhs), dim3(64), 0, s, kNormBlocks, part, out2, outinf);
   return hipGetLastError();
 }
 
