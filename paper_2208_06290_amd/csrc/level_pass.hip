@@ -83,8 +83,13 @@ struct CoupleArgs {
   const int32_t* start = nullptr;
 };
 
-template <typename TZ, typename SA, typename SB, int WC, int NCB, bool FULL, bool BF, int CPL = 0>
-__global__ __launch_bounds__(kLpThreads, (lp_occupancy<TZ, NCB, FULL>())) void level_pass_rows_kernel(
+//
+// NT: threads; one column block (narrow Z) on tiles up to 128 or 64 rows takes
+// two waves or one, as waves without rows would only hold places of the CU.
+// Products of N = 131072 rows in tiles of 128 with 240 FP32 columns, one
+// vector: 43 us (four waves: 57).
+template <typename TZ, typename SA, typename SB, int WC, int NCB, bool FULL, bool BF, int CPL = 0, int NT = kLpThreads>
+__global__ __launch_bounds__(NT, (lp_occupancy<TZ, NCB, FULL>())) void level_pass_rows_kernel(
     const Tile* __restrict__ tiles, int zchunks, int c_base, int bchunks, int kbc, TZ* Z, int64_t ldz, int nz,
     const SA* A1, int64_t lda, int ka, const TZ* __restrict__ W, int64_t w_ld, int64_t w_pstride, int node_shift,
     const SB* __restrict__ B1, int64_t ldb, int kb_total, TZ* __restrict__ P, GroupStrides gs, int red_off,
@@ -92,7 +97,7 @@ __global__ __launch_bounds__(kLpThreads, (lp_occupancy<TZ, NCB, FULL>())) void l
   static_assert(CPL == 0 || (WC == 1 && NCB == 1 && !BF), "the fused coupling solve is for one narrow chunk");
   using M = Mfma<TZ>;
   using V = typename M::V;
-  constexpr int WR = 4 / WC;
+  constexpr int WR = NT / 64 / WC;
   constexpr int kCw = 16 * NCB * WC;  // columns of a chunk
   constexpr int kWc = 16 * NCB;       // columns of a wave
   constexpr int RP = kRp<TZ>, kGr = 16 * RP, NG = 4 / RP;  // rows of a group, groups of a wave
@@ -137,7 +142,7 @@ __global__ __launch_bounds__(kLpThreads, (lp_occupancy<TZ, NCB, FULL>())) void l
       }
     // the children's product sums as B fragments: group q, lane, 4 rows
     TZ* Ts = reinterpret_cast<TZ*>(smem_raw) + (red_off / sizeof(TZ)) * 2;
-    for (int e = tid; e < 2 * nt * 64; e += kLpThreads) {
+    for (int e = tid; e < 2 * nt * 64; e += NT) {
       const int q = e >> 6, h = q >= nt, c = e & 15, i0 = 16 * (h ? q - nt : q) + 4 * ((e >> 4) & 3);
       TZ sum[4] = {TZ(0), TZ(0), TZ(0), TZ(0)};
       if (c < nz && i0 < r) {
@@ -180,7 +185,7 @@ __global__ __launch_bounds__(kLpThreads, (lp_occupancy<TZ, NCB, FULL>())) void l
   } else if (ka > 0) {
     const int nd = tl.node >> node_shift;
     const TZ* Wn = W + (int64_t)(nd >> 1) * w_pstride + (int64_t)(nd & 1) * ka;
-    for (int e = tid; e < ng * 4 * kCw; e += kLpThreads) {
+    for (int e = tid; e < ng * 4 * kCw; e += NT) {
       const int q = e & 3, c = (e >> 2) % kCw, g = e / (4 * kCw);
       const int k = 16 * g + 4 * q;
       const TZ* src = Wn + (int64_t)min(c0 + c, nz - 1) * w_ld;
@@ -404,10 +409,10 @@ __global__ __launch_bounds__(kLpThreads, (lp_occupancy<TZ, NCB, FULL>())) void l
           for (int t = 0; t < 4; ++t) rd[(wr * 16 + M::crow(lq, t)) * kCw + kWc * wc + 16 * cb + li] = pacc[cb][t];
         __syncthreads();
 #pragma unroll
-        for (int u = 0; u < (16 * kCw + kLpThreads - 1) / kLpThreads; ++u) {
-          const int e = tid + u * kLpThreads;
+        for (int u = 0; u < (16 * kCw + NT - 1) / NT; ++u) {
+          const int e = tid + u * NT;
           const int kr = kr0 + (e & 15), c = e >> 4;
-          if ((16 * kCw % kLpThreads == 0 || e < 16 * kCw) && kr < k1 && c0 + c < nz) {
+          if ((16 * kCw % NT == 0 || e < 16 * kCw) && kr < k1 && c0 + c < nz) {
             TZ sum = rd[(e & 15) * kCw + c];
 #pragma unroll
             for (int x = 1; x < WR; ++x) sum += rd[(x * 16 + (e & 15)) * kCw + c];
@@ -641,21 +646,21 @@ __global__ __launch_bounds__(kLpThreads, (MB > 2 || NKS > 8) ? 2 : 3) void level
 }
 
 
-template <typename TZ, typename SA, typename SB, int WC, int NCB, bool FULL, bool BF>
+template <typename TZ, typename SA, typename SB, int WC, int NCB, bool FULL, bool BF, int NT = kLpThreads>
 static hipError_t launch_rows_part(hipStream_t s, int ntiles, int zchunks, int c_base, int bchunks, int kbc,
                                    const Tile* tiles, TZ* Z, int64_t ldz, int nz, const SA* A1, int64_t lda, int ka,
                                    const TZ* W, int64_t w_ld, int64_t w_pstride, int node_shift, const SB* B1,
                                    int64_t ldb, int kb, TZ* P, GroupStrides gs) {
   if (zchunks == 0) return hipSuccess;
-  constexpr int WR = 4 / WC, kCw = 16 * NCB * WC;
+  constexpr int WR = NT / 64 / WC, kCw = 16 * NCB * WC;
   const size_t red = kb > 0 ? sizeof(TZ) * WR * 16 * kCw : 0;
   const size_t wsz = std::max(red, (BF ? 2 : sizeof(TZ)) * (size_t)kCw * ((ka + 15) & ~15));
   const int64_t grid = (int64_t)ntiles * zchunks * bchunks;
   if (grid > 0x7fffffff) return hipErrorInvalidValue;
-  auto k = level_pass_rows_kernel<TZ, SA, SB, WC, NCB, FULL, BF>;
+  auto k = level_pass_rows_kernel<TZ, SA, SB, WC, NCB, FULL, BF, 0, NT>;
   hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(wsz + red));
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(kLpThreads), wsz + red, s, tiles, zchunks, c_base, bchunks, kbc, Z,
+  hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(NT), wsz + red, s, tiles, zchunks, c_base, bchunks, kbc, Z,
                      ldz, nz, A1, lda, ka, W, w_ld, w_pstride, node_shift, B1, ldb, kb, P, gs, (int)wsz, CoupleArgs<TZ>());
   return hipGetLastError();
 }
@@ -708,8 +713,23 @@ static hipError_t launch_rows(hipStream_t s, int ntiles, int c_base, const Tile*
                                                                       kb, P, gs)
   // waves over columns only where every one of them has 16 columns of its own
   // (a projection of one vector on 128-row tiles: 333 us with two waves on the
-  // same 16 columns, 231 us with those two idle)
+  // same 16 columns, 231 us without)
   const int cols = nz - c_base;
+  if constexpr (!BF) {
+    if (cols <= 16 && sh.rows <= 128) {  // no more waves than rows
+      const int kbc = ka > 0 ? std::max(kb, 1) : 64, bchunks = kb > 0 ? (kb + kbc - 1) / kbc : 1;
+#define HODLR_LPN(FULLV, NTV)                                                                                        \
+  return launch_rows_part<TZ, SA, SB, 1, 1, FULLV, BF, NTV>(s, ntiles, 1, c_base, bchunks, kbc, tiles, Z, ldz, nz, A1, \
+                                                            lda, ka, W, w_ld, w_pstride, node_shift, B1, ldb, kb, P, gs)
+      if (sh.rows <= 64) {
+        if (sh.mult(64)) HODLR_LPN(true, 64);
+        HODLR_LPN(false, 64);
+      }
+      if (sh.mult(64)) HODLR_LPN(true, 128);
+      HODLR_LPN(false, 128);
+#undef HODLR_LPN
+    }
+  }
   if (sh.rows <= 64 && cols > 32) HODLR_LPS(4);
   if (sh.rows <= 128 && cols > 16) HODLR_LPS(2);
   HODLR_LPS(1);
