@@ -33,7 +33,9 @@ constexpr int trsm_occupancy() {
 // applies it to its blocks; the factor operands and the next owner's inverted
 // diagonal block are fetched before the barrier.  The products run transposed
 // (X^T = B^T M^{-T}) so that accumulator rows are matrix rows on the lanes:
-// every global load and store covers whole 128-byte lines.  Leaf blocks take
+// every global load and store covers whole 128-byte lines; transposed factors come
+// in runs of four rows a lane (N = 2^18, leaf 128, FP64, 32 columns: 137 us, by
+// elements 182; N = 2^17, FP32, one: 33 and 86).  Leaf blocks take
 // 32-column chunks with 128 registers per lane (four workgroups per CU: the
 // steps are short and latency-bound, so more resident workgroups pay more than
 // wider chunks).
@@ -120,6 +122,8 @@ __global__ __launch_bounds__(64 * NW, (trsm_occupancy<T, NW, NQ, NCB>())) void t
       for (int t = 0; t < 4; ++t) xb[li * kCwT + 16 * cb + M::crow(lq, t)] = nv[t];
     }
   };
+  // rows of block k that K-step ks takes: transposed factors are read in runs of 4 rows
+  auto krow = [&](int ks) { return TRANS ? 4 * lq + ks : 4 * ks + lq; };
   // B_b^T -= X_k^T M_bk^T on accumulator block q2
   auto update = [&](int q2, const T (&av)[NQ][4], const T* xb) {
     if constexpr (BF) {
@@ -127,7 +131,7 @@ __global__ __launch_bounds__(64 * NW, (trsm_occupancy<T, NW, NQ, NCB>())) void t
       for (int cb = 0; cb < NCB; ++cb) {
         T xv[4];
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) xv[ks] = xb[(4 * ks + lq) * kCwT + 16 * cb + li];
+        for (int ks = 0; ks < 4; ++ks) xv[ks] = xb[krow(ks) * kCwT + 16 * cb + li];
         acc[q2][cb] = Mma16<T, true>::mma(xv, av[q2], acc[q2][cb]);
       }
     } else {
@@ -135,7 +139,7 @@ __global__ __launch_bounds__(64 * NW, (trsm_occupancy<T, NW, NQ, NCB>())) void t
       for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb)
-          acc[q2][cb] = M::mma(xb[(4 * ks + lq) * kCwT + 16 * cb + li], av[q2][ks], acc[q2][cb]);
+          acc[q2][cb] = M::mma(xb[krow(ks) * kCwT + 16 * cb + li], av[q2][ks], acc[q2][cb]);
     }
   };
 
@@ -159,7 +163,7 @@ __global__ __launch_bounds__(64 * NW, (trsm_occupancy<T, NW, NQ, NCB>())) void t
           load_inv(sweep, k, iv0);
           owner(q, iv0, xb);
         }
-        // the factor operands M(16 b + li, 16 k + 4 ks + lq) of this wave's blocks
+        // the factor operands M(16 b + li, 16 k + krow(ks)) of this wave's blocks
         // on the far side of k do not depend on X_k: fetched before the barrier
         // (clamped in range, no branches)
         T av[NQ][4];
@@ -167,11 +171,10 @@ __global__ __launch_bounds__(64 * NW, (trsm_occupancy<T, NW, NQ, NCB>())) void t
         for (int q2 = 0; q2 < NQ; ++q2) {
           if (sweep == 0 ? q2 < q : q2 > q) continue;  // never on the far side: compile time
           const int b = min(NW * q2 + w, nbk - 1);
+          const int i = 16 * b + li;
+          if constexpr (TRANS) load_run(F + 16 * k + 4 * lq + (int64_t)i * lul, av[q2]);
 #pragma unroll
-          for (int ks = 0; ks < 4; ++ks) {
-            const int i = 16 * b + li, j = 16 * k + 4 * ks + lq;
-            av[q2][ks] = -(TRANS ? F[j + (int64_t)i * lul] : F[i + (int64_t)j * lul]);
-          }
+          for (int ks = 0; ks < 4; ++ks) av[q2][ks] = -(TRANS ? av[q2][ks] : F[i + (int64_t)(16 * k + 4 * ks + lq) * lul]);
         }
         // look-ahead: the wave owning the next block updates it first and forms
         // X_next at once, so the next step starts without waiting for it
@@ -228,14 +231,6 @@ __global__ __launch_bounds__(64 * NW, (trsm_occupancy<T, NW, NQ, NCB>())) void t
 // per step.  Each step still waits for that barrier, which more resident
 // workgroups cover: 64 columns and three workgroups per CU in FP64.
 constexpr int kTwThreads = 256;
-
-template <typename S, typename T>
-__device__ __forceinline__ void load_run4(const S* p, T (&d)[4]) {
-  typedef S V4 __attribute__((ext_vector_type(4), aligned(sizeof(S))));
-  const V4 v = *reinterpret_cast<const V4*>(p);
-#pragma unroll
-  for (int t = 0; t < 4; ++t) d[t] = (T)v[t];
-}
 
 template <typename T, typename S, int TRANS, int NB, int NC, bool BF>
 __global__ __launch_bounds__(kTwThreads, (NB * NC * (int)sizeof(T) <= 64 ? 3 : 2)) void trsm_wide_kernel(int ldl, const int64_t* __restrict__ leaf_off, const T* lu,
@@ -310,7 +305,7 @@ __global__ __launch_bounds__(kTwThreads, (NB * NC * (int)sizeof(T) <= 64 ? 3 : 2
 #pragma unroll
       for (int n = 0; n < NC; ++n) {
         T x[4];
-        load_run4(Bb + src[0] + cb[n] * ldb, x);
+        load_run(Bb + src[0] + cb[n] * ldb, x);
 #pragma unroll
         for (int t = 0; t < 4; ++t) acc[b][n][t] = x[t];
       }
@@ -443,7 +438,7 @@ hipError_t launch_leaf_trsm(hipStream_t s, int trans, int nleaf, int ldl, const 
   // rows, FP64, 340 columns: 483 against 405).  With 256 rows the accumulators
   // leave two workgroups per CU and the barriers are in the open (FP64, 384
   // columns: 5.4 against 7.2 ms), and few columns leave waves without any (32
-  // adjoint columns on leaf 128: 181 against 217 us).
+  // adjoint columns on leaf 128: 137 against 217 us).
   const bool wide = ldl <= 128 && ncols > 64;
   // blocks of at most 64 rows: one 16-row block per wave; else four blocks per
   // wave and 32 columns
