@@ -473,7 +473,11 @@ def construct_bench(hodlr, W, cfg, N, leaf_offsets, ranks, steps, dev, cpu=True)
     kt = hodlr.kernel_times()
     hodlr.timing(False)
     del A
-    leaves_b, steps_b = construct_model(N, ranks, m_max, dim, kind == "laplace_dl", 8 if dtype == torch.float64 else 4)
+    # the tiled steps cover blocks above 512 rows or rank 32 (smaller ones are one workgroup's, "aca_block")
+    off = [int(x) for x in leaf_offsets]
+    tall = [max(off[(a + 1) << (L - l)] - off[a << (L - l)] for a in range(1 << l)) > 512 for l in range(1, L + 1)]
+    tiled = [r for r, t in zip(ranks, tall) if t or r > 32]
+    leaves_b, steps_b = construct_model(N, tiled, m_max, dim, kind == "laplace_dl", 8 if dtype == torch.float64 else 4)
     aca_ms = kt.get("aca_step", (float("nan"), 0))[0]
     nsteps = kt.get("aca_step", (0, 0))[1]
     achieved = steps_b / (aca_ms * 1e-3)

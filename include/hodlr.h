@@ -170,7 +170,8 @@ typedef struct {
 
 /* Factorization (Section III-B Alg. "a:fact" / Section III-C Alg. "a:gpuf"):
  * batched LU with partial pivoting of every leaf, Y_big = D^{-1} U_big on all
- * columns, then for l = L-1 .. 0: the coupling products V^T Y, the LU of
+ * columns, then for l = L-1 .. 0: the coupling products V^T Y, the inversion
+ * (Gauss-Jordan with partial pivoting) of
  * K_g = [[V_a^T Y_a, I], [I, V_b^T Y_b]] (eq. "e:k") and the update of
  * Y_big(:, 1:R_l) (eqs. "e:node1", "e:node2").
  *   A        the matrix (see hodlr_matrix)
