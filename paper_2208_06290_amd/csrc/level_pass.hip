@@ -441,7 +441,7 @@ __global__ __launch_bounds__(NT, (lp_occupancy<TZ, NCB, FULL>())) void level_pas
 // blocks (the product's sum over rows does not depend on their order).
 constexpr int kZtLd = 17;  // padded row length of the per-wave 16 x 16 turn-around buffer
 
-template <typename TZ, typename SA, typename SB, int MB, int NKS, int NCB, int RP>
+template <typename TZ, typename SA, typename SB, int MB, int NKS, int NCB, int RP, bool BF = false>
 __global__ __launch_bounds__(kLpThreads, (MB > 2 || NKS > 8) ? 2 : 3) void level_pass_block_kernel(
     const Tile* __restrict__ tiles, int zchunks, int c_base, int bchunks, TZ* Z, int64_t ldz, int nz, const SA* __restrict__ A1,
     int64_t lda, const TZ* __restrict__ W, int64_t w_ld, int64_t w_pstride, int node_shift,
@@ -478,7 +478,14 @@ __global__ __launch_bounds__(kLpThreads, (MB > 2 || NKS > 8) ? 2 : 3) void level
     const TZ* Wn = W + (int64_t)(nd >> 1) * w_pstride + (int64_t)(nd & 1) * ka;
     for (int e = tid; e < kCw * ka; e += kLpThreads) {
       const int c = e % kCw, k = e / kCw;
-      Ws[e] = Wn[k + (int64_t)(c0 + c) * w_ld];
+      const TZ v = Wn[k + (int64_t)(c0 + c) * w_ld];
+      // BF: as the update's packed A operands, element (k, c) to group k / 16, block
+      // c / 16, lane (k % 4, c % 16), slot (k / 4) % 4
+      if constexpr (BF)
+        reinterpret_cast<__bf16*>(Ws)[((((k >> 4) * NCB + (c >> 4)) * 4 + (k & 3)) * 16 + (c & 15)) * 4 +
+                                      ((k >> 2) & 3)] = (__bf16)v;
+      else
+        Ws[e] = v;
     }
   }
 
@@ -546,11 +553,24 @@ __global__ __launch_bounds__(kLpThreads, (MB > 2 || NKS > 8) ? 2 : 3) void level
 
   // update of one 16-row MFMA block, and its contribution to the product
   auto update = [&](V (&acc)[NCB], const TZ (&acur)[NKS > 0 ? NKS : 1]) {
+    if constexpr (BF) {  // four K-steps as one MFMA (NKS is a multiple of 4)
+      const s4* Wp = reinterpret_cast<const s4*>(Ws);
 #pragma unroll
-    for (int ks = 0; ks < NKS; ++ks)
+      for (int g = 0; g < NKS / 4; ++g) {
+        TZ av[4];
 #pragma unroll
-      for (int cb = 0; cb < NCB; ++cb)
-        acc[cb] = M::mma(Ws[(4 * ks + lq) * kCw + 16 * cb + li], acur[ks], acc[cb]);
+        for (int j = 0; j < 4; ++j) av[j] = acur[4 * g + j];
+        const s4 ap = pack_bf16(av);
+#pragma unroll
+        for (int cb = 0; cb < NCB; ++cb) acc[cb] = mma_bf16(Wp[((g * NCB + cb) * 4 + lq) * 16 + li], ap, acc[cb]);
+      }
+    } else {
+#pragma unroll
+      for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+        for (int cb = 0; cb < NCB; ++cb)
+          acc[cb] = M::mma(Ws[(4 * ks + lq) * kCw + 16 * cb + li], acur[ks], acc[cb]);
+    }
   };
   auto stage_b = [&](const TZ (&bcur)[MB > 0 ? 4 * MB : 1]) {
 #pragma unroll
@@ -564,15 +584,32 @@ __global__ __launch_bounds__(kLpThreads, (MB > 2 || NKS > 8) ? 2 : 3) void level
     for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb) bv[kk][mb] = bt[(4 * kk + lq) * kBtLd + 16 * mb + li];
+    s4 bp[BF && MB > 0 ? MB : 1];  // bfloat16: packed once for every Z block
+    if constexpr (BF) {
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) {
+        TZ v[4];
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) v[kk] = bv[kk][mb];
+        bp[mb] = pack_bf16(v);
+      }
+    }
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) {
 #pragma unroll
       for (int t = 0; t < 4; ++t) zt[li * kZtLd + M::crow(lq, t)] = acc[cb][t];
+      TZ zv[4];
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        const TZ zv = zt[(4 * kk + lq) * kZtLd + li];
+      for (int kk = 0; kk < 4; ++kk) zv[kk] = zt[(4 * kk + lq) * kZtLd + li];
+      if constexpr (BF) {
+        const s4 zp = pack_bf16(zv);
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb) pacc[mb][cb] = M::mma(bv[kk][mb], zv, pacc[mb][cb]);
+        for (int mb = 0; mb < MB; ++mb) pacc[mb][cb] = mma_bf16(bp[mb], zp, pacc[mb][cb]);
+      } else {
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+          for (int mb = 0; mb < MB; ++mb) pacc[mb][cb] = M::mma(bv[kk][mb], zv[kk], pacc[mb][cb]);
       }
     }
   };
@@ -736,7 +773,7 @@ static hipError_t launch_rows(hipStream_t s, int ntiles, int c_base, const Tile*
 #undef HODLR_LPS
 }
 
-template <typename TZ, typename SA, typename SB, int MB, int NKS, int NCB, int RP>
+template <typename TZ, typename SA, typename SB, int MB, int NKS, int NCB, int RP, bool BF>
 static hipError_t launch_block_part(hipStream_t s, int ntiles, int zchunks, int c_base, int nz, int bchunks,
                                     const Tile* tiles, TZ* Z, int64_t ldz, const SA* A1, int64_t lda, const TZ* W,
                                     int64_t w_ld, int64_t w_pstride, int node_shift, const SB* B1, int64_t ldb, int kb,
@@ -748,7 +785,7 @@ static hipError_t launch_block_part(hipStream_t s, int ntiles, int zchunks, int 
   const size_t smem = smem_main > smem_red ? smem_main : smem_red;
   const int64_t grid = (int64_t)ntiles * zchunks * bchunks;
   if (grid > 0x7fffffff) return hipErrorInvalidValue;
-  auto k = level_pass_block_kernel<TZ, SA, SB, MB, NKS, NCB, RP>;
+  auto k = level_pass_block_kernel<TZ, SA, SB, MB, NKS, NCB, RP, BF>;
   hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(kLpThreads), smem, s, tiles, zchunks, c_base, bchunks, Z, ldz, nz,
@@ -758,17 +795,18 @@ static hipError_t launch_block_part(hipStream_t s, int ntiles, int zchunks, int 
 
 // The first nblk 16-column blocks of Z: chunks of 64 columns, then the blocks
 // that are left as one narrower chunk.
-template <typename TZ, typename SA, typename SB, int MB, int NKS, int RP>
+template <typename TZ, typename SA, typename SB, int MB, int NKS, int RP, bool BF = false>
 static hipError_t launch_block_chunks(hipStream_t s, int ntiles, int nblk, int nz, int bchunks, const Tile* tiles,
                                       TZ* Z, int64_t ldz, const SA* A1, int64_t lda, const TZ* W, int64_t w_ld,
                                       int64_t w_pstride, int node_shift, const SB* B1, int64_t ldb, int kb, TZ* P,
                                       GroupStrides gs) {
   const int n64 = nblk / 4, nb = nblk % 4;
-  hipError_t e = launch_block_part<TZ, SA, SB, MB, NKS, 4, RP>(s, ntiles, n64, 0, nz, bchunks, tiles, Z, ldz, A1, lda,
-                                                               W, w_ld, w_pstride, node_shift, B1, ldb, kb, P, gs);
+  hipError_t e = launch_block_part<TZ, SA, SB, MB, NKS, 4, RP, BF>(s, ntiles, n64, 0, nz, bchunks, tiles, Z, ldz, A1,
+                                                                   lda, W, w_ld, w_pstride, node_shift, B1, ldb, kb, P,
+                                                                   gs);
   if (e != hipSuccess) return e;
 #define HODLR_LPB(NCBV)                                                                                            \
-  return launch_block_part<TZ, SA, SB, MB, NKS, NCBV, RP>(s, ntiles, 1, 64 * n64, nz, bchunks, tiles, Z, ldz, A1,   \
+  return launch_block_part<TZ, SA, SB, MB, NKS, NCBV, RP, BF>(s, ntiles, 1, 64 * n64, nz, bchunks, tiles, Z, ldz, A1,   \
                                                           lda, W, w_ld, w_pstride, node_shift, B1, ldb, kb, P, gs)
   if (nb == 1) HODLR_LPB(1);
   if (nb == 2) HODLR_LPB(2);
@@ -813,6 +851,25 @@ static hipError_t launch_block(hipStream_t s, int ntiles, const Tile* tiles, TZ*
 #undef HODLR_LPM
 }
 
+// bfloat16 operands, ka and kb of 0, 16 or 32
+template <typename TZ, typename SA, typename SB>
+static hipError_t launch_block_bf(hipStream_t s, int ntiles, const Tile* tiles, TZ* Z, int64_t ldz, int nblk, int nz,
+                                  const SA* A1, int64_t lda, int ka, const TZ* W, int64_t w_ld, int64_t w_pstride,
+                                  int node_shift, const SB* B1, int64_t ldb, int kb, TZ* P, GroupStrides gs) {
+#define HODLR_LPX(MBV, NKSV)                                                                                       \
+  return launch_block_chunks<TZ, SA, SB, MBV, NKSV, 2, true>(s, ntiles, nblk, nz, 1, tiles, Z, ldz, A1, lda, W, w_ld, \
+                                                             w_pstride, node_shift, B1, ldb, kb, P, gs)
+#define HODLR_LPY(MBV)               \
+  if (ka == 0) HODLR_LPX(MBV, 0);    \
+  if (ka == 16) HODLR_LPX(MBV, 4);   \
+  HODLR_LPX(MBV, 8)
+  if (kb == 0) { HODLR_LPY(0); }
+  if (kb == 16) { HODLR_LPY(1); }
+  HODLR_LPY(2);
+#undef HODLR_LPY
+#undef HODLR_LPX
+}
+
 template <typename TZ, typename SA, typename SB>
 hipError_t launch_level_pass(hipStream_t s, int ntiles, const Tile* tiles, TileShape sh, TZ* Z, int64_t ldz, int nz,
                              const SA* A1, int64_t lda, int ka, const TZ* W, int64_t w_ld, int64_t w_pstride,
@@ -825,15 +882,30 @@ hipError_t launch_level_pass(hipStream_t s, int ntiles, const Tile* tiles, TileS
                       64 * lda * (int64_t)sizeof(SA) < (1ll << 31) && 64 * ldb * (int64_t)sizeof(SB) < (1ll << 31);
   int c_base = 0;
   if (blocks) {
+    // 4-byte elements, tile heights multiples of 32, even leading dimensions
+    // and 16-byte aligned operands (every paired access is naturally
+    // aligned): two rows per lane
+    auto al16 = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
+    const bool pair = sizeof(TZ) == 4 && sh.mult(32) && ldz % 2 == 0 && (ka == 0 || lda % 2 == 0) &&
+                      (kb == 0 || ldb % 2 == 0) && al16(Z) && (ka == 0 || al16(A1)) && (kb == 0 || al16(B1));
     // bfloat16 products only where the factorization uses them (Z and A1 both
-    // Y), where the row kernel moves 16 bytes a lane and nothing but W and P
-    // through LDS (N = 2^19, rank 64: 5.69 ms a factorization, 6.67 ms with the
-    // turn-arounds of the blocked kernel); other shapes of a BF16
-    // factorization are computed in FP32
+    // Y); other shapes of a BF16 factorization are computed in FP32.  The row
+    // kernel moves 16 bytes a lane and nothing but W and P through LDS (N = 2^19,
+    // rank 64: 5.69 ms a factorization, 6.67 ms with the turn-arounds of the
+    // blocked kernel; rank 48 the same; N = 2^17, leaf 64, rank 32: 0.74 against
+    // 0.79); up to rank 32 on tiles above 64 rows the blocked kernel streams
+    // faster (N = 2^20, rank 32: 5.32 against 6.06 ms; N = 2^18, leaf 128: 1.23, 1.26)
     if constexpr (sizeof(TZ) == 4 && std::is_same<SA, TZ>::value) {
-      if (bf)
-        return launch_rows<TZ, SA, SB, true>(s, ntiles, 0, tiles, sh, Z, ldz, nz, A1, lda, ka, W, w_ld, w_pstride,
+      if (bf) {
+        if (pair && ka <= 32 && kb <= 32 && sh.rows > 64 && nz > 16) {
+          c_base = nz / 16 * 16;
+          const hipError_t e = launch_block_bf<TZ, SA, SB>(s, ntiles, tiles, Z, ldz, nz / 16, nz, A1, lda, ka, W, w_ld,
+                                                           w_pstride, node_shift, B1, ldb, kb, P, gs);
+          if (e != hipSuccess || c_base == nz) return e;
+        }
+        return launch_rows<TZ, SA, SB, true>(s, ntiles, c_base, tiles, sh, Z, ldz, nz, A1, lda, ka, W, w_ld, w_pstride,
                                              node_shift, B1, ldb, kb, P, gs);
+      }
     }
     // the blocked kernel from 17 columns on: it streams Z in 16-row blocks and
     // is bound by HBM (N = 2^20, rank 32, 2 r r_l columns: FP64 10.56 ms a
@@ -843,12 +915,6 @@ hipError_t launch_level_pass(hipStream_t s, int ntiles, const Tile* tiles, TileS
     if (nz > 16) {
       c_base = nz / 16 * 16;
       hipError_t e;
-      // 4-byte elements, tile heights multiples of 32, even leading dimensions
-      // and 16-byte aligned operands (every paired access is naturally
-      // aligned): two rows per lane
-      auto al16 = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
-      const bool pair = sizeof(TZ) == 4 && sh.mult(32) && ldz % 2 == 0 && (ka == 0 || lda % 2 == 0) &&
-                        (kb == 0 || ldb % 2 == 0) && al16(Z) && (ka == 0 || al16(A1)) && (kb == 0 || al16(B1));
       bool done = false;
       if constexpr (sizeof(TZ) == 4) {
         if (pair) {

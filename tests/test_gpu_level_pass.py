@@ -21,6 +21,8 @@ SHAPES = {
     "192": (192, [32, 48, 16]),
     "256": (256, [31, 20, 64]),
     "16": (16, [5, 16, 13]),
+    "256_32": (256, [32, 16, 32]),
+    "96_32": (96, [16, 32, 16]),
 }
 
 
