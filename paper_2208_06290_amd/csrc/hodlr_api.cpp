@@ -331,7 +331,7 @@ struct hodlr_factors {
   int64_t ldd = 0, ldu = 0, ldv = 0;
   // device plan
   DevMem mem;
-  PlanUpload up;  // host copies of the plan until the first verdict
+  PlanUpload up;  // host copies of the plan until the first factorization has ended
   int64_t* d_off = nullptr;
   int32_t* d_rpre = nullptr;
   std::vector<Tile*> d_tiles;                 // per tile level q = 0..L
@@ -1181,7 +1181,7 @@ hodlr_status hodlr_factor(const hodlr_matrix* A, hodlr_dtype compute, int32_t fl
     delete F;
     return s;
   }
-  F->up = PlanUpload();  // the verdict has waited for the copy
+  F->up = PlanUpload();  // reading the pivot report has waited for the copy
   *out = F;
   return s;
 }
