@@ -35,7 +35,10 @@ constexpr int kCsTile = kCsThreads * kCsEpt;  // elements of a block row / colum
 constexpr double kPi = 3.141592653589793238462643383279502884;
 
 // the entry of points p and q from |x_p - x_q|^2, the first two differences and
-// the normal and weight of q
+// the normal and weight of q.  The sum of two products is written out as the
+// fused operation that is meant: left to the compiler, one kernel fused the
+// first product and another the second, and an ulp decides the pivots of a
+// block that has used up its numerical rank.
 __device__ __forceinline__ double kernel_value(const ConstructKernel& k, double d2, double dx0, double dx1, double n0,
                                                double n1, double wq) {
   switch (k.kind) {
@@ -46,7 +49,7 @@ __device__ __forceinline__ double kernel_value(const ConstructKernel& k, double 
       return (1.0 + s) * exp(-s);
     }
     default: {  // Laplace double layer: w_q n_q . (x_p - x_q) / (2 pi |x_p - x_q|^2)
-      const double num = n0 * dx0 + n1 * dx1;
+      const double num = fma(n0, dx0, n1 * dx1);
       return num / (2.0 * kPi * d2) * wq;
     }
   }

@@ -32,3 +32,19 @@ def test_blocks(kind, dim, rank, m, n):
         for k, j in enumerate(J):
             assert j >= 0 and V[t0 + j, k] == 1.0, k
         assert np.linalg.norm(U[s0:e0] @ V[t0:f0].T - Uo @ Vo.T) <= 1e-12 * np.linalg.norm(M)
+
+
+@pytest.mark.parametrize("kind,dim", [("laplace_dl", 2), ("gauss", 2), ("matern32", 3)])
+@pytest.mark.parametrize("leaf,levels", [(64, 1), (128, 1), (200, 1), (256, 1), (150, 2), (256, 2)])
+def test_one_workgroup_equals_the_tiled_steps_to_the_bit(kind, dim, leaf, levels):
+    """The first columns of rank 33, which takes the tiled steps, are the columns
+    of every smaller rank: the pivots of a block that has used up its numerical
+    rank follow from the last bit of the entries."""
+    n = leaf << levels
+    spec = _spec(kind, n, dim, 3, 0.1)
+    off = np.arange((1 << levels) + 1, dtype=np.int64) * leaf
+    ranks = [0] * (levels - 1)
+    tiled = _gpu_build(spec, [33] + ranks, off)
+    for rank in (6, 24, 32):
+        A = _gpu_build(spec, [rank] + ranks, off)
+        assert (A.U == tiled.U[:rank]).all() and (A.V == tiled.V[:rank]).all(), rank
