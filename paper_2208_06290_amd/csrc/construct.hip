@@ -350,7 +350,8 @@ __global__ __launch_bounds__(NT, 2) void aca_block_kernel(ConstructKernel kd, co
   };
   // The largest modulus, lowest index on ties, of candidates x (absent: NaN or
   // out of the block; last: before these): published per wave with its row g
-  // (whole groups of 8 below k), then chosen from the waves.  Moduli are compared as integers.
+  // (whole groups of 8 below k), then chosen from the waves; a wave without
+  // candidates offers zero.  Moduli are compared as integers.
   auto pick = [&](int sb, double x, bool in, bool last, const double (&g)[kCbRank], int k, int& wave) {
     const unsigned long long bits = __builtin_bit_cast(unsigned long long, x) & 0x7fffffffffffffffull;
     const bool open = in && (last || x == x);
@@ -364,7 +365,7 @@ __global__ __launch_bounds__(NT, 2) void aca_block_kernel(ConstructKernel kd, co
     if (lane == (int)__builtin_ctzll(hit)) {
       ckey[sb][w] = ((unsigned long long)mh << 32) | ml;
       cidx[sb][w] = tid;
-      cval[sb][w] = x;
+      cval[sb][w] = mh ? x : 0.0;
 #pragma unroll
       for (int l0 = 0; l0 < kCbRank; l0 += 8)
         if (l0 < k) {

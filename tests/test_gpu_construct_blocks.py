@@ -48,3 +48,19 @@ def test_one_workgroup_equals_the_tiled_steps_to_the_bit(kind, dim, leaf, levels
     for rank in (6, 24, 32):
         A = _gpu_build(spec, [rank] + ranks, off)
         assert (A.U == tiled.U[:rank]).all() and (A.V == tiled.V[:rank]).all(), rank
+
+
+@pytest.mark.parametrize("kind,dim", [("gauss", 2), ("laplace_dl", 2)])
+@pytest.mark.parametrize("row", [0, 70])
+def test_rows_of_nan_are_skipped_by_both_routes(kind, dim, row):
+    """A point that is not a number makes its residual row one without a pivot:
+    the step is exhausted (zero columns) and the next row is taken."""
+    m, rank = 100, 8
+    spec = _spec(kind, 2 * m, dim, 3, 0.1)
+    spec.points[row] = np.nan
+    off = np.array([0, m, 2 * m], dtype=np.int64)
+    A, tiled = _gpu_build(spec, [rank], off), _gpu_build(spec, [33], off)
+    for got, want in ((A.U, tiled.U[:rank]), (A.V, tiled.V[:rank])):
+        assert ((got == want) | (got.isnan() & want.isnan())).all()
+    if row == 0:  # the first row searched by the block on top
+        assert not A.U[0, :m].any() and not A.V[0, m:].any()
