@@ -12,14 +12,14 @@
 // I_a, V_b = [v_k] to rows I_b of the level's columns of U_big / V_big.
 //
 // Blocks of up to kCbRows rows and columns and ranks up to kCbRank take all their
-// steps in one workgroup (aca_block_kernel).  The others
-// advance together: step k is one launch for the
-// residual rows (a workgroup per 1024-column tile of a block, writing v
-// unnormalized and the tile's largest modulus) and one for the residual
-// columns (each workgroup first reduces its block's row partials to j_k and
-// the pivot value, normalizes its tile of v, then forms its tile of u and the
-// tile's largest modulus over unused rows); the next row launch reduces those
-// to i_{k+1}.  Partials are reduced in a fixed order (deterministic).
+// steps in one workgroup (aca_block_kernel) where that pays (aca_own_launches).
+// The others advance together: step k is one launch for the residual rows (a
+// workgroup per 1024-column tile of a block, writing v unnormalized and the
+// tile's largest modulus) and one for the residual columns (each workgroup first
+// reduces its block's row partials to j_k and the pivot value, normalizes its
+// tile of v, then forms its tile of u and the tile's largest modulus over unused
+// rows); the next row launch reduces those to i_{k+1}.  Partials are reduced in a
+// fixed order (deterministic).
 #include "wave.h"
 
 #include <algorithm>
@@ -34,25 +34,20 @@ constexpr int kCsEpt = 4;
 constexpr int kCsTile = kCsThreads * kCsEpt;  // elements of a block row / column per workgroup
 constexpr double kPi = 3.141592653589793238462643383279502884;
 
-// the entry of points p and q from |x_p - x_q|^2, the first two differences and
-// the normal and weight of q.  The sum of two products is written out as the
-// fused operation that is meant: left to the compiler, one kernel fused the
-// first product and another the second, and an ulp decides the pivots of a
-// block that has used up its numerical rank.
-__device__ __forceinline__ double kernel_value(const ConstructKernel& k, double d2, double dx0, double dx1, double n0,
-                                               double n1, double wq) {
-  switch (k.kind) {
-    case HODLR_KERNEL_GAUSS:
-      return exp(-d2 / (2.0 * (k.ell * k.ell)));
-    case HODLR_KERNEL_MATERN32: {
-      const double s = sqrt(3.0) * sqrt(d2) / k.ell;
-      return (1.0 + s) * exp(-s);
-    }
-    default: {  // Laplace double layer: w_q n_q . (x_p - x_q) / (2 pi |x_p - x_q|^2)
-      const double num = fma(n0, dx0, n1 * dx1);
-      return num / (2.0 * kPi * d2) * wq;
-    }
-  }
+// the entry of points p and q from |x_p - x_q|^2 (Gaussian, Matern)
+__device__ __forceinline__ double radial_value(const ConstructKernel& k, double d2) {
+  if (k.kind == HODLR_KERNEL_GAUSS) return exp(-d2 / (2.0 * (k.ell * k.ell)));
+  const double s = sqrt(3.0) * sqrt(d2) / k.ell;
+  return (1.0 + s) * exp(-s);
+}
+// Laplace double layer, w_q n_q . (x_p - x_q) / (2 pi |x_p - x_q|^2), from the
+// two differences and the normal and weight of q.  The sum of two products is
+// written out as the fused operation that is meant: left to the compiler, one
+// kernel fused the first product and another the second, and an ulp decides the
+// pivots of a block that has used up its numerical rank.
+__device__ __forceinline__ double layer_value(double d2, double dx0, double dx1, double n0, double n1, double wq) {
+  const double num = fma(n0, dx0, n1 * dx1);
+  return num / (2.0 * kPi * d2) * wq;
 }
 
 __device__ __forceinline__ double kernel_offdiag(const ConstructKernel& k, int64_t p, int64_t q) {
@@ -63,8 +58,8 @@ __device__ __forceinline__ double kernel_offdiag(const ConstructKernel& k, int64
     if (d == 0) dx0 = t;
     if (d == 1) dx1 = t;
   }
-  if (k.kind != HODLR_KERNEL_LAPLACE_DL) return kernel_value(k, d2, dx0, dx1, 0.0, 0.0, 0.0);
-  return kernel_value(k, d2, dx0, dx1, k.nrm[q], k.nrm[q + k.ldp], k.w[q]);
+  if (k.kind != HODLR_KERNEL_LAPLACE_DL) return radial_value(k, d2);
+  return layer_value(d2, dx0, dx1, k.nrm[q], k.nrm[q + k.ldp], k.w[q]);
 }
 
 __device__ __forceinline__ double kernel_entry(const ConstructKernel& k, int64_t p, int64_t q) {
@@ -335,8 +330,8 @@ __global__ __launch_bounds__(NT, 2) void aca_block_kernel(ConstructKernel kd, co
       if (d == 0) dx0 = t;
       if (d == 1) dx1 = t;
     }
-    if (!dl) return kernel_value(kd, d2, dx0, dx1, 0.0, 0.0, 0.0);
-    return kernel_value(kd, d2, dx0, dx1, cpt[3][j], cpt[4][j], cpt[5][j]);
+    if (!dl) return radial_value(kd, d2);
+    return layer_value(d2, dx0, dx1, cpt[3][j], cpt[4][j], cpt[5][j]);
   };
   // x - sum_{l<k} c_l g_l in order of l (both are zero from l = k on)
   auto residual = [&](double x, const double* c, const double (&g)[kCbRank], int k) {
@@ -447,8 +442,38 @@ int aca_tile_elems() { return kCsTile; }
 
 int aca_block_class(int m, int n, int rank) {
   const int rows = std::max(m, n);
-  if (rank > kCbRank || rows > kCbRows) return -1;
+  if (rank > kCbRank || rows > kCbRows) return 3;
   return rows <= 128 ? 0 : rows <= 256 ? 1 : 2;
+}
+
+// A class's launch is a chain of 2 rank half steps (one a round of its workgroups:
+// 512 threads a CU) in front of the tiled steps.  These are bound by their 2 rank
+// launches, about 20 us a step, until their tiles fill the chip (8 of 256 threads
+// a CU), and by memory beyond; below that a few more tiles cost nothing and the
+// chain is time added.  So a class, the shortest blocks first, gets its launch
+// where enough work stays behind to keep the tiled steps above their launches:
+// rows times rank of 2^24 for every round; the shortest blocks, whose tiles are
+// nearly empty, as soon as all tiles together fill the chip.  Gaussian kernel, rank
+// 32, us with none, the first, the first two and all three classes:
+//   leaf 128, N = 2^13: 681, 743, -, 929; 2^16: 1319, 1330, -, 1442;
+//     2^17: 2741, 2566, 2408, 2293; rank 16, 2^17: 936, 876, 842, 861
+//   leaf 64, N = 2^15: 962, 1000, -, 1150; 2^16: 1606, 1415, 1460, 1533
+//   leaf 256 (no first), N = 2^17: 2502, -, 2324, 2217; rank 16: 858, -, 818, 833
+// Where every block has a class there are no other launches (N = 1024, leaf
+// 128, rank 32: 516 and 308).
+int aca_own_launches(const int64_t (&blocks)[4], const int64_t (&tiles)[4], const int64_t (&work)[4]) {
+  if (blocks[3] == 0) return 7;
+  const int64_t all = tiles[0] + tiles[1] + tiles[2] + tiles[3];
+  int64_t left = work[0] + work[1] + work[2] + work[3];
+  int own = 0;
+  for (int c = 0; c < 3; ++c) {
+    if (blocks[c] == 0) continue;
+    left -= work[c];
+    const double rounds = std::max(1.0, (double)blocks[c] * (128 << c) / (256 * 512));
+    if (c == 0 ? all < 256 * 8 : left < rounds * (1 << 24)) break;
+    own |= 1 << c;
+  }
+  return own;
 }
 
 hipError_t launch_aca_blocks(hipStream_t s, const ConstructKernel& k, int cls, int nblocks, const AcaBlock* blocks,

@@ -1720,9 +1720,12 @@ hodlr_status hodlr_construct(const hodlr_kernel* k, int64_t n, int32_t levels, c
          hodlr::launch_construct_leaves<float>(st, kd, nleaf, d_off, m_max, static_cast<float*>(D), ldd));
     if (R == 0) return HODLR_OK;
     // the sibling blocks of every level: those of one workgroup by class, then
-    // the tiled ones and their tiles
+    // the tiled ones and their tiles; aca_own_launches decides which classes
+    // stay tiled
     const int te = hodlr::aca_tile_elems();
     std::vector<hodlr::AcaBlock> blocks[4];
+    std::vector<int> cls;
+    int64_t count[4] = {}, ntile[4] = {}, work[4] = {};
     int col = 0, kmax = 0;
     for (int l = 1; l <= L; ++l) {
       const int r = rk[l - 1];
@@ -1737,20 +1740,30 @@ hodlr_status hodlr_construct(const hodlr_kernel* k, int64_t n, int32_t levels, c
           B.n = (int32_t)(off[(size_t)(b + 1) * per] - B.c0);
           B.col = col;
           B.rank = r;
-          const int cls = hodlr::aca_block_class(B.m, B.n, r);
-          if (cls >= 0) {
-            blocks[cls].push_back(B);
-            continue;
-          }
-          B.tile0 = (int32_t)tiles.size();
           B.ntile = (std::max(B.m, B.n) + te - 1) / te;
-          for (int t = 0; t < B.ntile; ++t) tiles.push_back({(int32_t)blocks[3].size(), t, (int32_t)tiles.size()});
-          blocks[3].push_back(B);
-          kmax = std::max(kmax, r);
+          const int c = hodlr::aca_block_class(B.m, B.n, r);
+          ++count[c];
+          ntile[c] += B.ntile;
+          work[c] += (int64_t)B.m * r;
+          cls.push_back(c);
+          all.push_back(B);
         }
       }
       col += r;
     }
+    const int own = hodlr::aca_own_launches(count, ntile, work);
+    for (size_t i = 0; i < all.size(); ++i) {
+      hodlr::AcaBlock& B = all[i];
+      if (own >> cls[i] & 1) {
+        blocks[cls[i]].push_back(B);
+        continue;
+      }
+      B.tile0 = (int32_t)tiles.size();
+      for (int t = 0; t < B.ntile; ++t) tiles.push_back({(int32_t)blocks[3].size(), t, (int32_t)tiles.size()});
+      blocks[3].push_back(B);
+      kmax = std::max(kmax, B.rank);
+    }
+    all.clear();
     for (auto& v : blocks) all.insert(all.end(), v.begin(), v.end());
     const size_t nt = tiles.size();
     hodlr::AcaBlock* d_blocks = nullptr;
@@ -1774,6 +1787,7 @@ hodlr_status hodlr_construct(const hodlr_kernel* k, int64_t n, int32_t levels, c
     }
     const hodlr::AcaBlock* d_cls = d_blocks;
     for (int c = 0; c < 3; ++c) {
+      if (blocks[c].empty()) continue;
       HL("aca_block", hodlr::launch_aca_blocks(st, kd, c, (int)blocks[c].size(), d_cls, U64, ldu64, V64, ldv64));
       d_cls += blocks[c].size();
     }

@@ -273,10 +273,13 @@ int aca_tile_elems();
 template <typename TS>
 hipError_t launch_construct_leaves(hipStream_t s, const ConstructKernel& k, int nleaf, const int64_t* d_off, int m_max,
                                    TS* D, int64_t ldd);
-// Blocks that one workgroup takes through all steps: the class of a block's
-// kernel (0 .. 2), or -1 for the tiled steps; the launch for nblocks of a class
-// (their tile0 and ntile are not used).
+// Blocks that one workgroup can take through all steps: the class of a block's
+// kernel (0 .. 2), or 3 for the tiled steps; the classes that get a launch of
+// their own (bit c; the others are tiled too) from the number of blocks, their
+// tiles and the sum of rows times rank of each class; the launch for nblocks of
+// a class (their tile0 and ntile are not used).
 int aca_block_class(int m, int n, int rank);
+int aca_own_launches(const int64_t (&blocks)[4], const int64_t (&tiles)[4], const int64_t (&work)[4]);
 hipError_t launch_aca_blocks(hipStream_t s, const ConstructKernel& k, int cls, int nblocks, const AcaBlock* blocks,
                              double* U, int64_t ldu, double* V, int64_t ldv);
 // step `step` of every tiled block (rank > step): the residual-row launch and the residual-column launch

@@ -64,3 +64,22 @@ def test_rows_of_nan_are_skipped_by_both_routes(kind, dim, row):
         assert ((got == want) | (got.isnan() & want.isnan())).all()
     if row == 0:  # the first row searched by the block on top
         assert not A.U[0, :m].any() and not A.V[0, m:].any()
+
+
+@pytest.mark.parametrize("n,leaf,ranks,own,tiled", [
+    (4096, 64, [16] * 6, 0, 16),            # a few small blocks join the tiled steps: no launch in front of them
+    (1024, 128, [16] * 3, 3, 0),            # nothing but small blocks: one launch a class
+    (1 << 17, 128, [32] * 10, 3, 32),       # the tiles fill the chip with and without the small blocks
+    (1 << 17, 128, [16] * 10, 2, 16),       # without the classes of 128 and 256 rows they do no more
+    (1 << 17, 256, [16] * 9, 1, 16),
+    (1 << 16, 128, [32] * 9, 0, 32),
+    (4096, 64, [20, 20, 20, 0, 0, 4], 0, 20),
+])
+def test_routes_by_size(n, leaf, ranks, own, tiled):
+    from paper_2208_06290_amd import hodlr
+    spec = _spec("gauss", n, 2, 3, 0.1)
+    hodlr.timing(True)
+    _gpu_build(spec, ranks, None)
+    kt = hodlr.kernel_times()
+    hodlr.timing(False)
+    assert kt.get("aca_block", (0, 0))[1] == own and kt.get("aca_step", (0, 0))[1] == tiled
