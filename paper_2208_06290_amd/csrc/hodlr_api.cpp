@@ -151,6 +151,10 @@ class DevicePool {
   }
   // the work that used the block has finished
   void put(const DevBlock& b) {
+    if (b.bytes > kPoolBytes) {
+      (void)hipFree(b.p);
+      return;
+    }
     std::vector<DevBlock> drop;
     {
       std::lock_guard<std::mutex> g(mu_);

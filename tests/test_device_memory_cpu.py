@@ -1,0 +1,93 @@
+"""Device memory of the library without a device: its host code, linked with a
+HIP runtime that only keeps count (mock_hip.cpp).  A block must not be handed
+on, or kept for that, while work that uses it has not been waited for."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from conftest import ROOT
+
+CSRC = os.path.join(ROOT, "paper_2208_06290_amd", "csrc")
+TESTS = os.path.dirname(os.path.abspath(__file__))
+HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+
+
+@pytest.fixture(scope="module")
+def built(tmp_path_factory):
+    d = str(tmp_path_factory.mktemp("mock"))
+
+    def run(*cmd):
+        r = subprocess.run(cmd, cwd=d, capture_output=True, text=True)
+        assert r.returncode == 0, r.stderr
+        return r.stdout
+
+    run(HIPCC, "-O1", "-std=c++17", "-fPIC", "--offload-host-only", "-w", "-I" + os.path.join(ROOT, "include"), "-c",
+        os.path.join(CSRC, "hodlr_api.cpp"), "-o", "api.o")
+    names = [w for w in run("nm", "-u", "api.o").split() if w.startswith("_ZN5hodlr") and "launch_" in w and
+             "aca_own_launches" not in w]
+    with open(os.path.join(d, "stubs.c"), "w") as f:
+        f.write("int mock_launch(void*);\n" + "".join(f"int {n}(void* s) {{ return mock_launch(s); }}\n" for n in names))
+    run("gcc", "-O1", "-fPIC", "-c", "stubs.c", "-o", "stubs.o")
+    run("g++", "-O1", "-std=c++17", "-fPIC", "-c", os.path.join(TESTS, "mock_hip.cpp"), "-o", "mock.o")
+    run("g++", "-shared", "-Wl,-Bsymbolic", "-Wl,-z,defs", "-o", "libmock.so", "api.o", "stubs.o", "mock.o", "-lpthread")
+    return os.path.join(d, "libmock.so")
+
+
+@pytest.fixture
+def lib(built, tmp_path):
+    copy = shutil.copy(built, tmp_path / "lib.so")  # its own pool and counters
+    lib = ctypes.CDLL(str(copy))
+    for f in ("mock_pending", "mock_graph_work", "mock_mallocs", "mock_frees"):
+        getattr(lib, f).restype = ctypes.c_long
+    lib.mock_used.restype = ctypes.c_size_t
+    lib.mock_capacity.argtypes = [ctypes.c_size_t]
+    lib.mock_fail_in.argtypes = [ctypes.c_long]
+    lib.hodlr_destroy.argtypes = [ctypes.c_void_p]
+    lib.hodlr_destroy.restype = None
+    return lib
+
+
+S1, S2 = ctypes.c_void_p(0x10), ctypes.c_void_p(0x20)  # streams
+FAKE = 0x1000  # device addresses, never read
+
+
+def _matrix(n, leaf, rank, dtype=0):
+    from paper_2208_06290_amd import hodlr
+    m = hodlr._Matrix()
+    m.n, m.levels, m.dtype = n, (n // leaf).bit_length() - 1, dtype
+    m.ranks = (ctypes.c_int32 * max(1, m.levels))(*[rank] * m.levels)
+    m.D = m.U = m.V = FAKE
+    m.ldd = m.ldu = m.ldv = n
+    return m
+
+
+def _factor(lib, m, stream):
+    h = ctypes.c_void_p()
+    st = lib.hodlr_factor(ctypes.byref(m), 0, 0, stream, ctypes.byref(h), None)
+    return st, h
+
+
+def _bytes(lib, n, leaf, rank):
+    """What a factorization of this shape allocates."""
+    before = lib.mock_used()
+    st, h = _factor(lib, _matrix(n, leaf, rank), S1)
+    assert st == 0
+    return h, lib.mock_used() - before
+
+
+def test_a_block_above_the_bound_leaves_the_kept_ones_alone(lib):
+    small, nb = _bytes(lib, 4096, 64, 16)
+    large, big = _bytes(lib, 1 << 20, 256, 32)
+    assert nb < 1 << 30 and big > 4 << 30
+    lib.hodlr_destroy(small)
+    assert lib.mock_used() == nb + big  # kept
+    lib.hodlr_destroy(large)
+    assert lib.mock_used() < big, "a block larger than the bound goes straight back"
+    assert lib.mock_used() >= nb, "and takes no other with it"
+    count = lib.mock_mallocs()
+    st, again = _factor(lib, _matrix(4096, 64, 16), S2)
+    assert st == 0 and lib.mock_mallocs() == count
+    lib.hodlr_destroy(again)
