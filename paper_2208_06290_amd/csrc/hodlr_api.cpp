@@ -723,6 +723,16 @@ hodlr_status dispatch_factor(hodlr_factors* F, hipStream_t st) {
   return run_factor<float, float>(F, st, bf);
 }
 
+// The factorization, its event and its verdict.  After an error nothing that
+// was queued uses the factors any more (no event tells when it has ended).
+hodlr_status factor_and_report(hodlr_factors* F, hipStream_t st, hodlr_info* info) {
+  hodlr_status s = dispatch_factor(F, st);
+  if (s == HODLR_OK && hipEventRecord(F->ready, st) != hipSuccess) s = HODLR_ERR_HIP;
+  if (s == HODLR_OK) s = verdict(F, st, info);
+  if (s < 0) (void)hipStreamSynchronize(st);
+  return s;
+}
+
 // ---- solve-side workspace --------------------------------------------------
 // The workspace of stream st (created on first use).
 Workspace* get_ws(hodlr_factors* F, hipStream_t st) {
@@ -1174,11 +1184,8 @@ hodlr_status hodlr_factor(const hodlr_matrix* A, hodlr_dtype compute, int32_t fl
     delete F;
     return s;
   }
-  s = dispatch_factor(F, st);
-  if (s == HODLR_OK && hipEventRecord(F->ready, st) != hipSuccess) s = HODLR_ERR_HIP;
-  if (s == HODLR_OK) s = verdict(F, st, info);
+  s = factor_and_report(F, st, info);
   if (s < 0) {
-    hipStreamSynchronize(st);
     F->mem.release();
     hipEventDestroy(F->ready);
     hipEventDestroy(F->na_done);
@@ -1227,12 +1234,11 @@ hodlr_status hodlr_refactor(hodlr_factors* F, const hodlr_matrix* A, void* strea
     DevMem none;
     Embedded X;
     if ((s = embed_complex(A, st, none, X, static_cast<double*>(const_cast<void*>(F->D)),
-                           static_cast<double*>(const_cast<void*>(F->U)), static_cast<double*>(const_cast<void*>(F->V)))))
+                           static_cast<double*>(const_cast<void*>(F->U)), static_cast<double*>(const_cast<void*>(F->V))))) {
+      (void)hipStreamSynchronize(st);  // copies already queued
       return s;
-    s = dispatch_factor(F, st);
-    if (s == HODLR_OK && hipEventRecord(F->ready, st) != hipSuccess) s = HODLR_ERR_HIP;
-    if (s == HODLR_OK) s = verdict(F, st, info);
-    return s;
+    }
+    return factor_and_report(F, st, info);
   }
   F->D = A->D;
   F->U = A->U;
@@ -1241,10 +1247,7 @@ hodlr_status hodlr_refactor(hodlr_factors* F, const hodlr_matrix* A, void* strea
     F->lu = const_cast<void*>(F->D);
     F->Y = const_cast<void*>(F->U);
   }
-  s = dispatch_factor(F, st);
-  if (s == HODLR_OK && hipEventRecord(F->ready, st) != hipSuccess) s = HODLR_ERR_HIP;
-  if (s == HODLR_OK) s = verdict(F, st, info);
-  return s;
+  return factor_and_report(F, st, info);
 }
 
 hodlr_status hodlr_solve(const hodlr_factors* F, int64_t nrhs, double* B, int64_t ldb, const hodlr_solve_opts* o,

@@ -91,3 +91,24 @@ def test_a_block_above_the_bound_leaves_the_kept_ones_alone(lib):
     st, again = _factor(lib, _matrix(4096, 64, 16), S2)
     assert st == 0 and lib.mock_mallocs() == count
     lib.hodlr_destroy(again)
+
+
+@pytest.mark.parametrize("dtype", [0, 3])  # FP64; complex, whose embedding the factorization owns
+@pytest.mark.parametrize("launch", [0, 1, 2, 5, 9, 12])
+def test_a_failed_refactorization_leaves_no_work_behind(lib, dtype, launch):
+    m = _matrix(1024, 64, 8, dtype)
+    st, h = _factor(lib, m, S1)
+    assert st == 0
+    lib.mock_fail_in(launch)
+    assert lib.hodlr_refactor(h, ctypes.byref(m), S2, None) == -3
+    lib.hodlr_destroy(h)  # its memory goes to the pool
+    assert lib.mock_pending(S2) == 0
+
+
+@pytest.mark.parametrize("dtype", [0, 3])
+@pytest.mark.parametrize("launch", [0, 1, 3, 6, 12])
+def test_a_failed_factorization_leaves_no_work_behind(lib, dtype, launch):
+    lib.mock_fail_in(launch)
+    st, h = _factor(lib, _matrix(1024, 64, 8, dtype), S2)
+    assert st == -3 and not h
+    assert lib.mock_pending(S2) == 0
