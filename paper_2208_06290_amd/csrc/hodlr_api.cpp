@@ -96,6 +96,12 @@ static hodlr_status hip_fail(hipError_t e, const char* what) {
   return HODLR_ERR_HIP;
 }
 
+// Is st recording into a graph?  (The null stream cannot.)
+static bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+  return st && hipStreamIsCapturing(st, &c) == hipSuccess && c != hipStreamCaptureStatusNone;
+}
+
 // ---------------------------------------------------------------------------
 // plan and factor object
 // ---------------------------------------------------------------------------
@@ -208,9 +214,14 @@ DevicePool& pool() {
   return *p;
 }
 
-// Device memory of one owner.  alloc() gives one array; reserve() collects
-// arrays (256-byte aligned parts) that commit() places in a single block.
+// Device memory of one owner, for work on `stream`.  alloc() gives one array;
+// reserve() collects arrays (256-byte aligned parts) that commit() places in a
+// single block.  As device memory cannot be allocated for a stream that records
+// into a graph, none is given then, whatever the pool holds: a replay would use
+// blocks that have other owners by then.
 struct DevMem {
+  explicit DevMem(hipStream_t s = nullptr) : stream(s) {}
+  hipStream_t stream;
   std::vector<DevBlock> blocks;
   size_t bytes = 0;
   std::vector<std::pair<void**, size_t>> parts;
@@ -219,6 +230,7 @@ struct DevMem {
   hodlr_status alloc(X** p, size_t count) {
     *p = nullptr;
     if (count == 0) return HODLR_OK;
+    if (capturing(stream)) return HODLR_ERR_ALLOC;
     DevBlock b;
     hodlr_status s = pool().take(count * sizeof(X), &b);
     if (s) return s;
@@ -247,6 +259,19 @@ struct DevMem {
     for (const DevBlock& b : blocks) pool().put(b);
     blocks.clear();
     bytes = 0;
+  }
+  // release() once the stream has ended the work queued with the blocks; s, or
+  // the error of that wait (the blocks are then not handed on)
+  hodlr_status finish(hodlr_status s) {
+    if (blocks.empty()) return s;
+    const hipError_t e = hipStreamSynchronize(stream);
+    if (e != hipSuccess) {
+      for (const DevBlock& b : blocks) (void)hipFree(b.p);
+      blocks.clear();
+      if (s == HODLR_OK) s = HODLR_ERR_HIP;
+    }
+    release();
+    return s;
   }
 };
 
@@ -533,6 +558,7 @@ int kvecs(int r) { return 2 * ((r + 15) & ~15); }
 
 hodlr_status allocate_factors(hodlr_factors* F, hipStream_t st) {
   DevMem& M = F->mem;
+  M.stream = st;
   const int L = F->L;
   const size_t ts = F->tsize;
   hodlr_status s;
@@ -740,7 +766,7 @@ Workspace* get_ws(hodlr_factors* F, hipStream_t st) {
   auto it = F->wsmap.find(st);
   if (it != F->wsmap.end()) return it->second.get();
   std::unique_ptr<Workspace> w(new Workspace());
-  w->stream = st;
+  w->stream = w->mem.stream = st;
   if (hipEventCreateWithFlags(&w->done, hipEventDisableTiming) != hipSuccess) return nullptr;
   Workspace* p = w.get();
   F->wsmap[st] = std::move(w);
@@ -1159,17 +1185,13 @@ hodlr_status hodlr_factor(const hodlr_matrix* A, hodlr_dtype compute, int32_t fl
     // factor the real embedding, which the factorization then owns
     if (flags & HODLR_INPLACE) return HODLR_ERR_UNSUPPORTED;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    DevMem M;
+    DevMem M(st);
     Embedded X;
     hodlr_status s = embed_complex(A, st, M, X, nullptr, nullptr, nullptr);
     if (s == HODLR_OK) s = hodlr_factor(&X.E, compute, 0, stream, out, info);
-    if (*out) {
-      (*out)->cplx = 1;
-      (*out)->emb = std::move(M);
-    } else {
-      hipStreamSynchronize(st);
-      M.release();
-    }
+    if (!*out) return M.finish(s);
+    (*out)->cplx = 1;
+    (*out)->emb = std::move(M);
     return s;
   }
   hodlr_factors* F = new hodlr_factors();
@@ -1177,8 +1199,7 @@ hodlr_status hodlr_factor(const hodlr_matrix* A, hodlr_dtype compute, int32_t fl
   hodlr_status s = setup(F, A, compute, flags);
   if (s == HODLR_OK) s = allocate_factors(F, st);
   if (s != HODLR_OK) {
-    if (!F->mem.blocks.empty()) (void)hipStreamSynchronize(st);  // the plan's copy
-    F->mem.release();
+    s = F->mem.finish(s);  // the plan's copy
     if (F->ready) hipEventDestroy(F->ready);
     if (F->na_done) hipEventDestroy(F->na_done);
     delete F;
@@ -1186,7 +1207,7 @@ hodlr_status hodlr_factor(const hodlr_matrix* A, hodlr_dtype compute, int32_t fl
   }
   s = factor_and_report(F, st, info);
   if (s < 0) {
-    F->mem.release();
+    s = F->mem.finish(s);
     hipEventDestroy(F->ready);
     hipEventDestroy(F->na_done);
     delete F;
@@ -1311,13 +1332,11 @@ hodlr_status hodlr_matvec(const hodlr_matrix* A, int32_t trans, int64_t nrhs, co
   if (A && A->dtype == HODLR_C128) {
     if (nrhs > 0 && (!X || !Yo || ldx < A->n || ldy < A->n)) return HODLR_ERR_ARG;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    DevMem M;
+    DevMem M(st);
     Embedded E;
     hodlr_status s = embed_complex(A, st, M, E, nullptr, nullptr, nullptr);
     if (s == HODLR_OK) s = hodlr_matvec(&E.E, trans, nrhs, X, 2 * ldx, Yo, 2 * ldy, stream);
-    hipStreamSynchronize(st);
-    M.release();
-    return s;
+    return M.finish(s);
   }
   hodlr_factors F;
   std::vector<int64_t> off;
@@ -1330,15 +1349,14 @@ hodlr_status hodlr_matvec(const hodlr_matrix* A, int32_t trans, int64_t nrhs, co
   s = setup(&F, A, A->dtype == HODLR_F64 ? HODLR_F64 : HODLR_F32, 0);
   if (s) return s;
   hipStream_t st = static_cast<hipStream_t>(stream);
+  F.mem.stream = st;
   plan(&F, F.L);
   s = F.up.send(F.mem, st);
   double* tree = nullptr;
   const size_t treeN = (((size_t)1 << (F.L + 1)) - 2) * (size_t)std::max(F.R, 1) * nrhs;
   if (!s) s = F.mem.alloc(&tree, std::max<size_t>(treeN, 1));
   if (!s) s = matvec_dispatch(&F, st, trans ? 1 : 0, (int)nrhs, X, ldx, Yo, ldy, tree);
-  hipStreamSynchronize(st);
-  F.mem.release();
-  return s;
+  return F.mem.finish(s);
 }
 
 hodlr_status hodlr_grad(const hodlr_factors* Fc, int64_t nrhs, const double* X, int64_t ldx, const double* Lam,
@@ -1406,7 +1424,7 @@ hodlr_status hodlr_factors_y(const hodlr_factors* Fc, double* Yo, int64_t ldy, v
   if (!F || (F->R > 0 && (!Yo || ldy < (F->cplx ? F->n / 2 : F->n)))) return HODLR_ERR_ARG;
   if (F->R == 0) return HODLR_OK;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  DevMem M;
+  DevMem M(st);
   double* Yr = Yo;
   int64_t ldr = ldy;
   if (F->cplx) {  // the embedded Y first, then the complex Y from it
@@ -1427,12 +1445,7 @@ hodlr_status hodlr_factors_y(const hodlr_factors* Fc, double* Yo, int64_t ldy, v
   };
   // no buffers needed; the stream's done event tells hodlr_destroy and
   // hodlr_refactor when Y_big has been read
-  hodlr_status s = on_stream(F, st, -1, [&](Workspace&) { return convert(); });
-  if (F->cplx) {
-    hipStreamSynchronize(st);
-    M.release();
-  }
-  return s;
+  return M.finish(on_stream(F, st, -1, [&](Workspace&) { return convert(); }));
 }
 
 hodlr_status hodlr_logdet(const hodlr_factors* Fc, double* sign, double* logabs, void* stream) {
@@ -1598,7 +1611,7 @@ hodlr_status hodlr_logdet_grad(const hodlr_factors* Fc, void* dD, void* dU, void
   if (F->singular) return HODLR_ERR_SINGULAR;  // log|det A| is -inf: no gradient
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (hipStreamWaitEvent(st, F->ready, 0) != hipSuccess) return HODLR_ERR_HIP;
-  DevMem M;
+  DevMem M(st);
   hodlr_status s;
   if (F->compute == HODLR_F64)
     s = logdet_grad_impl<double, double>(F, st, M, dD, dU, dV);
@@ -1606,10 +1619,7 @@ hodlr_status hodlr_logdet_grad(const hodlr_factors* Fc, void* dD, void* dU, void
     s = logdet_grad_impl<float, double>(F, st, M, dD, dU, dV);
   else
     s = logdet_grad_impl<float, float>(F, st, M, dD, dU, dV);
-  // the temporaries are released once the stream has used them
-  if (hipStreamSynchronize(st) != hipSuccess && s == HODLR_OK) s = HODLR_ERR_HIP;
-  M.release();
-  return s;
+  return M.finish(s);  // the temporaries are released once the stream has used them
 }
 
 size_t hodlr_factor_bytes(const hodlr_factors* Fc) {
@@ -1709,7 +1719,7 @@ hodlr_status hodlr_construct(const hodlr_kernel* k, int64_t n, int32_t levels, c
   for (int r : rk) R += r;
   hodlr::ConstructKernel kd{(int)k->kind, k->dim, k->points, k->ldp, k->normals, k->weights, k->curvature, k->ell,
                             k->shift};
-  DevMem M;
+  DevMem M(st);
   std::vector<hodlr::AcaBlock> all;
   std::vector<hodlr::AcaTile> tiles;
   auto run = [&]() -> hodlr_status {
@@ -1806,11 +1816,8 @@ hodlr_status hodlr_construct(const hodlr_kernel* k, int64_t n, int32_t levels, c
     }
     return HODLR_OK;
   };
-  s = run();
   // the host vectors the copies read and the temporaries live until the stream is done
-  if (hipStreamSynchronize(st) != hipSuccess && s == HODLR_OK) s = HODLR_ERR_HIP;
-  M.release();
-  return s;
+  return M.finish(run());
 }
 
 }  // extern "C"

@@ -112,3 +112,30 @@ def test_a_failed_factorization_leaves_no_work_behind(lib, dtype, launch):
     st, h = _factor(lib, _matrix(1024, 64, 8, dtype), S2)
     assert st == -3 and not h
     assert lib.mock_pending(S2) == 0
+
+
+@pytest.mark.parametrize("dtype", [0, 3])
+def test_calls_that_allocate_are_refused_under_capture(lib, dtype):
+    """As hipMalloc refuses then, so does the pool, whatever it holds."""
+    m = _matrix(1024, 64, 8, dtype)
+    ld = ctypes.c_int64(1024)
+    X, Y = ctypes.c_void_p(FAKE), ctypes.c_void_p(2 * FAKE)
+
+    def matvec(s):
+        return lib.hodlr_matvec(ctypes.byref(m), 0, ctypes.c_int64(1), X, ld, Y, ld, s)
+
+    st, h = _factor(lib, m, S1)
+    assert st == 0 and matvec(S1) == 0
+    st, other = _factor(lib, m, S1)
+    lib.hodlr_destroy(other)  # the pool has blocks of every size needed
+    lib.mock_record(S1, 1)
+    assert matvec(S1) == -2
+    assert _factor(lib, m, S1)[0] == -2
+    assert lib.hodlr_solve(h, ctypes.c_int64(1), X, ld, None, S1, None) == -2  # no workspace of this stream yet
+    assert lib.mock_graph_work() == 0  # nothing was recorded
+    lib.mock_record(S1, 0)
+    assert matvec(S1) == 0 and lib.hodlr_solve(h, ctypes.c_int64(1), X, ld, None, S1, None) == 0
+    lib.mock_record(S1, 1)
+    assert lib.hodlr_solve(h, ctypes.c_int64(1), X, ld, None, S1, None) == 0
+    lib.mock_record(S1, 0)
+    lib.hodlr_destroy(h)
