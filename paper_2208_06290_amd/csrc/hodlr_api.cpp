@@ -6,6 +6,7 @@
 // synchronisations are the singularity verdict of a factorization and the
 // residual norm of each refinement step.
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -399,6 +400,9 @@ struct hodlr_factors {
   int device = 0;
   std::mutex na_mu;
   hipEvent_t na_done = nullptr;
+  // a call was recorded into a graph: its replays use the factors and
+  // workspaces at times that no event of the library covers
+  std::atomic<bool> recorded{false};
   // complex matrices: the factors are those of the real embedding, whose
   // D, U, V the factorization owns here (n, off, ranks are the embedded ones)
   int cplx = 0;
@@ -759,6 +763,16 @@ hodlr_status factor_and_report(hodlr_factors* F, hipStream_t st, hodlr_info* inf
   return s;
 }
 
+// Before memory that replays of a recorded call may use is handed on: waits for
+// the device, as hipFree does.
+hodlr_status wait_for_replays(const hodlr_factors* F) {
+  if (!F->recorded) return HODLR_OK;
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess || hipSetDevice(F->device) != hipSuccess) return HODLR_ERR_HIP;
+  const hipError_t e = hipDeviceSynchronize();
+  return hipSetDevice(dev) == hipSuccess && e == hipSuccess ? HODLR_OK : HODLR_ERR_HIP;
+}
+
 // ---- solve-side workspace --------------------------------------------------
 // The workspace of stream st (created on first use).
 Workspace* get_ws(hodlr_factors* F, hipStream_t st) {
@@ -824,7 +838,10 @@ size_t noalloc_bytes(const hodlr_factors* F, int nrhs) {
 hodlr_status ensure_ws(hodlr_factors* F, Workspace& W, int nrhs) {
   if (nrhs <= W.nrhs) return HODLR_OK;
   // the old buffers may still be read by queued work of this stream
-  if (W.nrhs >= 0 && hipStreamSynchronize(W.stream) != hipSuccess) return HODLR_ERR_HIP;
+  if (W.nrhs >= 0) {
+    if (hipStreamSynchronize(W.stream) != hipSuccess) return HODLR_ERR_HIP;
+    if (hodlr_status s = wait_for_replays(F)) return s;
+  }
   W.mem.release();
   W.nrhs = -1;
   const size_t ts = F->tsize;
@@ -1062,6 +1079,7 @@ hodlr_status on_stream(hodlr_factors* F, hipStream_t st, int nrhs, Fn fn) {
   std::lock_guard<std::mutex> g(W->mu);
   hodlr_status s = ensure_ws(F, *W, nrhs);
   if (s) return s;
+  if (capturing(st)) F->recorded = true;
   if (hipStreamWaitEvent(st, F->ready, 0) != hipSuccess) return HODLR_ERR_HIP;
   s = fn(*W);
   if (hipEventRecord(W->done, st) != hipSuccess && s >= 0) s = HODLR_ERR_HIP;
@@ -1319,6 +1337,7 @@ hodlr_status hodlr_solve_noalloc(const hodlr_factors* Fc, int32_t trans, int64_t
   if (nrhs <= kNarrow && need + z.pmax * ts + 256 <= scratch_capacity()) W.sP2 = take(z.pmax * ts);
   hipStream_t st = static_cast<hipStream_t>(stream);
   std::lock_guard<std::mutex> g(F->na_mu);
+  if (capturing(st)) F->recorded = true;
   if (hipStreamWaitEvent(st, F->ready, 0) != hipSuccess) return HODLR_ERR_HIP;
   hodlr_status s = F->compute == HODLR_F64 ? solve_impl<double>(F, W, trans, (int)nrhs, B, ldb, nullptr, st, nullptr)
                                            : solve_impl<float>(F, W, trans, (int)nrhs, B, ldb, nullptr, st, nullptr);
@@ -1634,7 +1653,8 @@ size_t hodlr_factor_bytes(const hodlr_factors* Fc) {
 void hodlr_destroy(hodlr_factors* F) {
   if (!F) return;
   // wait only for this factorization's own work: the factorization itself and
-  // the last call on each stream that used it
+  // the last call on each stream that used it (and for replays of recorded ones)
+  (void)wait_for_replays(F);
   hipEventSynchronize(F->ready);
   hipEventSynchronize(F->na_done);
   for (auto& kv : F->wsmap) {

@@ -139,3 +139,34 @@ def test_calls_that_allocate_are_refused_under_capture(lib, dtype):
     assert lib.hodlr_solve(h, ctypes.c_int64(1), X, ld, None, S1, None) == 0
     lib.mock_record(S1, 0)
     lib.hodlr_destroy(h)
+
+
+@pytest.mark.parametrize("through", ["solve", "noalloc", "y_big"])
+def test_release_waits_for_replays_of_recorded_calls(lib, through):
+    """hipFree waited for the device; blocks that go to the pool must as well
+    where a graph may still be replaying."""
+    m = _matrix(1024, 64, 8)
+    ld, X = ctypes.c_int64(1024), ctypes.c_void_p(FAKE)
+    st, h = _factor(lib, m, S1)
+
+    def call(n, stream):
+        n = ctypes.c_int64(n)
+        if through == "noalloc":
+            return lib.hodlr_solve_noalloc(h, 0, n, X, ld, stream)
+        if through == "y_big":
+            return lib.hodlr_factors_y(h, X, ld, stream)
+        return lib.hodlr_solve(h, n, X, ld, None, stream, None)
+
+    assert st == 0 and call(1, S1) == 0
+    lib.mock_record(S1, 1)
+    assert call(1, S1) == 0
+    lib.mock_record(S1, 0)
+    assert lib.mock_graph_work() > 0
+    if through == "solve":  # a larger workspace replaces the recorded one
+        assert call(2, S1) == 0 and lib.mock_graph_work() == 0
+        lib.mock_record(S1, 1)
+        assert call(2, S1) == 0
+        lib.mock_record(S1, 0)
+    frees = lib.mock_frees()
+    lib.hodlr_destroy(h)
+    assert lib.mock_graph_work() == 0 and lib.mock_frees() == frees
