@@ -103,6 +103,7 @@ def _timed_path(hodlr, A, precision, B, refine, steps, warmup, adjoint=False):
     import torch
 
     _say(f"{precision}: factor + warmup")
+    hodlr.release_memory()  # no block of an earlier factorization
     free0 = torch.cuda.mem_get_info()[0]
     F = hodlr.factor(A, precision)
     torch.cuda.synchronize()

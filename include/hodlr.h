@@ -31,7 +31,8 @@
  * Device memory: blocks that a factorization, a workspace or a call's
  * temporaries no longer need (their work has finished) are kept for the next
  * ones, at most 4 GiB per device; a block not reused by the 64 releases after
- * it is freed, and all are freed when an allocation fails.
+ * it is freed, and all are freed when an allocation of the library fails or
+ * hodlr_release_memory is called (other allocators' failures do not reach it).
  *
  * Errors: negative status = invalid argument / resource error, detected
  * before any kernel is launched where possible; nothing is written then.
@@ -352,9 +353,14 @@ hodlr_status hodlr_construct(const hodlr_kernel *k, int64_t n, int32_t levels, c
 size_t hodlr_factor_bytes(const hodlr_factors *F);
 
 /* Release F.  Waits for F's own pending work only (the factorization and
- * the last call on each stream that used F), not for the whole device.
+ * the last call on each stream that used F), not for the whole device unless
+ * a call on F was recorded into a HIP graph, whose replays it waits for.
  * NULL is ignored. */
 void hodlr_destroy(hodlr_factors *F);
+
+/* Free the device memory that is kept for reuse (see above) on the current
+ * device. */
+void hodlr_release_memory(void);
 
 const char *hodlr_status_string(hodlr_status s);
 

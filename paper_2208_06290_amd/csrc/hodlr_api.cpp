@@ -116,7 +116,8 @@ namespace {
 // them, so any stream may take them; a block is handed to one owner at a time.
 // Bounded: per device at most kPoolBytes (a block larger than that goes
 // straight back), a block that kPoolAge later returns have not found a use for
-// is freed, and everything is freed when an allocation fails.
+// is freed, and everything is freed when an allocation fails or on request
+// (hodlr_release_memory).
 constexpr size_t kPoolBytes = size_t(4) << 30;
 constexpr uint64_t kPoolAge = 64;
 
@@ -1639,6 +1640,11 @@ hodlr_status hodlr_logdet_grad(const hodlr_factors* Fc, void* dD, void* dU, void
   else
     s = logdet_grad_impl<float, float>(F, st, M, dD, dU, dV);
   return M.finish(s);  // the temporaries are released once the stream has used them
+}
+
+void hodlr_release_memory(void) {
+  int dev = -1;
+  if (hipGetDevice(&dev) == hipSuccess) pool().give_back(dev);
 }
 
 size_t hodlr_factor_bytes(const hodlr_factors* Fc) {

@@ -65,7 +65,7 @@ KERNELS = {"gauss": 0, "matern32": 1, "laplace_dl": 2}
 EXPORTS = ["hodlr_factor", "hodlr_refactor", "hodlr_solve", "hodlr_solve_adjoint", "hodlr_solve_noalloc",
            "hodlr_solve_noalloc_bytes", "hodlr_matvec", "hodlr_grad", "hodlr_logdet", "hodlr_logdet_grad",
            "hodlr_factors_y", "hodlr_factor_bytes", "hodlr_destroy", "hodlr_status_string", "hodlr_timing_enable",
-           "hodlr_kernel_times", "hodlr_construct"]
+           "hodlr_kernel_times", "hodlr_construct", "hodlr_release_memory"]
 
 _lib = None
 
@@ -96,6 +96,8 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.hodlr_factor_bytes.restype = ctypes.c_size_t
     lib.hodlr_destroy.argtypes = [vp]
     lib.hodlr_destroy.restype = None
+    lib.hodlr_release_memory.argtypes = []
+    lib.hodlr_release_memory.restype = None
     lib.hodlr_status_string.argtypes = [ctypes.c_int]
     lib.hodlr_status_string.restype = ctypes.c_char_p
     lib.hodlr_timing_enable.argtypes = [i32]
@@ -417,6 +419,11 @@ def kernel_times(reset: bool = False) -> dict:
     cnt = (ctypes.c_int64 * cap)()
     k = lib.hodlr_kernel_times(names, ms, cnt, cap)
     return {names[i].decode(): (ms[i], cnt[i]) for i in range(min(k, cap))}
+
+
+def release_memory():
+    """Free the device memory of released factorizations that the library keeps for the next ones."""
+    load_library().hodlr_release_memory()
 
 
 def timing(enable: bool):

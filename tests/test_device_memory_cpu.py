@@ -170,3 +170,15 @@ def test_release_waits_for_replays_of_recorded_calls(lib, through):
     frees = lib.mock_frees()
     lib.hodlr_destroy(h)
     assert lib.mock_graph_work() == 0 and lib.mock_frees() == frees
+
+
+def test_kept_blocks_are_given_back_on_request(lib):
+    a, na = _bytes(lib, 4096, 64, 16)
+    b, nb = _bytes(lib, 1024, 64, 8)
+    lib.hodlr_destroy(a)
+    assert lib.mock_used() == na + nb
+    lib.hodlr_release_memory()
+    assert lib.mock_used() == nb  # what has an owner stays
+    lib.hodlr_destroy(b)
+    lib.hodlr_release_memory()
+    assert lib.mock_used() == 0
