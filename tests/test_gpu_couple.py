@@ -65,3 +65,30 @@ def test_singular_coupling_reported(t, column):
     with pytest.raises(hodlr.HodlrError) as e:
         hodlr.factor(A, "fp64")
     assert e.value.info == dict(level=0, node=0, column=column)
+
+
+@pytest.mark.parametrize("what", ["solve", "wide", "adjoint", "slogdet"])
+@pytest.mark.parametrize("rank", [8, 16, 24, 32, 40, 48, 56, 64])
+def test_uncorrected_ranks_at_scale_40(rank, what):
+    """Multiples of 8, whose products with K^{-1} are not corrected, where |V^T Y|
+    reaches 700 and cond(K) 3e5: 1e-8 of x, a hundredth of the cond(K)^2 unit
+    roundoffs that such a product may cost at ranks 32 and 64 (1e-6 and 9e-6).
+    (The one-column-at-a-time elimination before this one: 1.2e-9 and 3e-10 of x,
+    this one 3e-10 and 1e-9; over 16 matrices each the two scatter about the same
+    error.)  The determinant comes from the pivots and keeps the bar of the others."""
+    from paper_2208_06290_amd import hodlr
+    inp = W.synthetic(1024, 128, [rank] * 3, seed=rank)
+    inp.U, inp.V = inp.U * 40.0, inp.V * 40.0
+    H = O.from_inputs(inp)
+    B = np.random.default_rng(rank).standard_normal((H.N, 20 if what == "wide" else 3))
+    b = torch.as_tensor(np.ascontiguousarray(B.T), device=DEV)
+    F = hodlr.factor(hodlr.HODLRMatrix.from_inputs(inp.to(DEV)), "fp64")
+    if what == "slogdet":
+        A = O.assemble_dense(H)
+        so, lo = np.linalg.slogdet(A)
+        sign, logabs = F.slogdet()
+        assert sign == so and abs(logabs - lo) < 100 * np.linalg.cond(A) * 2.0 ** -53 * max(1.0, abs(lo))
+    elif what == "adjoint":
+        assert _rel(F.solve_adjoint(b).cpu().numpy().T, O.solve_adjoint(H, B)) < 1e-8
+    else:
+        assert _rel(F.solve(b).cpu().numpy().T, O.solve(O.factor(H), B)) < 1e-8
