@@ -182,3 +182,24 @@ def test_kept_blocks_are_given_back_on_request(lib):
     lib.hodlr_destroy(b)
     lib.hodlr_release_memory()
     assert lib.mock_used() == 0
+
+
+@pytest.mark.parametrize("call", ["solve", "adjoint", "noalloc", "grad", "y_big", "y_big complex", "logdet", "logdet_grad"])
+def test_release_waits_for_the_last_call_on_every_stream(lib, call):
+    st, h = _factor(lib, _matrix(1024, 64, 8, 3 if "complex" in call else 0), S1)
+    n, ld, X = ctypes.c_int64(2), ctypes.c_int64(1024), ctypes.c_void_p(FAKE)
+    d = ctypes.c_double()
+    assert st == 0
+    for s in (S1, S2):
+        assert 0 == {"solve": lambda: lib.hodlr_solve(h, n, X, ld, None, s, None),
+                     "adjoint": lambda: lib.hodlr_solve_adjoint(h, n, X, ld, None, s, None),
+                     "noalloc": lambda: lib.hodlr_solve_noalloc(h, 1, n, X, ld, s),
+                     "grad": lambda: lib.hodlr_grad(h, n, X, ld, X, ld, X, X, X, s),
+                     "y_big": lambda: lib.hodlr_factors_y(h, X, ld, s),
+                     "y_big complex": lambda: lib.hodlr_factors_y(h, X, ld, s),
+                     "logdet": lambda: lib.hodlr_logdet(h, ctypes.byref(d), ctypes.byref(d), s),
+                     "logdet_grad": lambda: lib.hodlr_logdet_grad(h, X, X, X, s)}[call]()
+    lib.hodlr_destroy(h)
+    assert lib.mock_pending(S2) == 0
+    if call != "noalloc":  # one scratch, whose calls the caller orders: the last one is waited for
+        assert lib.mock_pending(S1) == 0

@@ -75,3 +75,28 @@ def test_release_waits_for_y_big():
         assert _err(x, want) < 1e-12
         torch.cuda.synchronize()
         assert _err(Y.cpu().numpy().T, ref) < 1e-12
+
+
+def test_y_big_queued_at_release_is_not_overwritten():
+    """The factorization is released while work in front of Y_big is still
+    running; a problem of the same size takes its blocks on another stream."""
+    from paper_2208_06290_amd import hodlr
+    inp, _, _ = _problem(2)
+    ref = O.y_big(O.factor(O.from_inputs(inp)))
+    A = hodlr.HODLRMatrix.from_inputs(inp.to(DEV))
+    B = hodlr.HODLRMatrix(A.D.clone(), 3.0 * A.U, A.V.clone(), A.ranks)
+    ahead = torch.randn(4096, 4096, device=DEV)
+    torch.cuda.synchronize()
+    s, t = torch.cuda.Stream(), torch.cuda.Stream()
+    for _ in range(4):
+        with torch.cuda.stream(s):
+            F = hodlr.factor(A, "fp64")
+            for _ in range(40):  # some milliseconds
+                ahead = (ahead @ ahead).clamp_(-1.0, 1.0)
+            Y = F.y_big()
+            del F
+        with torch.cuda.stream(t):
+            G = hodlr.factor(B, "fp64")
+        torch.cuda.synchronize()
+        assert _err(Y.cpu().numpy().T, ref) < 1e-12
+        del G
