@@ -506,15 +506,14 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 1) void couple_factor_kernel
     return;
   }
   // W = K^{-1} rhs: wave w takes the column blocks w, w + NW, ..; row blocks
-  // 0 .. nt - 1 are the first child's, nt .. 2 nt - 1 the second's
-  const bool vec = r % 4 == 0;
+  // 0 .. nt - 1 are the first child's, nt .. 2 nt - 1 the second's (r % 8 = 0 here)
   T* Wg = W + (int64_t)g * n2 * Rp;
   for (int c0 = 16 * w; c0 < Rp; c0 += 16 * NW) {
     const int64_t c = min(c0 + li, Rp - 1);
     T bv[NB][4];
 #pragma unroll
     for (int q = 0; q < NB; ++q)
-      if (q < 2 * nt) load_col4((q < nt ? Pa : Pb) + c * r, r, 16 * (q < nt ? q : q - nt) + 4 * lq, vec, bv[q]);
+      if (q < 2 * nt) load_col4((q < nt ? Pa : Pb) + c * r, r, 16 * (q < nt ? q : q - nt) + 4 * lq, true, bv[q]);
 #pragma unroll 2
     for (int rb = 0; rb < 2 * nt; ++rb) {
       V acc = vzero<V>();
@@ -526,7 +525,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 1) void couple_factor_kernel
             acc = M::mma(K[16 * rb + row4_of_lane<T>(li) + (16 * q + 4 * lq + s) * ldk], bv[q][s], acc);
         }
       if (c0 + li < Rp)
-        store_col4(Wg + c * n2 + (rb < nt ? 0 : r), r, 16 * (rb < nt ? rb : rb - nt) + 4 * lq, vec, acc);
+        store_col4(Wg + c * n2 + (rb < nt ? 0 : r), r, 16 * (rb < nt ? rb : rb - nt) + 4 * lq, true, acc);
     }
   }
 }

@@ -124,8 +124,7 @@ __global__ __launch_bounds__(NT, (lp_occupancy<TZ, NCB, FULL>())) void level_pas
   // W chunk to LDS, negated: element (k, c) of the chunk, k = 16 g + 4 q + s, in slot s of
   // lane 16 q + c % 16 of fragment (g, c / 16)
   if constexpr (CPL > 0) {
-    const int nd = tl.node >> node_shift, half = nd & 1, nt = ng, r = ka;
-    const bool vec = r % 4 == 0;
+    const int nd = tl.node >> node_shift, half = nd & 1, nt = ng, r = ka;  // r % 8 = 0
     // K^{-1} rows of this wave's block (half r + 16 w + row), all columns
     const TZ* Kg = cpl.Kinv + (int64_t)(nd >> 1) * cpl.kp * cpl.kp;
     const int row = half * r + min(16 * w + (sizeof(TZ) == 8 ? 4 * (li & 3) + (li >> 2) : li), r - 1);
@@ -152,12 +151,7 @@ __global__ __launch_bounds__(NT, (lp_occupancy<TZ, NCB, FULL>())) void level_pas
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
             const TZ* col = cpl.items + ((int64_t)min(it + u, i1 - 1) * nz + c) * r;
-            if (vec) {
-              load_run(col + i0, v[u]);
-            } else {
-#pragma unroll
-              for (int t = 0; t < 4; ++t) v[u][t] = i0 + t < r ? col[min(i0 + t, r - 1)] : TZ(0);
-            }
+            load_run(col + i0, v[u]);
           }
 #pragma unroll
           for (int u = 0; u < 4; ++u)
@@ -940,7 +934,7 @@ hipError_t launch_coupled_pass(hipStream_t s, int trans, int ntiles, const Tile*
                                const TZ* items, const int32_t* d_start, int node_shift, const SB* B1, int64_t ldb,
                                int kb, TZ* P, GroupStrides gs) {
   if (ntiles == 0 || nz == 0) return hipSuccess;
-  if (r < 1 || r > 64 || kp < 2 * r || nz > 16 || sh.rows < 1 || sh.rows > kTileRows) return hipErrorInvalidValue;
+  if (r < 1 || r > 64 || r % 8 || kp < 2 * r || nz > 16 || sh.rows < 1 || sh.rows > kTileRows) return hipErrorInvalidValue;
   constexpr int kCw = 16;
   const int nt = (r + 15) / 16;
   const size_t part = std::max(sizeof(TZ) * 4 * 16 * kCw, sizeof(TZ) * kCw * 16 * nt);  // W, or a reduction buffer
