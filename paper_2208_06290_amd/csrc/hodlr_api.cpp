@@ -791,11 +791,15 @@ Workspace* get_ws(hodlr_factors* F, hipStream_t st) {
 // Most columns of a solve whose passes form W themselves; most item columns a
 // workgroup sums for that (a node's tiles times right-hand sides, read by every
 // workgroup of the level): beyond, the reduction comes first.  Most tiles of
-// such a pass: every workgroup reads K^{-1} of its parent, a quarter of its own
-// bytes, which costs what the launches saved once the chip is full (FP64, rank
-// 32, one column, with and without: N = 16384 98 and 118 us, 65536 154 and 186,
-// 262144 503 and 551, 524288 953 and 980, 1048576 the same or slower; FP32
-// adjoint, 524288: 906 and 893).
+// such a pass: every workgroup reads K^{-1} of its parent, r x 2r, besides the 2r
+// columns of its tile's rows, so r / rows of its own bytes again (a quarter at
+// rank 64 on 256 rows, three quarters at rank 48 on 64), mostly from L2.  That is
+// cheap while the chip is not full and costs what the launches saved once it is.
+// Time without the fused coupling solves over time with them, FP64 and FP32, both
+// directions, 1, 4 and 16 columns, leaves of 64 to 256 rows, ranks 8 to 64: N = 2^14
+// 1.15 .. 1.56; 2^16 1.13 .. 1.38; 2^17 1.07 .. 1.26; 2^18 (256-row tiles of
+// N = 2^18 are 1024) 1.02 .. 1.20, but for FP32 adjoints of rank 48 and 64, 0.98 ..
+// 1.03; 2^19 (2048) 0.99 .. 1.07 up to rank 32, 0.94 .. 1.03 above.
 constexpr int kNarrow = 16;
 constexpr int kCplLoads = 32;
 constexpr int kCplTiles = 1024;
