@@ -62,7 +62,8 @@ constexpr int lp_occupancy() {
 //
 // FULL: the tile heights are multiples of 64, so a wave has 64 rows or none;
 // otherwise a wave with fewer reads its last row in the place of those past
-// the end, zeroes them in B1 and never stores them.  K is padded with zero rows of
+// the end, never stores them, and zeroes them in B1 and Z before the product (an
+// infinity in the last row would make the sums of its column NaN).  K is padded with zero rows of
 // W (A1 re-reads its last column).  Columns past nz and B1 columns past kb
 // re-read the last one; their results are not stored.
 //
@@ -347,6 +348,18 @@ __global__ __launch_bounds__(NT, (lp_occupancy<TZ, NCB, FULL>())) void level_pas
     }
 
     if (kb_total > 0) {
+      if constexpr (!whole) {
+#pragma unroll
+        for (int rg = 0; rg < NG; ++rg)
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int h = 0; h < RP; ++h)
+              if (kGr * rg + 4 * RP * t + RP * lq + h > last) {
+#pragma unroll
+                for (int cb = 0; cb < NCB; ++cb) acc[RP * rg + h][cb][t] = TZ(0);
+              }
+      }
       // 16 rows of P at a time; the waves' partials go to one of two LDS
       // buffers in turn (the second takes the place of W, which no wave reads
       // after the first barrier), so one barrier separates two steps

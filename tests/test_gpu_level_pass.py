@@ -79,3 +79,21 @@ def test_narrow_levels_of_several_tiles(ranks, nrhs):
         F = hodlr.factor(hodlr.HODLRMatrix.from_inputs(inp.to(DEV)), "fp64")
         assert _rel(F.solve(b).cpu().numpy().T, O.solve(O.factor(H), B)) < 1e-12
         assert _rel(F.solve_adjoint(b).cpu().numpy().T, O.solve_adjoint(H, B)) < 1e-12
+
+
+@pytest.mark.parametrize("name", ["65_63", "129_127", "192", "96_32", "16"])
+def test_infinity_in_the_last_row_of_a_tile(name):
+    """One infinite entry of x in the last row of a leaf: the products of the other
+    leaves with it are infinite where the oracle's are, not NaN (generators of one
+    sign, so that no sum cancels)."""
+    hodlr, H, A = _case(name)
+    A.U.abs_(), A.V.abs_()
+    H = O.Hodlr(H.offsets, H.ranks, A.D.cpu().numpy().T, A.U.cpu().numpy().T, A.V.cpu().numpy().T)
+    x = np.abs(np.random.default_rng(1).standard_normal((H.N, 1)))
+    for a in (0, 2, 5):
+        xi = x.copy()
+        xi[H.offsets[a + 1] - 1] = np.inf
+        got = A.matvec(torch.as_tensor(np.ascontiguousarray(xi.T), device=DEV)).cpu().numpy().T
+        out = np.ones(H.N, bool)
+        out[H.offsets[a]:H.offsets[a + 1]] = False  # the leaf itself: D has both signs
+        assert np.isinf(O.matvec(H, xi)[out]).all() and (got[out] == np.inf).all(), a
