@@ -800,36 +800,39 @@ static hipError_t launch_block_part(hipStream_t s, int ntiles, int zchunks, int 
   return hipGetLastError();
 }
 
-// The first nblk 16-column blocks of Z: chunks of 64 columns, then the blocks
+// The first nblk 16-column blocks of Z: chunks of zw blocks (4; 2 or 1 where the
+// leading dimension is too large for the offsets inside one), then the blocks
 // that are left as one narrower chunk.
 template <typename TZ, typename SA, typename SB, int MB, int NKS, int RP, bool BF = false>
-static hipError_t launch_block_chunks(hipStream_t s, int ntiles, int nblk, int nz, int bchunks, const Tile* tiles,
-                                      TZ* Z, int64_t ldz, const SA* A1, int64_t lda, const TZ* W, int64_t w_ld,
-                                      int64_t w_pstride, int node_shift, const SB* B1, int64_t ldb, int kb, TZ* P,
-                                      GroupStrides gs) {
-  const int n64 = nblk / 4, nb = nblk % 4;
-  hipError_t e = launch_block_part<TZ, SA, SB, MB, NKS, 4, RP, BF>(s, ntiles, n64, 0, nz, bchunks, tiles, Z, ldz, A1,
-                                                                   lda, W, w_ld, w_pstride, node_shift, B1, ldb, kb, P,
-                                                                   gs);
+static hipError_t launch_block_chunks(hipStream_t s, int ntiles, int nblk, int zw, int nz, int bchunks,
+                                      const Tile* tiles, TZ* Z, int64_t ldz, const SA* A1, int64_t lda, const TZ* W,
+                                      int64_t w_ld, int64_t w_pstride, int node_shift, const SB* B1, int64_t ldb, int kb,
+                                      TZ* P, GroupStrides gs) {
+  const int n = nblk / zw, nb = nblk % zw;
+  hipError_t e = hipSuccess;
+#define HODLR_LPB(NCBV, CHUNKS, BASE)                                                                              \
+  e = launch_block_part<TZ, SA, SB, MB, NKS, NCBV, RP, BF>(s, ntiles, CHUNKS, BASE, nz, bchunks, tiles, Z, ldz, A1, lda, \
+                                                           W, w_ld, w_pstride, node_shift, B1, ldb, kb, P, gs)
+  if (zw == 4) HODLR_LPB(4, n, 0);
+  else if (zw == 2) HODLR_LPB(2, n, 0);
+  else HODLR_LPB(1, n, 0);
   if (e != hipSuccess) return e;
-#define HODLR_LPB(NCBV)                                                                                            \
-  return launch_block_part<TZ, SA, SB, MB, NKS, NCBV, RP, BF>(s, ntiles, 1, 64 * n64, nz, bchunks, tiles, Z, ldz, A1,   \
-                                                          lda, W, w_ld, w_pstride, node_shift, B1, ldb, kb, P, gs)
-  if (nb == 1) HODLR_LPB(1);
-  if (nb == 2) HODLR_LPB(2);
-  if (nb == 3) HODLR_LPB(3);
+  const int base = 16 * zw * n;
+  if (nb == 1) HODLR_LPB(1, 1, base);
+  if (nb == 2) HODLR_LPB(2, 1, base);
+  if (nb == 3) HODLR_LPB(3, 1, base);
 #undef HODLR_LPB
   return e;
 }
 
 template <typename TZ, typename SA, typename SB, int MB, int RP>
-static hipError_t launch_block_nks(int nks, hipStream_t s, int ntiles, int nblk, int nz, int bchunks,
+static hipError_t launch_block_nks(int nks, hipStream_t s, int ntiles, int nblk, int zw, int nz, int bchunks,
                                    const Tile* tiles, TZ* Z, int64_t ldz, const SA* A1, int64_t lda, const TZ* W,
                                    int64_t w_ld, int64_t w_pstride, int node_shift, const SB* B1, int64_t ldb, int kb,
                                    TZ* P, GroupStrides gs) {
 #define HODLR_LPF(NKSV)                                                                                            \
-  return launch_block_chunks<TZ, SA, SB, MB, NKSV, RP>(s, ntiles, nblk, nz, bchunks, tiles, Z, ldz, A1, lda, W, w_ld, \
-                                                       w_pstride, node_shift, B1, ldb, kb, P, gs)
+  return launch_block_chunks<TZ, SA, SB, MB, NKSV, RP>(s, ntiles, nblk, zw, nz, bchunks, tiles, Z, ldz, A1, lda, W,  \
+                                                       w_ld, w_pstride, node_shift, B1, ldb, kb, P, gs)
   switch (nks) {
     case 0: HODLR_LPF(0);
     case 4: HODLR_LPF(4);
@@ -841,13 +844,13 @@ static hipError_t launch_block_nks(int nks, hipStream_t s, int ntiles, int nblk,
 }
 
 template <typename TZ, typename SA, typename SB, int RP>
-static hipError_t launch_block(hipStream_t s, int ntiles, const Tile* tiles, TZ* Z, int64_t ldz, int nblk, int nz,
-                               const SA* A1, int64_t lda, int ka, const TZ* W, int64_t w_ld, int64_t w_pstride,
+static hipError_t launch_block(hipStream_t s, int ntiles, const Tile* tiles, TZ* Z, int64_t ldz, int nblk, int zw, int nz,
+                                const SA* A1, int64_t lda, int ka, const TZ* W, int64_t w_ld, int64_t w_pstride,
                                int node_shift, const SB* B1, int64_t ldb, int kb, TZ* P, GroupStrides gs) {
   const int bchunks = kb > 0 ? (kb + 63) / 64 : 1;
 #define HODLR_LPM(MBV)                                                                                              \
-  return launch_block_nks<TZ, SA, SB, MBV, RP>(ka / 4, s, ntiles, nblk, nz, bchunks, tiles, Z, ldz, A1, lda, W, w_ld, \
-                                               w_pstride, node_shift, B1, ldb, kb, P, gs)
+  return launch_block_nks<TZ, SA, SB, MBV, RP>(ka / 4, s, ntiles, nblk, zw, nz, bchunks, tiles, Z, ldz, A1, lda, W,   \
+                                               w_ld, w_pstride, node_shift, B1, ldb, kb, P, gs)
   switch (kb > 0 ? std::min(kb, 64) / 16 : 0) {
     case 0: HODLR_LPM(0);
     case 1: HODLR_LPM(1);
@@ -864,7 +867,7 @@ static hipError_t launch_block_bf(hipStream_t s, int ntiles, const Tile* tiles, 
                                   const SA* A1, int64_t lda, int ka, const TZ* W, int64_t w_ld, int64_t w_pstride,
                                   int node_shift, const SB* B1, int64_t ldb, int kb, TZ* P, GroupStrides gs) {
 #define HODLR_LPX(MBV, NKSV)                                                                                       \
-  return launch_block_chunks<TZ, SA, SB, MBV, NKSV, 2, true>(s, ntiles, nblk, nz, 1, tiles, Z, ldz, A1, lda, W, w_ld, \
+  return launch_block_chunks<TZ, SA, SB, MBV, NKSV, 2, true>(s, ntiles, nblk, 4, nz, 1, tiles, Z, ldz, A1, lda, W, w_ld, \
                                                              w_pstride, node_shift, B1, ldb, kb, P, gs)
 #define HODLR_LPY(MBV)               \
   if (ka == 0) HODLR_LPX(MBV, 0);    \
@@ -884,9 +887,18 @@ hipError_t launch_level_pass(hipStream_t s, int ntiles, const Tile* tiles, TileS
   if (ntiles == 0 || nz == 0 || (ka == 0 && kb == 0)) return hipSuccess;
   if (ka > 64 || sh.rows < 1 || sh.rows > kTileRows) return hipErrorInvalidValue;
   // whole 16 x 16 x 16 blocks, and byte offsets inside a 64-column chunk below
-  // 2^31 (the buffer addressing of the blocked kernel)
-  const bool blocks = sh.mult(16) && ka % 16 == 0 && kb % 16 == 0 && 64 * ldz * (int64_t)sizeof(TZ) < (1ll << 31) &&
-                      64 * lda * (int64_t)sizeof(SA) < (1ll << 31) && 64 * ldb * (int64_t)sizeof(SB) < (1ll << 31);
+  // 2^31 (the buffer addressing of the blocked kernel).  Products alone, of whole
+  // blocks of Z, may take narrower chunks of it (N = 2^22, rank 64 in FP32: 32 FP64 columns
+  // 7.0 ms, 64 12.4; the row kernel 8.3 and 15.7; FP64, rank 32, 64 columns: 7.9 and
+  // 8.7); with columns left over, which read all of B1 again, the row kernel is
+  // faster (17 columns: 4.0 ms, 6.7 with the blocked kernel)
+  auto bytes64 = [](int64_t ld, size_t size) { return 64 * ld * (int64_t)size; };
+  constexpr int64_t kReach = 1ll << 31;
+  const int64_t bz = bytes64(ldz, sizeof(TZ)), bb = bytes64(ldb, sizeof(SB));
+  const bool small_ld = bz < kReach && bb < kReach && bytes64(lda, sizeof(SA)) < kReach;
+  const int zw = bz <= kReach ? 4 : bz <= 2 * kReach ? 2 : 1;  // 16-column blocks of a chunk
+  const bool blocks = sh.mult(16) && ka % 16 == 0 && kb % 16 == 0 &&
+                      (small_ld || (ka == 0 && nz % 16 == 0 && bz <= 4 * kReach && bb <= kReach));
   int c_base = 0;
   if (blocks) {
     // 4-byte elements, tile heights multiples of 32, even leading dimensions
@@ -904,7 +916,7 @@ hipError_t launch_level_pass(hipStream_t s, int ntiles, const Tile* tiles, TileS
     // faster (N = 2^20, rank 32: 5.32 against 6.06 ms; N = 2^18, leaf 128: 1.23, 1.26)
     if constexpr (sizeof(TZ) == 4 && std::is_same<SA, TZ>::value) {
       if (bf) {
-        if (pair && ka <= 32 && kb <= 32 && sh.rows > 64 && nz > 16) {
+        if (pair && ka <= 32 && kb <= 32 && sh.rows > 64 && nz > 16 && zw == 4) {
           c_base = nz / 16 * 16;
           const hipError_t e = launch_block_bf<TZ, SA, SB>(s, ntiles, tiles, Z, ldz, nz / 16, nz, A1, lda, ka, W, w_ld,
                                                            w_pstride, node_shift, B1, ldb, kb, P, gs);
@@ -925,13 +937,13 @@ hipError_t launch_level_pass(hipStream_t s, int ntiles, const Tile* tiles, TileS
       bool done = false;
       if constexpr (sizeof(TZ) == 4) {
         if (pair) {
-          e = launch_block<TZ, SA, SB, 2>(s, ntiles, tiles, Z, ldz, nz / 16, nz, A1, lda, ka, W, w_ld, w_pstride,
+          e = launch_block<TZ, SA, SB, 2>(s, ntiles, tiles, Z, ldz, nz / 16, zw, nz, A1, lda, ka, W, w_ld, w_pstride,
                                           node_shift, B1, ldb, kb, P, gs);
           done = true;
         }
       }
       if (!done)
-        e = launch_block<TZ, SA, SB, 1>(s, ntiles, tiles, Z, ldz, nz / 16, nz, A1, lda, ka, W, w_ld, w_pstride,
+        e = launch_block<TZ, SA, SB, 1>(s, ntiles, tiles, Z, ldz, nz / 16, zw, nz, A1, lda, ka, W, w_ld, w_pstride,
                                         node_shift, B1, ldb, kb, P, gs);
       if (e != hipSuccess || c_base == nz) return e;
     }

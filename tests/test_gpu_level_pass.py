@@ -97,3 +97,29 @@ def test_infinity_in_the_last_row_of_a_tile(name):
         out = np.ones(H.N, bool)
         out[H.offsets[a]:H.offsets[a + 1]] = False  # the leaf itself: D has both signs
         assert np.isinf(O.matvec(H, xi)[out]).all() and (got[out] == np.inf).all(), a
+
+
+@pytest.mark.parametrize("nrhs", [17, 48, 64, 81])
+@pytest.mark.parametrize("ldx,ldv", [(1 << 22, 1 << 22), ((1 << 22) + 2, 2048), (2048, (1 << 22) + 2), (1 << 23, 1 << 23),
+                                     ((1 << 23) + 2, (1 << 23) + 2), (1 << 24, 1 << 24), ((1 << 24) + 2, (1 << 24) + 2)])
+def test_products_with_large_leading_dimensions(ldx, ldv, nrhs):
+    """64, 32 and 16 columns of x, U and V within the 2^31 bytes that an offset
+    reaches, one element more, and none."""
+    import ctypes
+    hodlr, H, A = _case("256")
+    ranks, n = [16, 64, 32], H.N
+    inp = W.synthetic(n, 256, ranks, seed=4)
+    H = O.from_inputs(inp)
+
+    def spread(t, ld):
+        s = torch.empty(t.shape[0], ld, dtype=t.dtype, device=DEV)[:, :n]
+        return s.copy_(t)
+
+    A = hodlr.HODLRMatrix(inp.D.to(DEV), spread(inp.U, ldv), spread(inp.V, ldv), ranks)
+    x = torch.as_tensor(np.random.default_rng(nrhs).standard_normal((nrhs, n)))
+    X, Y = spread(x, ldx), torch.empty(nrhs, n, dtype=torch.float64, device=DEV)
+    m = A.c_struct()
+    st = hodlr.load_library().hodlr_matvec(ctypes.byref(m), 0, nrhs, X.data_ptr(), ldx, Y.data_ptr(), n,
+                                           ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert st == 0
+    assert _rel(Y.cpu().numpy().T, O.matvec(H, x.numpy().T)) < 1e-12
