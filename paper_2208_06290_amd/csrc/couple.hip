@@ -366,7 +366,8 @@ __device__ __forceinline__ void gj_invert(T* K, int ldk, int n, int nid, int tid
 // 2h = 64, 8 up to 128.  W = K^{-1} rhs then streams 16 columns per wave from
 // and to memory, K^{-1} read from LDS.
 // (Ranks that correct their products, couple_corrects, leave W to
-// couple_apply_kernel and keep T_a and T_b in Kt for it: W is null.)
+// couple_apply_kernel and keep T_a and T_b in Kt for it.  W is null where no
+// level has columns above it, Kt where no rank corrects.)
 template <typename T, int NW>
 __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 1) void couple_factor_kernel(
     int r, int kp, int Rp, const T* __restrict__ segs, const int32_t* __restrict__ seg_start, T* __restrict__ Kinv,
@@ -497,7 +498,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 1) void couple_factor_kernel
     const int i = e.k < r ? e.k : e.k + h - r, j = e.c < r ? e.c : e.c + h - r;
     Kg[e.k + e.c * kp] = e.k < n2 && e.c < n2 ? K[i + j * ldk] : T(0);
   }
-  if (!W) {
+  if (couple_corrects(r)) {
     T* Tg = Kt + (int64_t)g * 2 * r * r;
     for (int e = tid; e < r * r; e += NT) {
       Tg[e] = Pa[(int64_t)Rp * r + e];
@@ -706,14 +707,13 @@ hipError_t launch_couple_factor(hipStream_t s, int nparents, int r, int kp, int 
   const int n = 2 * ((r + 15) & ~15);
   if (n > kCfMaxRows || kp < 2 * r || kp > n) return hipErrorInvalidValue;
   const size_t smem = sizeof(T) * (size_t)n * (n + 1);
-  T* const Wf = couple_corrects(r) ? nullptr : W;
 #define HODLR_CF(NW)                                                                                              \
   {                                                                                                               \
     auto k = couple_factor_kernel<T, NW>;                                                                         \
     hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);      \
     if (e != hipSuccess) return e;                                                                                \
     hipLaunchKernelGGL(k, dim3(nparents), dim3(64 * NW), smem, s, r, kp, Rp, segs, d_seg_start, Kinv, Kpiv, Kud, Kt, \
-                       Wf, info, level, L);                                                                       \
+                       W, info, level, L);                                                                        \
   }
   if (n <= 64) HODLR_CF(4) else HODLR_CF(8)
 #undef HODLR_CF

@@ -92,3 +92,25 @@ def test_uncorrected_ranks_at_scale_40(rank, what):
         assert _rel(F.solve_adjoint(b).cpu().numpy().T, O.solve_adjoint(H, B)) < 1e-8
     else:
         assert _rel(F.solve(b).cpu().numpy().T, O.solve(O.factor(H), B)) < 1e-8
+
+
+@pytest.mark.parametrize("ranks", [[8], [16], [24], [64], [16, 0], [0, 24], [12]])
+@pytest.mark.parametrize("precision,u", [("fp64", 2.0 ** -53), ("fp32", 2.0 ** -24)])
+def test_no_columns_above(ranks, precision, u):
+    """One level of a rank above zero: its coupling systems have no right-hand
+    sides (W is empty), and no rank that corrects its products keeps them."""
+    from paper_2208_06290_amd import hodlr
+    inp = W.synthetic(128 << len(ranks), 128, ranks, seed=sum(ranks))
+    H = O.from_inputs(inp)
+    Ho = O.factor(H)
+    A = O.assemble_dense(H)
+    bar = 100 * np.linalg.cond(A) * u
+    B = np.random.default_rng(1).standard_normal((H.N, 20))
+    b = torch.as_tensor(np.ascontiguousarray(B.T), device=DEV)
+    F = hodlr.factor(hodlr.HODLRMatrix.from_inputs(inp.to(DEV)), precision)
+    for k in (1, 20):
+        assert _rel(F.solve(b[:k]).cpu().numpy().T, O.solve(Ho, B[:, :k])) < bar
+        assert _rel(F.solve_adjoint(b[:k]).cpu().numpy().T, O.solve_adjoint(H, B[:, :k])) < bar
+    sign, logabs = F.slogdet()
+    so, lo = np.linalg.slogdet(A)
+    assert sign == so and abs(logabs - lo) < bar * max(1.0, abs(lo))
