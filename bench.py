@@ -39,16 +39,17 @@ PEAK = dict(hbm=8.0e12, f64=78.6e12, f32=157.3e12, bf16=2.5e15)
 # and profiles/counters_n1m_synthetic_fp64_fp32_bf16.md).
 # It is reported only while the kernel source is the one it was measured on.
 LEVEL_PASS_TRAFFIC = dict(
-    source_sha256="000a3cfbe028865a382020c1e736d879689e56ac5eadf5b6fe90b1f86aea5e5b",
-    n=1 << 20, leaf=256, rank=32, bytes_per_launch=4.2646e9)
+    source_sha256="b3c368642fed5bfd79d9c5bdf4b9598cec474284d5b7ce06521841a721835a05",
+    n=1 << 20, leaf=256, rank=32, bytes_per_launch=4.2618e9)
 
-# HBM traffic of one cross-approximation step (row + column launch) of the
-# construction of the double-layer matrix at N = 2^20, leaf 256, rank 32, from
-# the same two counter runs and copy calibration (summary and commands in
+# HBM traffic of one cross-approximation step (row + column launch, levels with
+# blocks above 512 rows) of the construction of the double-layer matrix at
+# N = 2^20, leaf 256, rank 32, from the same two counter runs and copy
+# calibration (summary and commands in
 # profiles/construct_aca_bie_n1m_fp64.md); reported only for that source.
 CONSTRUCT_TRAFFIC = dict(
-    source_sha256="477a0a4d62ad1017a94fabf7db84e260b0261532df6c4fee0bca09078fe1bae9",
-    n=1 << 20, leaf=256, rank=32, kind="laplace_dl", bytes_per_step=4.2422e9)
+    source_sha256="797c0bed8a2666ed855cb94fcf66d6b0f05e92a2cc6a8d385bfd2eb94204fe02",
+    n=1 << 20, leaf=256, rank=32, kind="laplace_dl", bytes_per_step=3.4975e9)
 
 
 def _say(*a):
