@@ -908,15 +908,16 @@ hipError_t launch_level_pass(hipStream_t s, int ntiles, const Tile* tiles, TileS
     const bool pair = sizeof(TZ) == 4 && sh.mult(32) && ldz % 2 == 0 && (ka == 0 || lda % 2 == 0) &&
                       (kb == 0 || ldb % 2 == 0) && al16(Z) && (ka == 0 || al16(A1)) && (kb == 0 || al16(B1));
     // bfloat16 products only where the factorization uses them (Z and A1 both
-    // Y); other shapes of a BF16 factorization are computed in FP32.  The row
+    // Y); other shapes of a BF16 factorization, and all its passes at leading
+    // dimensions beyond the buffer addressing, are computed in FP32.  The row
     // kernel moves 16 bytes a lane and nothing but W and P through LDS (N = 2^19,
     // rank 64: 5.69 ms a factorization, 6.67 ms with the turn-arounds of the
     // blocked kernel; rank 48 the same; N = 2^17, leaf 64, rank 32: 0.74 against
     // 0.79); up to rank 32 on tiles above 64 rows the blocked kernel streams
     // faster (N = 2^20, rank 32: 5.32 against 6.06 ms; N = 2^18, leaf 128: 1.23, 1.26)
     if constexpr (sizeof(TZ) == 4 && std::is_same<SA, TZ>::value) {
-      if (bf) {
-        if (pair && ka <= 32 && kb <= 32 && sh.rows > 64 && nz > 16 && zw == 4) {
+      if (bf && small_ld) {
+        if (pair && ka <= 32 && kb <= 32 && sh.rows > 64 && nz > 16) {
           c_base = nz / 16 * 16;
           const hipError_t e = launch_block_bf<TZ, SA, SB>(s, ntiles, tiles, Z, ldz, nz / 16, nz, A1, lda, ka, W, w_ld,
                                                            w_pstride, node_shift, B1, ldb, kb, P, gs);

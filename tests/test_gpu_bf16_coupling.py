@@ -90,3 +90,17 @@ def test_updates(name, store):
     A = hodlr.HODLRMatrix(inp.D.to(DEV, store), inp.U.to(DEV, store), inp.V.to(DEV, store), inp.ranks, off)
     got = hodlr.factor(A, "bf16").y_big().cpu().numpy().T[:, :Y.shape[1]]
     assert np.linalg.norm(got - Y) < bar * size
+
+
+@pytest.mark.gpu
+def test_long_leading_dimension_in_fp32(monkeypatch):
+    """Where 64 columns of V reach 2^31 bytes, the products of a BF16 factorization
+    are FP32 ones like its updates; with leaves of 32 rows nothing else of it
+    takes bfloat16 operands.  A hundredth of what rounding them would give."""
+    from paper_2208_06290_amd import hodlr
+    monkeypatch.setitem(SHAPES, "rows_32", (32, [16, 16, 16]))
+    inp, off, Y, size, bar = _bar("rows_32")
+    wide = torch.empty(inp.V.shape[0], 1 << 22, dtype=torch.float64, device=DEV)[:, :inp.n]
+    A = hodlr.HODLRMatrix(inp.D.to(DEV), inp.U.to(DEV), wide.copy_(inp.V), inp.ranks, off)
+    got = hodlr.factor(A, "bf16").y_big().cpu().numpy().T[:, :Y.shape[1]]
+    assert np.linalg.norm(got - Y) < bar / 400 * size
