@@ -39,8 +39,8 @@ PEAK = dict(hbm=8.0e12, f64=78.6e12, f32=157.3e12, bf16=2.5e15)
 # and profiles/counters_n1m_synthetic_fp64_fp32_bf16.md).
 # It is reported only while the kernel source is the one it was measured on.
 LEVEL_PASS_TRAFFIC = dict(
-    source_sha256="b3c368642fed5bfd79d9c5bdf4b9598cec474284d5b7ce06521841a721835a05",
-    n=1 << 20, leaf=256, rank=32, bytes_per_launch=4.2618e9)
+    source_sha256="661f5576ee325fccd36eca577c0e8808e4c8edc816bad143a76e4d884872457e",
+    n=1 << 20, leaf=256, rank=32, bytes_per_launch=4.2620e9)
 
 # HBM traffic of one cross-approximation step (row + column launch, levels with
 # blocks above 512 rows) of the construction of the double-layer matrix at
